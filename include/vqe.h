@@ -121,8 +121,8 @@ typedef struct vqe_grad_opts {
     int32_t expect_mode;   /* energy evaluation used by PARAM_SHIFT: VQE_EXPECT_* */
     int32_t n_ckpt;        /* number of checkpoint states in ckpt (ADJOINT only; may be 0) */
     int32_t chunk_passes;  /* ADJOINT: > 0 waits for the state's stream after every chunk_passes
-                              window passes of the forward and reverse sweeps (one ansatz layer
-                              is about passes / layers), so that at most that many passes of
+                              window or tile passes of the forward and reverse sweeps (one ansatz
+                              layer is about passes / layers), so that at most that many passes of
                               this evaluation are queued on the device at a time and work that
                               other threads submit on other streams starts within one chunk;
                               0 queues the whole evaluation at once; < 0 is VQE_ERR_ARG.
@@ -169,16 +169,20 @@ int vqe_state_write(vqe_state* s, uint64_t offset, uint64_t count, const void* h
  * circuit plans its fused passes: gates are grouped into windows of at most
  * 5 (interpreted kernels) or VQE_MAX_WINDOW (specialised kernels) qubits, one
  * HBM read and write of the state per window, respecting the order of every
- * gate pair that shares a qubit. */
+ * gate pair that shares a qubit.  Specialised evaluations of 14 or more
+ * qubits run wider passes, planned on first use: tiles of 12 or 13 qubits
+ * that always hold the lowest ones, staged between registers and LDS. */
 int vqe_circuit_create(int n_qubits, const vqe_gate* gates, size_t n_gates, vqe_circuit** out);
 int vqe_circuit_free(vqe_circuit* c);
 
-/* n_params = 1 + the largest param_index used (0 if none); n_passes = fused
- * state sweeps per application under the current kernel form. */
+/* n_params = 1 + the largest param_index used (0 if none); n_passes = windows
+ * of the plan under the current kernel form: the fused state sweeps per
+ * application, except that tile passes (specialised, 14 or more qubits) take
+ * fewer sweeps than this. */
 int vqe_circuit_info(const vqe_circuit* c, size_t* n_params, size_t* n_passes);
 
-/* Inspection of the fused plan that an evaluation would use now (it depends
- * on the kernel form, see vqe_set_specialize: windows of at most 5 qubits for
+/* Inspection of the plan of windows of at most VQE_MAX_WINDOW qubits, which an
+ * evaluation uses now unless it runs tile passes (it depends on the kernel form, see vqe_set_specialize: windows of at most 5 qubits for
  * interpreted kernels, VQE_MAX_WINDOW for specialised ones; the same plan for
  * both dtypes, which are only checked): pass `pass` has a window of *window
  * qubits (listed ascending in qubits[0..*window-1]; the caller provides
@@ -281,9 +285,9 @@ int vqe_apply_hamiltonian(vqe_state* psi, vqe_state* lam, const vqe_hamiltonian*
  *     (may be NULL).
  * psi is overwritten; on return it holds U(theta)|0> for PARAM_SHIFT and the
  * reference |0...0> (up to rounding) for ADJOINT, possibly with the sign -1:
- * the specialised reverse kernels un-apply rotations by angles beyond a
- * quarter turn as a half turn (a sign on psi and lam together, which the
- * gradient does not see) and three shears. */
+ * the specialised reverse kernels of states below 14 qubits un-apply
+ * rotations by angles beyond a quarter turn as a half turn (a sign on psi and
+ * lam together, which the gradient does not see) and three shears. */
 int vqe_energy_grad(vqe_state* psi, vqe_state* lam, const vqe_circuit* c,
                     const double* params, size_t n_params, const vqe_hamiltonian* h,
                     const vqe_grad_opts* opts, double* energy, double* grad);

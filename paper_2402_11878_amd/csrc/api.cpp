@@ -104,6 +104,18 @@ struct MidPlanPass {
     uint32_t gate_off, n_gates, slot_off, n_slots;
 };
 
+// Tile passes of one amplitude type (tile.cpp), made on first use.
+struct TilePlan {
+    bool ready = false;
+    int dev = -1;                        // device the kernels are loaded on
+    std::vector<PlannedPass> passes;
+    std::vector<TileKernel> k[2];        // [direction][pass]; sources dropped once loaded
+    std::vector<size_t> tab_off[2];      // first scalar of the pass in an evaluation's table
+    size_t tab_total = 0;                // scalars
+    std::vector<void*> fn[2];
+    uint32_t L = 0;                      // columns of the gradient partials, the same for every pass
+};
+
 struct vqe_circuit {
     int n = 0;
     std::vector<Gate> gates;
@@ -111,6 +123,7 @@ struct vqe_circuit {
     std::vector<BatchGate> bgates;  // gate table of the batched small-state kernel
     uint32_t n_mats = 0;            // matrices per evaluation (gates with a 2x2 matrix)
     Plan plan[2];  // [0]: interpreted (not built for circuits with excitation gates), [1]: specialised
+    TilePlan tile[2];  // per dtype (0: complex64, 1: complex128)
     bool has_excitation = false;
     // batched mid-size form (kMidWin < n <= kMidMaxQubits)
     std::vector<MidPlanPass> mid;
@@ -533,10 +546,11 @@ void plan_hwin(vqe_hamiltonian* h) {
 
 // Per-block partial-sum buffer of a state: room for the largest launch
 // (kMaxPartBlocks blocks x kMaxGradSlots slots).
+size_t part_doubles() { return std::max((size_t)kMaxPartBlocks * kMaxGradSlots, (size_t)kMaxBlocks * 2); }
+
 int ensure_part(vqe_state* s) {
     if (s->d_part) return VQE_OK;
-    const size_t count = std::max((size_t)kMaxPartBlocks * kMaxGradSlots, (size_t)kMaxBlocks * 2);
-    if (hipMalloc((void**)&s->d_part, count * sizeof(double)) != hipSuccess) {
+    if (hipMalloc((void**)&s->d_part, part_doubles() * sizeof(double)) != hipSuccess) {
         s->d_part = nullptr;
         set_error("hipMalloc of the partial-sum buffer failed");
         return VQE_ERR_OOM;
@@ -780,9 +794,57 @@ int ensure_jit(const vqe_circuit* c, const Plan& cpl, int d) {
     return VQE_OK;
 }
 
-// Fills the matrix table of a specialised plan (every pass, both directions)
-// for these parameters and uploads it on the state's stream.  The pinned
-// staging buffer is reused only after its previous upload has completed.
+// True if evaluations of c run tile passes: the specialised form from
+// kTileMinQubits qubits on (below, a tile would leave most of the chip idle;
+// the 7-qubit window passes remain).
+bool use_tiles(const vqe_circuit* c) { return use_specialised(c) && c->n >= kTileMinQubits; }
+
+// Plans the tile passes of c for dtype index d, generates their kernels and
+// loads them on the current device (once).
+int ensure_tiles(const vqe_circuit* cc, int d) {
+    vqe_circuit* c = const_cast<vqe_circuit*>(cc);
+    TilePlan& tp = c->tile[d];
+    int dev = 0;
+    VQE_HIP(hipGetDevice(&dev));
+    std::lock_guard<std::mutex> g(g_jit_plan_mu);
+    if (tp.ready && tp.dev == dev) return VQE_OK;
+    TilePlan np;
+    std::string msg;
+    const TileShape sh = tile_shape(d == 1, c->n);
+    if (!plan_tiles(c->n, c->gates, TileLimits{sh.T, sh.low, kTileMaxGates, kTileMaxPushes}, np.passes, msg)) {
+        set_error(msg);
+        return VQE_ERR_STATE;
+    }
+    const size_t P = np.passes.size();
+    std::vector<std::string> srcs;
+    for (int dir = 0; dir < 2; ++dir) {
+        np.k[dir].resize(P);
+        for (size_t p = 0; p < P; ++p) {
+            TileKernel& k = np.k[dir][p];
+            if (!tile_kernel(d == 1, sh, c->gates, np.passes[p], dir, k, msg)) {
+                set_error(msg);
+                return VQE_ERR_STATE;
+            }
+            srcs.push_back(std::move(k.src));
+            k.src.clear();
+            np.tab_off[dir].push_back(np.tab_total);
+            np.tab_total += (k.n_scalars + 15) / 16 * 16;  // whole cache lines per pass
+            np.L = std::max(np.L, (uint32_t)k.lane_param.size());
+        }
+    }
+    std::vector<void*> fns;
+    if (int rc = jit_prepare(srcs, fns, msg)) {
+        set_error(msg);
+        return rc;
+    }
+    np.fn[0].assign(fns.begin(), fns.begin() + (long)P);
+    np.fn[1].assign(fns.begin() + (long)P, fns.end());
+    np.dev = dev;
+    np.ready = true;
+    tp = std::move(np);
+    return VQE_OK;
+}
+
 // The state's matrix table (device) and its pinned staging copy, at least
 // `bytes` long; waits until the previous upload from the staging copy is done.
 int stage_mats(vqe_state* s, size_t bytes) {
@@ -826,6 +888,29 @@ bool shear_coefficients(double a, Mat2<T>& m) {
     return flip;
 }
 
+// Fills the tables of a circuit's tile passes (both directions) for these
+// parameters and uploads them on the state's stream.
+template <typename T>
+int upload_tables(vqe_state* s, const vqe_circuit* c, const TilePlan& tp, const double* params, const T** out) {
+    const size_t bytes = std::max<size_t>(tp.tab_total, 1) * sizeof(T);
+    if (int rc = stage_mats(s, bytes)) return rc;
+    std::vector<HalfAngle> h(c->gates.size());
+    for (size_t i = 0; i < h.size(); ++i) {
+        const double a = angle_of(c->gates[i], params) / 2;
+        h[i] = HalfAngle{std::cos(a), std::sin(a)};
+    }
+    for (int dir = 0; dir < 2; ++dir)
+        for (size_t p = 0; p < tp.passes.size(); ++p)
+            fill_tile_table<T>(tp.k[dir][p], c->gates, h.data(), dir, (T*)s->h_mats + tp.tab_off[dir][p]);
+    VQE_HIP(hipMemcpyAsync(s->d_mats, s->h_mats, bytes, hipMemcpyHostToDevice, s->stream));
+    VQE_HIP(hipEventRecord(s->mats_ev, s->stream));
+    *out = (const T*)s->d_mats;
+    return VQE_OK;
+}
+
+// Fills the matrix table of a specialised plan (every pass, both directions)
+// for these parameters and uploads it on the state's stream.  The pinned
+// staging buffer is reused only after its previous upload has completed.
 template <typename T>
 int upload_mats(vqe_state* s, const vqe_circuit* c, const Plan& pl, const double* params, const Mat2<T>** out) {
     const size_t bytes = std::max<size_t>(pl.mat_total, 1) * sizeof(Mat2<T>);
@@ -880,19 +965,58 @@ int apply_dense(vqe_state* s, const DenseArgs& a, const double* u) {
     return VQE_OK;
 }
 
-// Forward passes from |b0> (or in place on the current state when reset is false).
+void tile_args(const PlannedPass& p, int n, TileArgs& a) {
+    std::memset(&a, 0, sizeof(a));
+    a.n_units = 1ull << (n - p.K);
+    for (int j = 0; j < p.K; ++j) a.pos[j] = (uint32_t)p.pos[j];
+}
+
+template <typename T>
+int forward_tiles(vqe_state* s, const vqe_circuit* c, const double* params, const std::vector<size_t>& bounds,
+                  const std::vector<void*>& ckpt_ptr, bool zero, int chunk) {
+    const int d = sizeof(T) == 8 ? 1 : 0;
+    const TilePlan& tp = c->tile[d];
+    const T* tab = nullptr;
+    if (int rc = upload_tables<T>(s, c, tp, params, &tab)) return rc;
+    if (zero && tp.passes.empty()) VQE_HIP(launch_set_basis(s->dtype, s->data, 1ull << s->n, 0, s->stream));
+    void* cur = s->data;
+    TileArgs a;
+    for (size_t pi = 0; pi < tp.passes.size(); ++pi) {
+        void* out = s->data;
+        for (size_t k = 0; k < bounds.size(); ++k)
+            if (bounds[k] == pi + 1) out = ckpt_ptr[k];
+        ProfScope ps(VQE_KERNEL_WINDOW_FWD, (zero && pi == 0 ? 1.0 : 2.0) * (double)s->bytes, s->stream);
+        tile_args(tp.passes[pi], s->n, a);
+        a.first = zero && pi == 0 ? 1u : 0u;
+        VQE_HIP(launch_tile(tp.fn[0][pi], a, false, tab + tp.tab_off[0][pi], cur, out, nullptr, nullptr, nullptr, 0,
+                            s->stream));
+        ps.end();
+        cur = out;
+        if (chunk > 0 && (pi + 1) % (size_t)chunk == 0 && pi + 1 < tp.passes.size())
+            VQE_HIP(hipStreamSynchronize(s->stream));
+    }
+    return VQE_OK;
+}
+
+// Forward passes from |0...0> (zero) or in place on the current state.
 // ckpt_ptr[k] receives the state at boundary bounds[k] (pass index + 1).
 template <typename T>
-int forward(vqe_state* s, const vqe_circuit* c, const Plan& pl, const double* params,
-            const std::vector<size_t>& bounds, const std::vector<void*>& ckpt_ptr, int chunk = 0) {
-    void* cur = s->data;
+int forward(vqe_state* s, const vqe_circuit* c, const double* params, const std::vector<size_t>& bounds,
+            const std::vector<void*>& ckpt_ptr, bool zero, int chunk = 0) {
     const int d = sizeof(T) == 8 ? 1 : 0;
+    if (use_tiles(c)) {
+        if (int rc = ensure_tiles(c, d)) return rc;
+        return forward_tiles<T>(s, c, params, bounds, ckpt_ptr, zero, chunk);
+    }
+    const Plan& pl = plan_now(c);
+    void* cur = s->data;
     const Mat2<T>* mats = nullptr;
     if (pl.jit) {
         int rc = ensure_jit(c, pl, d);
         if (!rc) rc = upload_mats<T>(s, c, pl, params, &mats);
         if (rc) return rc;
     }
+    if (zero) VQE_HIP(launch_set_basis(s->dtype, s->data, 1ull << s->n, 0, s->stream));
     PassArgs<T> a;
     JitArgs ja;
     for (size_t pi = 0; pi < pl.passes.size(); ++pi) {
@@ -1053,12 +1177,48 @@ int expect_impl(vqe_state* s, const vqe_hamiltonian* h, int mode, double* energy
     return VQE_OK;
 }
 
+// Reverse tile passes on (psi, lam): column sums of the gradient terms of pass
+// p to sums[p L ..].
+template <typename T>
+int reverse_tiles(vqe_state* psi, vqe_state* lam, const TilePlan& tp, const std::vector<size_t>& bounds,
+                  const std::vector<void*>& ck, double* sums, int chunk) {
+    const size_t P = tp.passes.size();
+    const T* tab = (const T*)psi->d_mats;  // uploaded by forward_tiles()
+    hipStream_t st = psi->stream;
+    TileArgs a;
+    size_t waiting = 0;  // passes whose partials wait in d_part, the last of them pi
+    for (size_t pi = P; pi-- > 0;) {
+        const void* pin = psi->data;
+        for (size_t k = 0; k < bounds.size(); ++k)
+            if (bounds[k] == pi + 1) pin = ck[k];
+        tile_args(tp.passes[pi], psi->n, a);
+        const uint32_t nb = tile_blocks(a.n_units, true);
+        const size_t room = part_doubles() / ((size_t)nb * std::max(tp.L, 1u));  // passes that d_part holds
+        ProfScope ps(VQE_KERNEL_WINDOW_REV, 4.0 * (double)psi->bytes, st);
+        // the partials lie in ascending pass order, so a group is filled from its end
+        const size_t group = std::min(room, waiting + pi + 1);
+        ++waiting;
+        VQE_HIP(launch_tile(tp.fn[1][pi], a, true, tab + tp.tab_off[1][pi], pin, psi->data, lam->data, lam->data,
+                            psi->d_part + (group - waiting) * (size_t)nb * tp.L, tp.L, st));
+        ps.end();
+        if (waiting == group) {
+            VQE_HIP(launch_tile_reduce(psi->d_part, (uint32_t)waiting, nb, tp.L, sums + pi * tp.L, st));
+            waiting = 0;
+        }
+        if (chunk > 0 && (P - pi) % (size_t)chunk == 0 && pi > 0) VQE_HIP(hipStreamSynchronize(st));
+    }
+    return VQE_OK;
+}
+
 template <typename T>
 int adjoint_impl(vqe_state* psi, vqe_state* lam, const vqe_circuit* c, const double* params,
                  const vqe_hamiltonian* h, const vqe_grad_opts* o, double* energy, double* grad) {
+    const int d = sizeof(T) == 8 ? 1 : 0;
+    const bool tiles = use_tiles(c);
+    if (int rc0 = tiles ? ensure_tiles(c, d) : upload_plan(plan_now(c))) return rc0;
     const Plan& pl = plan_now(c);
-    if (int rc0 = upload_plan(pl)) return rc0;
-    const size_t P = pl.passes.size();
+    const TilePlan& tp = c->tile[d];
+    const size_t P = tiles ? tp.passes.size() : pl.passes.size();
     std::vector<size_t> bounds;
     std::vector<void*> ck;
     const int nck = o ? o->n_ckpt : 0;
@@ -1069,19 +1229,33 @@ int adjoint_impl(vqe_state* psi, vqe_state* lam, const vqe_circuit* c, const dou
         bounds.push_back(b);
         ck.push_back(o->ckpt[k]->data);
     }
-    int rc = ensure_res(psi, 2 + c->n_params);
+    const size_t n_sums = tiles ? P * tp.L : c->n_params;  // tile passes: column sums, added up by parameter at the end
+    int rc = ensure_res(psi, 2 + n_sums);
     if (rc) return rc;
     double* d_e = psi->d_res;
     double* d_g = psi->d_res + 2;
     hipStream_t st = psi->stream;
     const int chunk = o && o->chunk_passes > 0 ? o->chunk_passes : 0;
-    VQE_HIP(launch_set_basis(psi->dtype, psi->data, 1ull << psi->n, 0, st));
-    rc = forward<T>(psi, c, pl, params, bounds, ck, chunk);
+    rc = forward<T>(psi, c, params, bounds, ck, true, chunk);
     if (rc) return rc;
     rc = apply_h<T>(psi, lam->data, h, d_e);
     if (rc) return rc;
+    if (tiles) {
+        rc = reverse_tiles<T>(psi, lam, tp, bounds, ck, d_g, chunk);
+        if (rc) return rc;
+        VQE_HIP(hipMemcpyAsync(psi->h_res, psi->d_res, (2 + n_sums) * sizeof(double), hipMemcpyDeviceToHost, st));
+        VQE_HIP(hipStreamSynchronize(st));
+        const double nrm = psi->h_res[1];
+        *energy = psi->h_res[0] / nrm;
+        std::fill(grad, grad + c->n_params, 0.0);
+        for (size_t pi = 0; pi < P; ++pi) {
+            const std::vector<int32_t>& lp = tp.k[1][pi].lane_param;
+            for (size_t l = 0; l < lp.size(); ++l)
+                if (lp[l] >= 0) grad[lp[l]] += psi->h_res[2 + pi * tp.L + l] / nrm;
+        }
+        return VQE_OK;
+    }
     VQE_HIP(launch_zero(d_g, c->n_params, st));
-    const int d = sizeof(T) == 8 ? 1 : 0;
     const Mat2<T>* mats = (const Mat2<T>*)psi->d_mats;  // uploaded by forward()
     PassArgs<T> a;
     JitArgs ja;
@@ -1152,8 +1326,7 @@ int param_shift_impl(vqe_state* psi, const vqe_circuit* c, const double* params,
     for (size_t e = n_eval; e-- > 0;) {
         std::copy(params, params + P, th.begin());
         if (e > 0) th[shifts[e - 1].first] += shifts[e - 1].second;
-        VQE_HIP(launch_set_basis(psi->dtype, psi->data, 1ull << psi->n, 0, psi->stream));
-        rc = forward<T>(psi, c, plan_now(c), th.data(), nob, nock);
+        rc = forward<T>(psi, c, th.data(), nob, nock, true);
         if (rc) return rc;
         rc = mode == VQE_EXPECT_PER_TERM ? energy_per_term<T>(psi, h, e * per)
                                          : energy_grouped<T>(psi, h, psi->d_part, psi->d_res + e * per);
@@ -2036,8 +2209,8 @@ int vqe_apply_circuit(vqe_state* s, const vqe_circuit* c, const double* params, 
     VQE_HIP(hipSetDevice(s->device));
     const std::vector<size_t> nob;
     const std::vector<void*> nock;
-    const Plan& pl = plan_now(c);
-    return s->dtype == VQE_C64 ? forward<float>(s, c, pl, params, nob, nock) : forward<double>(s, c, pl, params, nob, nock);
+    return s->dtype == VQE_C64 ? forward<float>(s, c, params, nob, nock, false)
+                               : forward<double>(s, c, params, nob, nock, false);
     VQE_GUARD_END
 }
 
@@ -2382,6 +2555,7 @@ int vqe_circuit_prepare(const vqe_circuit* c, int dtype) {
         return VQE_ERR_ARG;
     }
     if (int rc = check_form(c, "vqe_circuit_prepare")) return rc;
+    if (use_tiles(c)) return ensure_tiles(c, dtype == VQE_C128 ? 1 : 0);
     const Plan& pl = plan_now(c);
     if (!pl.jit) return VQE_OK;
     return ensure_jit(c, pl, dtype == VQE_C128 ? 1 : 0);

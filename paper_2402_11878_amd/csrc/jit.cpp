@@ -472,8 +472,8 @@ int jit_prepare(const std::vector<std::string>& srcs, std::vector<void*>& fns, s
         const char* name = nullptr;
         for (int nv = 1; nv <= 2 && !name; ++nv)
             for (int dbl = 0; dbl < 2 && !name; ++dbl)
-                if (todo[i]->find(std::string(jit_kernel_name(nv, dbl)) + "(") != std::string::npos)
-                    name = jit_kernel_name(nv, dbl);
+                for (const char* cand : {jit_kernel_name(nv, dbl), tile_kernel_name(nv, dbl)})
+                    if (todo[i]->find(std::string(cand) + "(") != std::string::npos) name = cand;
         if (!name) {
             err = "specialised pass kernel without a known symbol (internal error)";
             return VQE_ERR_STATE;

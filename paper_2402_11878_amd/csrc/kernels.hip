@@ -1212,6 +1212,26 @@ reduce_kernel(const double* __restrict__ part, uint32_t nblocks, uint32_t nslots
     }
 }
 
+// Sums over blocks of the gradient partials of several tile passes: block
+// (p, c) sums the 16 columns c of pass p (128 bytes of every row); its 64 row
+// groups take every 64th row each, then one thread per column adds the group
+// sums in order.
+__global__ void __launch_bounds__(1024)
+tile_reduce_kernel(const double* __restrict__ part, uint32_t nblocks, uint32_t L, double* __restrict__ out) {
+    __shared__ double red[64][16];
+    const uint32_t l = threadIdx.x & 15, w = threadIdx.x >> 4;
+    const double* p = part + (uint64_t)blockIdx.x * nblocks * L + blockIdx.y * 16 + l;
+    double acc = 0.0;
+#pragma unroll 8
+    for (uint32_t b = w; b < nblocks; b += 64) acc += p[(uint64_t)b * L];
+    red[w][l] = acc;
+    __syncthreads();
+    if (w == 0) {
+        for (int k = 1; k < 64; ++k) acc += red[k][l];
+        out[(uint64_t)blockIdx.x * L + blockIdx.y * 16 + l] = acc;
+    }
+}
+
 // out[0] = sums[0] / sums[1] (the energy of eq. 7), out[1] = sums[1] (the norm).
 __global__ void energy_ratio_kernel(const double* __restrict__ sums, double* __restrict__ out) {
     if (threadIdx.x == 0) {
@@ -1396,6 +1416,38 @@ hipError_t launch_window_jit(void* fn, const JitArgs& a, int S, const void* mats
     return hipModuleLaunchKernel((hipFunction_t)fn, w.grid, 1, 1, kBlock, 1, 1, 0, st, params, nullptr);
 }
 
+
+// A reverse pass reduces its gradient terms per block, so its blocks take
+// several cosets: at least 2048 blocks (the chip holds 512 at a time), 16
+// cosets each beyond, at most 16384 blocks.  In-place copies of two 30-qubit
+// complex128 states by 12-qubit tiles: one coset per block 4.85 TB/s, 16384
+// blocks in runs of 64 side by side 4.70, 2048 blocks 4.5.  Forward passes
+// have nothing to reduce and take one coset per block.
+uint32_t tile_blocks(uint64_t units, bool reverse) {
+    if (!reverse) return (uint32_t)units;
+    const uint64_t want = units / 16 < 2048 ? 2048 : units / 16 > 16384 ? 16384 : units / 16;
+    return (uint32_t)(units < want ? units : want);
+}
+
+hipError_t launch_tile(void* fn, const TileArgs& a, bool reverse, const void* tab, const void* in0, void* out0,
+                       const void* in1, void* out1, double* gpart, uint32_t L, hipStream_t st) {
+    TileArgs ka = a;
+    const uint32_t grid = tile_blocks(a.n_units, reverse);
+    uint32_t cpt = (uint32_t)(a.n_units / grid), mlog = log2_pow2(a.n_units);
+    if ((uint64_t)cpt * grid != a.n_units || (mlog >= 3 && grid < 8)) return hipErrorInvalidValue;
+    uint32_t gs = grid / 8 < 64 ? grid / 8 : 64;
+    if (gs < 1) gs = 1;
+    void* params[] = {&ka, (void*)&tab, &cpt, &mlog, &gs, &L, (void*)&in0, (void*)&out0, (void*)&in1, (void*)&out1,
+                      (void*)&gpart};
+    return hipModuleLaunchKernel((hipFunction_t)fn, grid, 1, 1, kTileThreads, 1, 1, 0, st, params, nullptr);
+}
+
+hipError_t launch_tile_reduce(const double* part, uint32_t n_pass, uint32_t nblocks, uint32_t L, double* out,
+                              hipStream_t st) {
+    if (n_pass == 0 || L == 0) return hipSuccess;
+    hipLaunchKernelGGL(tile_reduce_kernel, dim3(n_pass, L / 16), dim3(1024), 0, st, part, nblocks, L, out);
+    return hipGetLastError();
+}
 
 template <typename T>
 hipError_t launch_hwin(int n, const HwDesc& w, const void* psi, void* lam, const HwGroup* groups,

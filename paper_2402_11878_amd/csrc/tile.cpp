@@ -1,0 +1,857 @@
+// Tile passes: the specialised kernels of states of at least kTileMinQubits
+// qubits.  A pass reads and writes the state once, like a window pass, but
+// its window has 12 or 13 qubits instead of 7: a block of 256 threads keeps
+// the coset (2^T amplitudes) of psi, in reverse passes of lam too, in
+// registers, 2^R amplitudes per thread and vector, and works through the
+// window's gates in stages of R register bits each; between two stages the
+// vectors change layout through LDS (one write and one read per amplitude,
+// against four or more vector instructions per amplitude and lane transpose
+// bit).  The state crosses HBM once per pass, so the pass count is what a
+// large state pays for: 10 passes instead of 23 at 32 qubits x 8 layers.
+//
+// What the generated code does about arithmetic, the second cost:
+//   * permutation gates (CNOT, X) rename registers at generation time;
+//   * RY and RX run unnormalised, R = c [[1, -t], [t, 1]] with t = tan(a/2) and
+//     c = cos(a/2): two fused multiply-adds per amplitude instead of four
+//     operations (three as shears); the factors c wait until the next
+//     multiplication of the whole vector;
+//   * all diagonal gates (RZ, CZ) of a stage that can stand together are one
+//     multiplication by a phase from a host-made table of 2^m entries, which
+//     also carries the pending factors c;
+//   * the Z-gradient terms of such a group come from one product
+//     Im(conj(lam) psi) per amplitude and a tree of signed sums;
+//   * gradient terms are summed over the lanes of a wave as they appear, two at
+//     a time (each exchange halves the number of values), so that no more than
+//     six values per thread wait and one lane ends up with each total.
+#include <algorithm>
+#include <cmath>
+#include <sstream>
+
+#include "vqe_internal.h"
+
+namespace vqe {
+namespace {
+
+enum OpKind { K_GRAD, K_ROTY, K_ROTX, K_R2, K_CNOT, K_FLIP, K_DIAG };
+
+// One gate (or its gradient term) on the register bits of a stage.  On each of
+// its bits it acts like Z (diagonal), like X, like Y, or otherwise; two ops
+// commute if on every shared bit both act like the same Pauli.
+struct Op {
+    OpKind kind;
+    int gate;
+    int bit[4];
+    uint32_t z = 0, x = 0, y = 0, other = 0;
+};
+
+bool commute(const Op& a, const Op& b) {
+    const uint32_t ma = a.z | a.x | a.y | a.other, mb = b.z | b.x | b.y | b.other, shared = ma & mb;
+    return (shared & ~((a.z & b.z) | (a.x & b.x) | (a.y & b.y))) == 0;
+}
+
+bool is_rot(OpKind k) { return k == K_ROTY || k == K_ROTX; }
+
+struct Layout {
+    int reg[8];  // tile bit of register bit i
+    int thr[8];  // tile bit of thread bit i
+};
+
+struct Gen {
+    bool dbl;
+    TileShape sh;
+    int NV, N;
+    const std::vector<Gate>* gates;
+    TileKernel* out;
+    std::ostringstream o;
+    std::vector<int> loc;        // variable holding register entry p
+    std::vector<int> pending;    // rotations whose factor c is still to be applied
+    // gradient terms waiting at each level of the lane sums, as variables and their lane -> push map
+    struct Node {
+        std::string var;
+        std::vector<int> lane;
+    };
+    std::vector<Node> level[7];
+    int vars = 0, pushes = 0, chunk = 0;
+
+    std::string R(int v, int p) const { return "r" + std::to_string(v) + "_" + std::to_string(loc[p]); }
+    std::string I(int v, int p) const { return "i" + std::to_string(v) + "_" + std::to_string(loc[p]); }
+
+    // ---- tables
+    uint32_t entry(TileEntry e, uint32_t scalars) {
+        e.off = out->n_scalars;
+        out->n_scalars += scalars;
+        out->entries.push_back(std::move(e));
+        return out->entries.back().off;
+    }
+
+    // ---- ops
+    void rot(const Op& k) {
+        TileEntry e;
+        e.kind = TF_ROT;
+        e.gate = k.gate;
+        const uint32_t off = entry(e, 1);
+        o << "  { const T t = tab[" << off << "];\n";
+        const int b = 1 << k.bit[0];
+        for (int p = 0; p < N; ++p) {
+            if (p & b) continue;
+            const int q = p | b;
+            for (int v = 0; v < NV; ++v) {
+                o << "    { const T xr = " << R(v, p) << ", xi = " << I(v, p) << ", yr = " << R(v, q) << ", yi = "
+                  << I(v, q) << ";\n      ";
+                if (k.kind == K_ROTY)
+                    o << R(v, p) << " = xr - t * yr; " << I(v, p) << " = xi - t * yi; " << R(v, q)
+                      << " = yr + t * xr; " << I(v, q) << " = yi + t * xi; }\n";
+                else  // [[1, -i t], [-i t, 1]]
+                    o << R(v, p) << " = xr + t * yi; " << I(v, p) << " = xi - t * yr; " << R(v, q)
+                      << " = yr + t * xi; " << I(v, q) << " = yi - t * xr; }\n";
+            }
+        }
+        o << "  }\n";
+        pending.push_back(k.gate);
+    }
+
+    void scale() {
+        if (pending.empty()) return;
+        TileEntry e;
+        e.kind = TF_SCALE;
+        e.rots.swap(pending);
+        const uint32_t off = entry(e, 1);
+        o << "  { const T s = tab[" << off << "];\n";
+        for (int p = 0; p < N; ++p)
+            for (int v = 0; v < NV; ++v) o << "    " << R(v, p) << " *= s; " << I(v, p) << " *= s;\n";
+        o << "  }\n";
+    }
+
+    // The diagonal gates `ops` as one phase per value of their bits.
+    void phase(const std::vector<Op>& ops) {
+        TileEntry e;
+        e.kind = TF_PHASE;
+        for (const Op& k : ops) {
+            e.diag.push_back(k.gate);
+            e.diag_bits.push_back(k.z);
+            e.mask |= k.z;
+        }
+        e.rots.swap(pending);
+        const uint32_t mask = e.mask;
+        const int m = __builtin_popcount(mask);
+        const uint32_t off = entry(e, 2u << m);
+        for (uint32_t idx = 0; idx < (1u << m); ++idx) {
+            o << "  { const T pr = tab[" << off + 2 * idx << "], pi = tab[" << off + 2 * idx + 1 << "];\n";
+            for (int p = 0; p < N; ++p) {
+                uint32_t at = 0;
+                for (int b = 0, k = 0; b < sh.R; ++b)
+                    if ((mask >> b) & 1) at |= ((uint32_t)(p >> b) & 1u) << k++;
+                if (at != idx) continue;
+                for (int v = 0; v < NV; ++v)
+                    o << "    { const T ar = " << R(v, p) << ", ai = " << I(v, p) << "; " << R(v, p)
+                      << " = pr * ar - pi * ai; " << I(v, p) << " = pr * ai + pi * ar; }\n";
+            }
+            o << "  }\n";
+        }
+    }
+
+    // A real 2x2 matrix between two patterns (H; excitations).
+    void matrix(const Op& k) {
+        TileEntry e;
+        e.gate = k.gate;
+        e.kind = TF_R2;
+        const uint32_t off = entry(e, 4);
+        o << "  { const T ca = tab[" << off << "], cb = tab[" << off + 1 << "], cc = tab[" << off + 2 << "], cd = tab["
+          << off + 3 << "];\n";
+        uint32_t mask, A, B;
+        pattern(k, mask, A, B);
+        for (int p = 0; p < N; ++p) {
+            if ((p & (int)mask) != (int)A) continue;
+            const int q = p ^ (int)(A ^ B);
+            for (int v = 0; v < NV; ++v)
+                o << "    { const T ar = " << R(v, p) << ", ai = " << I(v, p) << ", br = " << R(v, q) << ", bi = "
+                  << I(v, q) << ";\n      " << R(v, p) << " = ca * ar + cb * br; " << I(v, p)
+                  << " = ca * ai + cb * bi; " << R(v, q) << " = cc * ar + cd * br; " << I(v, q)
+                  << " = cc * ai + cd * bi; }\n";
+        }
+        o << "  }\n";
+    }
+
+    // Patterns between which an op acts: bit clear / set, or the A and B of an excitation.
+    void pattern(const Op& k, uint32_t& mask, uint32_t& A, uint32_t& B) const {
+        const Gate& g = (*gates)[k.gate];
+        if (g.kind == VQE_GATE_SEXC) {
+            A = 1u << k.bit[0];
+            B = 1u << k.bit[1];
+        } else if (g.kind == VQE_GATE_DEXC) {
+            A = (1u << k.bit[0]) | (1u << k.bit[1]);
+            B = (1u << k.bit[2]) | (1u << k.bit[3]);
+        } else {
+            A = 0;
+            B = 1u << k.bit[0];
+        }
+        mask = A | B;
+    }
+
+    void rename(const Op& k) {
+        const int c = k.kind == K_CNOT ? 1 << k.bit[0] : 0, t = 1 << (k.kind == K_CNOT ? k.bit[1] : k.bit[0]);
+        for (int p = 0; p < N; ++p)
+            if ((p & c) == c && !(p & t)) std::swap(loc[p], loc[p | t]);
+    }
+
+    // ---- gradient terms
+    std::string fresh() { return "v" + std::to_string(vars++); }
+
+    // Hands over one term (an expression of type T, this thread's share).
+    void push(const std::string& expr, int param) {
+        const int id = pushes++;
+        out->lane_param.resize(std::max<size_t>(out->lane_param.size(), 64 * (size_t)(id / 64 + 1)), -1);
+        term_param.push_back(param);
+        Node n{fresh(), std::vector<int>(64, id)};
+        o << "  double " << n.var << " = (double)(" << expr << ");\n";
+        carry(0, n);
+        if (pushes % 64 == 0) flush();
+    }
+    std::vector<int> term_param;
+
+    void carry(int lv, Node n) {
+        while (lv < 6 && !level[lv].empty()) {
+            n = join(lv, level[lv].back(), n);
+            level[lv].pop_back();
+            ++lv;
+        }
+        if (lv == 6) total(n);
+        else level[lv].push_back(n);
+    }
+
+    // Sum of a (lanes with bit 5 - lv clear) and b (set) over that lane bit.
+    Node join(int lv, const Node& a, const Node& b) {
+        Node n{fresh(), a.lane};
+        for (int l = 0; l < 64; ++l)
+            if ((l >> (5 - lv)) & 1) n.lane[l] = b.lane[l];
+        o << "  double " << n.var << " = comb<" << 5 - lv << ">(" << a.var << ", " << b.var << ");\n";
+        return n;
+    }
+
+    void total(const Node& n) {
+        o << "  acc" << chunk << " += " << n.var << ";\n";
+        std::vector<char> seen(pushes, 0);
+        for (int l = 0; l < 64; ++l)
+            if (!seen[n.lane[l]]) {
+                seen[n.lane[l]] = 1;
+                out->lane_param[64 * chunk + l] = term_param[n.lane[l]];
+            }
+        ++chunk;
+    }
+
+    // Brings every waiting term to a total (missing partners: the value itself on both halves).
+    void flush() {
+        bool any = false;
+        for (auto& l : level) any = any || !l.empty();
+        if (!any) return;
+        Node carry_n;
+        bool have = false;
+        for (int lv = 0; lv < 6; ++lv) {
+            Node* here = level[lv].empty() ? nullptr : &level[lv].back();
+            if (!here && !have) continue;
+            Node n = here && have ? join(lv, *here, carry_n) : here ? join(lv, *here, *here) : join(lv, carry_n, carry_n);
+            level[lv].clear();
+            carry_n = n;
+            have = true;
+        }
+        total(carry_n);
+    }
+
+    void gradient(const Op& k) {
+        const Gate& g = (*gates)[k.gate];
+        uint32_t mask, A, B;
+        pattern(k, mask, A, B);
+        const std::string acc = fresh();
+        o << "  T " << acc << " = 0;\n";
+        for (int p = 0; p < N; ++p) {
+            if ((p & (int)mask) != (int)A) continue;
+            const int q = p ^ (int)(A ^ B);
+            const std::string pr = R(0, p), pi = I(0, p), qr = R(0, q), qi = I(0, q);
+            const std::string lr = R(1, p), li = I(1, p), mr = R(1, q), mi = I(1, q);
+            if (g.kind == VQE_GATE_RX)  // Im<lam|X|psi>
+                o << "  " << acc << " += " << lr << " * " << qi << "; " << acc << " -= " << li << " * " << qr << "; "
+                  << acc << " += " << mr << " * " << pi << "; " << acc << " -= " << mi << " * " << pr << ";\n";
+            else  // Im<lam|Y|psi>, and Re<lam|K|psi> with K = |B><A| - |A><B| of an excitation: the same form
+                o << "  " << acc << " += " << mr << " * " << pr << "; " << acc << " += " << mi << " * " << pi << "; "
+                  << acc << " -= " << lr << " * " << qr << "; " << acc << " -= " << li << " * " << qi << ";\n";
+        }
+        push(acc, g.pidx);
+    }
+
+    // Im<lam|Z_b|psi> for the bits of the given RZ gates: d = Im(conj(lam) psi)
+    // per entry once, then for each bit the sum of differences, passing the sums on.
+    void gradient_z(const std::vector<Op>& ops) {
+        std::vector<std::string> d(N);
+        for (int p = 0; p < N; ++p) {
+            d[p] = fresh();
+            o << "  T " << d[p] << " = " << R(1, p) << " * " << I(0, p) << "; " << d[p] << " -= " << I(1, p) << " * "
+              << R(0, p) << ";\n";
+        }
+        uint32_t want = 0;
+        for (const Op& k : ops) want |= 1u << k.bit[0];
+        for (int b = 0; b < sh.R; ++b) {
+            const size_t half = d.size() / 2;  // entries are indexed by the bits b and up
+            std::vector<std::string> s(half);
+            if ((want >> b) & 1) {
+                const std::string acc = fresh();
+                for (size_t i = 0; i < half; ++i)
+                    o << (i ? "  " + acc + " += " : "  T " + acc + " = ") << d[2 * i] << " - " << d[2 * i + 1] << ";\n";
+                // every parameterised gate on the bit has this term
+                for (const Op& k : ops)
+                    if (k.bit[0] == b) push(acc, (*gates)[k.gate].pidx);
+            }
+            if (!(want >> (b + 1))) break;
+            for (size_t i = 0; i < half; ++i) {
+                s[i] = fresh();
+                o << "  T " << s[i] << " = " << d[2 * i] << " + " << d[2 * i + 1] << ";\n";
+            }
+            d.swap(s);
+        }
+    }
+
+    // Emits the ops of a stage in an order that respects every pair that does
+    // not commute: gradient terms and register renames as soon as they are
+    // ready, then rotations, diagonal gates last (so that they merge).
+    // Gradient terms read normalised vectors (pending factors applied first).
+    void stage(std::vector<Op> ops) {
+        const size_t max_pending = dbl ? 14 : 4;  // each factor may be as small as 2^-60 (2^-26)
+        auto ready = [&](size_t i) {
+            for (size_t j = 0; j < i; ++j)
+                if (!commute(ops[j], ops[i])) return false;
+            return true;
+        };
+        auto z_term = [&](const Op& k) { return k.kind == K_GRAD && (*gates)[k.gate].kind == VQE_GATE_RZ; };
+        auto is_diag = [&](const Op& k) { return k.kind == K_DIAG || z_term(k); };
+        while (!ops.empty()) {
+            bool progress = false;
+            for (size_t i = 0; i < ops.size();) {
+                const Op& k = ops[i];
+                if (is_diag(k) || is_rot(k.kind) || (k.kind == K_GRAD && !pending.empty()) || !ready(i)) {
+                    ++i;
+                    continue;
+                }
+                if (k.kind == K_GRAD) gradient(k);
+                else if (k.kind == K_CNOT || k.kind == K_FLIP) rename(k);
+                else matrix(k);
+                ops.erase(ops.begin() + (long)i);
+                progress = true;
+                i = 0;
+            }
+            if (ops.empty()) break;
+            for (size_t i = 0; i < ops.size();) {
+                if (is_rot(ops[i].kind) && pending.size() < max_pending && ready(i)) {
+                    rot(ops[i]);
+                    ops.erase(ops.begin() + (long)i);
+                    progress = true;
+                } else {
+                    ++i;
+                }
+            }
+            if (progress) continue;
+            std::vector<Op> diag, zt;
+            for (size_t i = 0; i < ops.size();) {
+                if (is_diag(ops[i]) && ready(i)) {
+                    (z_term(ops[i]) ? zt : diag).push_back(ops[i]);
+                    ops.erase(ops.begin() + (long)i);
+                } else {
+                    ++i;
+                }
+            }
+            if (!diag.empty()) phase(diag);
+            if (!zt.empty()) {
+                scale();
+                gradient_z(zt);
+            }
+            if (diag.empty() && zt.empty()) scale();  // a gradient term or a rotation waits for the factors
+        }
+    }
+
+    // ---- layouts
+    bool split = false;  // exchange real and imaginary parts one after the other (half the LDS)
+    int elem_bytes() const { return (dbl ? 16 : 8) / (split ? 2 : 1); }
+    int bank_bits() const { return dbl ? (split ? 4 : 3) : (split ? 5 : 4); }  // 128 bytes, what LDS serves per clock
+
+    // LDS slot of tile index j: the lowest bank_bits() bits are XORed with all
+    // groups of bits above them, so that amplitudes a fixed power of two apart
+    // lie in different banks.
+    uint32_t slot(uint32_t j) const {
+        const int nb = bank_bits();
+        uint32_t f = 0;
+        for (uint32_t v = j >> nb; v; v >>= nb) f ^= v;
+        return j ^ (f & ((1u << nb) - 1));
+    }
+
+    // Layout with register bits `regs` and wave bits `wave` (tile bits); the
+    // others go to the lanes in ascending order, for loads and stores, or with
+    // lowest lane bits that differ modulo bank_bits() (conflict-free in LDS).
+    Layout layout(const std::vector<int>& regs, const std::vector<int>& wave, bool memory) const {
+        Layout L{};
+        std::vector<int> rest;
+        for (int b = 0; b < sh.T; ++b)
+            if (std::find(regs.begin(), regs.end(), b) == regs.end() &&
+                std::find(wave.begin(), wave.end(), b) == wave.end())
+                rest.push_back(b);
+        if (!memory) {
+            const int nb = bank_bits();
+            std::vector<int> first;
+            uint32_t used = 0;
+            for (int b : rest)
+                if ((int)first.size() < nb && !((used >> (b % nb)) & 1)) {
+                    first.push_back(b);
+                    used |= 1u << (b % nb);
+                }
+            for (int b : rest)
+                if (std::find(first.begin(), first.end(), b) == first.end()) first.push_back(b);
+            rest = first;
+        }
+        rest.insert(rest.end(), wave.begin(), wave.end());
+        for (int i = 0; i < sh.R; ++i) L.reg[i] = regs[i];
+        for (int i = 0; i < sh.T - sh.R; ++i) L.thr[i] = rest[i];
+        return L;
+    }
+
+    // The thread's byte offset in LDS under layout L, as variable `b0`, and its
+    // variants with some of the low slot bits flipped.
+    void lds_base(const Layout& L) {
+        const int nb = bank_bits(), eb = elem_bytes();
+        o << "    u32 t_ = tid; asm volatile(\"\" : \"+v\"(t_));\n    const u32 j = 0";
+        const int TB = sh.T - sh.R;
+        for (int k = 0; k < TB;) {
+            int e = k + 1;
+            while (e < TB && L.thr[e] == L.thr[e - 1] + 1) ++e;
+            o << " | (((t_ >> " << k << ") & " << ((1u << (e - k)) - 1) << "u) << " << L.thr[k] << ")";
+            k = e;
+        }
+        o << ";\n    const u32 b0 = (j ^ ((0";
+        for (int s = nb; s < sh.T; s += nb) o << " ^ (j >> " << s << ")";
+        o << ") & " << ((1u << nb) - 1) << "u)) * " << eb << "u;\n";
+        std::vector<uint32_t> flips;
+        for (int p = 0; p < N; ++p) flips.push_back(reg_slot(L, p) & ((1u << nb) - 1));
+        std::sort(flips.begin(), flips.end());
+        flips.erase(std::unique(flips.begin(), flips.end()), flips.end());
+        for (uint32_t f : flips)
+            if (f) o << "    const u32 b" << f << " = b0 ^ " << f * (uint32_t)eb << "u;\n";
+    }
+
+    uint32_t reg_slot(const Layout& L, int p) const {
+        uint32_t j = 0;
+        for (int i = 0; i < sh.R; ++i)
+            if ((p >> i) & 1) j |= 1u << L.reg[i];
+        return slot(j);
+    }
+
+    std::string lds_at(const Layout& L, int p) const {
+        const uint32_t s = reg_slot(L, p), m = (1u << bank_bits()) - 1;
+        return std::string(split ? "*(T*)" : "*(V*)") + "(lds + b" + std::to_string(s & m) + " + " +
+               std::to_string((s & ~m) * (uint32_t)elem_bytes()) + "u)";
+    }
+
+    // Changes the layout of every vector through LDS.  If both layouts have
+    // the same wave bits, every wave writes and reads the same quarter of the
+    // buffer, its own: no barrier.  Otherwise one barrier between writing and
+    // reading, and one before the next vector overwrites the buffer.  None is
+    // needed before the first write: the reads of the exchange before it lay in
+    // this layout's own quarters.  LDS serves a wave's accesses in order, so
+    // between a wave's own writes and reads only the compiler has to be held
+    // back (wave_sync: lanes exchange data, which it does not see).
+    void exchange(const Layout& from, const Layout& to) {
+        const int W = sh.T - sh.R;
+        const bool own = std::equal(from.thr + 6, from.thr + W, to.thr + 6);
+        const std::vector<int> old = loc;
+        std::vector<int> ident(N);
+        for (int p = 0; p < N; ++p) ident[p] = p;
+        bool first = true;
+        for (int v = 0; v < NV; ++v) {
+            std::vector<std::string> got(N);
+            for (int half = 0; half < (split ? 2 : 1); ++half) {
+                o << (!own && !first ? "  __syncthreads();\n" : "  wave_sync();\n");
+                first = false;
+                loc = old;
+                o << "  {\n";
+                lds_base(from);
+                for (int p = 0; p < N; ++p) {
+                    o << "    " << lds_at(from, p) << " = ";
+                    if (split) o << (half ? I(v, p) : R(v, p)) << ";\n";
+                    else o << "V{" << R(v, p) << ", " << I(v, p) << "};\n";
+                }
+                o << "  }\n" << (own ? "  wave_sync();\n" : "  __syncthreads();\n");
+                loc = ident;
+                if (split) {
+                    for (int p = 0; p < N; ++p) got[p] = fresh(), o << "  T " << got[p] << ";\n";
+                    o << "  {\n";
+                    lds_base(to);
+                    for (int p = 0; p < N; ++p) o << "    " << got[p] << " = " << lds_at(to, p) << ";\n";
+                    o << "  }\n";
+                    for (int p = 0; p < N; ++p) o << "  " << (half ? I(v, p) : R(v, p)) << " = " << got[p] << ";\n";
+                } else {
+                    o << "  {\n";
+                    lds_base(to);
+                    for (int p = 0; p < N; ++p)
+                        o << "    { const V w = " << lds_at(to, p) << "; " << R(v, p) << " = w.x; " << I(v, p)
+                          << " = w.y; }\n";
+                    o << "  }\n";
+                }
+            }
+        }
+        loc = ident;
+    }
+
+    std::string reg_offset(const Layout& L, int p) const {
+        std::string e;
+        for (int i = 0; i < sh.R; ++i)
+            if ((p >> i) & 1) e += (e.empty() ? "bit[" : " + bit[") + std::to_string(L.reg[i]) + "]";
+        return e.empty() ? "0" : e;
+    }
+
+    void thread_offset(const char* name, const Layout& L) {
+        o << "  u64 " << name << " = 0;\n";
+        for (int k = 0; k < sh.T - sh.R; ++k)
+            o << "  if ((tid >> " << k << ") & 1) " << name << " += bit[" << L.thr[k] << "];\n";
+    }
+};
+
+std::string prelude(bool dbl) {
+    const char* T = dbl ? "double" : "float";
+    std::ostringstream o;
+    o << "typedef unsigned long long u64;\ntypedef unsigned int u32;\ntypedef " << T << " T;\n"
+      << "struct __attribute__((aligned(" << (dbl ? 16 : 8) << "))) V { T x, y; };\n"
+      << "struct TileArgs { u64 n_units; u32 pos[" << kTileMaxBits << "]; u32 first; };\n"
+      << "__device__ __forceinline__ void wave_sync() {\n"
+      << "  __builtin_amdgcn_fence(__ATOMIC_RELEASE, \"wavefront\");\n  __builtin_amdgcn_wave_barrier();\n"
+      << "  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, \"wavefront\");\n}\n"
+      // comb<L>(a, b): lanes with bit L clear get the sum of a over that bit, lanes with it set the sum of b.
+      // L = 5, 4: one swap per dword exchanges the halves; below, DPP: row_ror:8, row_half_mirror (pairs
+      // lane l with l ^ 7: the lower bits are summed later) and quad permutes.
+      << "template <int L> __device__ __forceinline__ u32 dpp(u32 v) {\n"
+      << "  constexpr int C = L == 3 ? 0x128 : L == 2 ? 0x141 : L == 1 ? 0x4E : 0xB1;\n"
+      << "  return (u32)__builtin_amdgcn_update_dpp(0, (int)v, C, 0xF, 0xF, false);\n}\n"
+      << "template <int L> __device__ __forceinline__ double comb(double a, double b) {\n"
+      << "  const u64 x = __builtin_bit_cast(u64, a), y = __builtin_bit_cast(u64, b);\n"
+      << "  if constexpr (L >= 4) {\n"
+      << "    const auto l = L == 5 ? __builtin_amdgcn_permlane32_swap((u32)x, (u32)y, false, false)\n"
+      << "                          : __builtin_amdgcn_permlane16_swap((u32)x, (u32)y, false, false);\n"
+      << "    const auto h = L == 5 ? __builtin_amdgcn_permlane32_swap((u32)(x >> 32), (u32)(y >> 32), false, false)\n"
+      << "                          : __builtin_amdgcn_permlane16_swap((u32)(x >> 32), (u32)(y >> 32), false, false);\n"
+      << "    return __builtin_bit_cast(double, ((u64)h[0] << 32) | l[0]) +\n"
+      << "           __builtin_bit_cast(double, ((u64)h[1] << 32) | l[1]);\n"
+      << "  } else {\n"
+      << "    const bool hb = (threadIdx.x >> L) & 1;\n"
+      << "    const u64 keep = hb ? y : x, send = hb ? x : y;\n"
+      << "    const u64 got = ((u64)dpp<L>((u32)(send >> 32)) << 32) | dpp<L>((u32)send);\n"
+      << "    return __builtin_bit_cast(double, keep) + __builtin_bit_cast(double, got);\n"
+      << "  }\n}\n";
+    return o.str();
+}
+
+// c = cos(a/2) of an unnormalised rotation, kept away from zero (below the
+// rounding of sin(a/2) ~ 1 in either type), and t = tan(a/2).
+template <typename T>
+void rot_numbers(const HalfAngle& h, double& c, double& t) {
+    const double cmin = sizeof(T) == 8 ? 0x1p-60 : 0x1p-26;
+    c = std::fabs(h.c) < cmin ? std::copysign(cmin, h.c) : h.c;
+    t = h.s / c;
+}
+
+}  // namespace
+
+const char* tile_kernel_name(int NV, bool dbl) {
+    return NV == 2 ? (dbl ? "vqe_tile_rev_c128" : "vqe_tile_rev_c64") : (dbl ? "vqe_tile_fwd_c128" : "vqe_tile_fwd_c64");
+}
+
+bool tile_kernel(bool dbl, const TileShape& sh, const std::vector<Gate>& gates, const PlannedPass& p, int dir,
+                 TileKernel& out, std::string& msg) {
+    if (p.K != sh.T) {
+        msg = "tile pass of the wrong size (internal error)";
+        return false;
+    }
+    int local[64] = {0};
+    for (int j = 0; j < p.K; ++j) local[p.pos[j]] = j;
+    std::vector<Gate> lg;
+    for (int gi : p.gates) {
+        Gate g = gates[gi];
+        g.q0 = local[g.q0];
+        g.q1 = local[g.q1];
+        g.q2 = local[g.q2];
+        g.q3 = local[g.q3];
+        lg.push_back(g);
+    }
+    // stages: the window's gates by R register bits
+    std::vector<PlannedPass> stages;
+    const int big = 1 << 20;
+    if (!plan_passes(sh.T, lg, PlanLimits{sh.R, big, big, big}, stages, msg)) return false;
+    Gen g;
+    g.dbl = dbl;
+    g.sh = sh;
+    g.NV = dir == 1 ? 2 : 1;
+    g.N = 1 << sh.R;
+    g.gates = &gates;
+    g.split = dir == 0;  // forward passes: half the LDS, twice the blocks per CU
+    g.out = &out;
+    g.loc.resize(g.N);
+    for (int i = 0; i < g.N; ++i) g.loc[i] = i;
+    out = TileKernel();
+
+    if (dir == 1) std::reverse(stages.begin(), stages.end());
+
+    // Layouts: the load, one per stage, the store.  Loads and stores keep the
+    // lowest bits in the lanes (128-byte runs).  The two wave bits of every
+    // layout are chosen so that as few layout changes as possible move data
+    // between waves (those need barriers): a shortest path over the pairs.
+    struct Node {
+        uint32_t used;
+        bool memory;
+    };
+    const uint32_t low = (1u << sh.low) - 1;
+    std::vector<Node> nodes{{0, true}};
+    for (const PlannedPass& s : stages) {
+        uint32_t u = 0;
+        for (int j = 0; j < s.K; ++j) u |= 1u << s.pos[j];
+        nodes.push_back({u, false});
+    }
+    nodes.push_back({0, true});
+    // a stage off the lowest bits takes the layout of the load or store beside it
+    if (nodes.size() > 2 && !(nodes[1].used & low)) {
+        nodes[1].memory = true;
+        nodes.erase(nodes.begin());
+    }
+    const bool load_is_stage = !stages.empty() && nodes[0].used != 0;
+    if (nodes.size() > 1 && !(nodes[nodes.size() - 2].used & low) && !stages.empty()) {
+        nodes[nodes.size() - 2].memory = true;
+        nodes.pop_back();
+    }
+    const int wave_bits = sh.T - sh.R - 6;
+    std::vector<uint32_t> pairs;
+    for (uint32_t m = 0; m < (1u << sh.T); ++m)
+        if (__builtin_popcount(m) == wave_bits) pairs.push_back(m);
+    auto fits = [&](const Node& nd, uint32_t w) { return !(w & nd.used) && !(nd.memory && (w & low)); };
+    std::vector<std::vector<int>> best(nodes.size(), std::vector<int>(pairs.size(), 1 << 20)), from(best);
+    for (size_t i = 0; i < nodes.size(); ++i)
+        for (size_t w = 0; w < pairs.size(); ++w) {
+            if (!fits(nodes[i], pairs[w])) continue;
+            if (i == 0) best[i][w] = 0;
+            for (size_t v = 0; i > 0 && v < pairs.size(); ++v)
+                if (best[i - 1][v] + (v != w) < best[i][w]) {
+                    best[i][w] = best[i - 1][v] + (v != w);
+                    from[i][w] = (int)v;
+                }
+        }
+    size_t at = std::min_element(best.back().begin(), best.back().end()) - best.back().begin();
+    if (best.back()[at] >= (1 << 20)) {
+        msg = "tile pass without a layout (internal error)";
+        return false;
+    }
+    std::vector<Layout> layouts(nodes.size());
+    std::vector<std::vector<int>> regs(nodes.size());
+    for (size_t i = nodes.size(); i-- > 0;) {
+        std::vector<int> wave;
+        for (int b = 0; b < sh.T; ++b)
+            if ((pairs[at] >> b) & 1) wave.push_back(b);
+        std::vector<int>& r = regs[i];
+        for (int b = 0; b < sh.T; ++b)
+            if ((nodes[i].used >> b) & 1) r.push_back(b);
+        // filled up with the highest other bits
+        for (int b = sh.T - 1; (int)r.size() < sh.R; --b)
+            if (!((nodes[i].used >> b) & 1) && !((pairs[at] >> b) & 1)) r.push_back(b);
+        std::sort(r.begin(), r.end());
+        layouts[i] = g.layout(r, wave, nodes[i].memory);
+        at = (size_t)(i ? from[i][at] : 0);
+    }
+    const Layout Lin = layouts.front(), Lout = layouts.back();
+
+    // body first: it determines the tables and the number of gradient terms
+    size_t node = 0;
+    auto go_to = [&](size_t next) {
+        const Layout &x = layouts[node], &y = layouts[next];
+        if (!std::equal(x.reg, x.reg + sh.R, y.reg) || !std::equal(x.thr, x.thr + sh.T - sh.R, y.thr)) g.exchange(x, y);
+        node = next;
+    };
+    for (size_t si = 0; si < stages.size(); ++si) {
+        go_to(si + (load_is_stage ? 0 : 1));
+        const std::vector<int>& r = regs[node];
+        int rbit[32];
+        for (int i = 0; i < sh.R; ++i) rbit[r[i]] = i;
+        std::vector<Op> ops;
+        auto add = [&](int li, bool grad) {
+            const Gate& gt = lg[li];
+            Op k{};
+            k.gate = p.gates[li];
+            int q[4];
+            const int nq = gate_qubits(gt, q);
+            uint32_t all = 0;
+            for (int i = 0; i < nq; ++i) {
+                k.bit[i] = rbit[q[i]];
+                all |= 1u << k.bit[i];
+            }
+            switch (gt.kind) {
+                case VQE_GATE_RY: k.kind = K_ROTY; k.y = all; break;
+                case VQE_GATE_RX: k.kind = K_ROTX; k.x = all; break;
+                case VQE_GATE_RZ: k.kind = K_DIAG; k.z = all; break;
+                case VQE_GATE_CZ: k.kind = K_DIAG; k.z = all; break;
+                case VQE_GATE_X: k.kind = K_FLIP; k.x = all; break;
+                case VQE_GATE_CNOT:
+                    k.kind = K_CNOT;
+                    k.z = 1u << k.bit[0];
+                    k.x = 1u << k.bit[1];
+                    break;
+                case VQE_GATE_SEXC:
+                case VQE_GATE_DEXC:
+                default: k.kind = K_R2; k.other = all; break;  // excitations, H
+            }
+            if (grad) k.kind = K_GRAD;
+            ops.push_back(k);
+        };
+        const std::vector<int>& sg = stages[si].gates;
+        if (dir == 0) {
+            for (int li : sg) add(li, false);
+        } else {
+            for (size_t i = sg.size(); i-- > 0;) {
+                if (lg[sg[i]].pidx >= 0) add(sg[i], true);
+                add(sg[i], false);
+            }
+        }
+        g.stage(std::move(ops));
+    }
+    g.scale();
+    go_to(nodes.size() - 1);
+    g.flush();
+    const std::string body = g.o.str();
+    const int chunks = g.chunk;
+    const std::vector<int> end = g.loc;  // variable of every register entry at the store
+    g.o.str("");
+
+    std::ostringstream& o = g.o;
+    const int NV = g.NV;
+    // in and out may be the same state: not __restrict__, or a pass of renames
+    // alone could load an amplitude after its place was overwritten
+    o << prelude(dbl) << "extern \"C\" __global__ void __launch_bounds__(" << kTileThreads << ", 2)\n"
+      << tile_kernel_name(NV, dbl) << "(const TileArgs a, const T* __restrict__ tab, u32 cpt, u32 mlog, u32 gs, u32 L, "
+         "const V* in0, V* out0, const V* in1, V* out1, "
+         "double* __restrict__ gpart) {\n"
+      << "  __shared__ __attribute__((aligned(16))) char lds[" << (g.elem_bytes() << sh.T) << "];\n"
+      << "  const u32 tid = threadIdx.x;\n  u64 bit[" << sh.T << "];\n"
+      << "#pragma unroll\n  for (int j = 0; j < " << sh.T << "; ++j) bit[j] = 1ull << a.pos[j];\n";
+    g.thread_offset("off_in", Lin);
+    g.thread_offset("off_out", Lout);
+    for (int c = 0; c < chunks; ++c) o << "  double acc" << c << " = 0.0;\n";
+    // Work order: blocks are dispatched round-robin over the 8 XCDs; XCD x
+    // takes the eighth x of the cosets, and gs consecutive blocks of it walk a
+    // contiguous run side by side (neighbouring cosets share pages).
+    o << "  for (u32 it = 0; it < cpt; ++it) {\n"
+      << "    u64 base;\n"
+      << "    if (mlog < 3) base = (u64)blockIdx.x * cpt + it;\n"
+      << "    else { const u32 bx = blockIdx.x >> 3; base = ((u64)(blockIdx.x & 7) << (mlog - 3)) + (u64)(bx / gs) * gs * cpt + "
+         "(u64)it * gs + bx % gs; }\n"
+      << "    if (base >= a.n_units) break;\n"
+      << "    const bool origin = base == 0 && tid == 0;\n"
+      << "#pragma unroll\n    for (int j = 0; j < " << sh.T
+      << "; ++j) { const u64 low = base & (bit[j] - 1); base = ((base ^ low) << 1) | low; }\n";
+    for (int i = 0; i < g.N; ++i) g.loc[i] = i;
+    for (int v = 0; v < NV; ++v)
+        for (int q = 0; q < g.N; ++q)
+            o << "    T r" << v << "_" << q << " = 0, i" << v << "_" << q << " = 0;\n";
+    if (NV == 1) o << "    if (a.first) { r0_0 = origin ? T(1) : T(0); } else\n";
+    o << "    {\n";
+    for (int q = 0; q < g.N; ++q)
+        for (int v = 0; v < NV; ++v)
+            o << "      const V l" << v << "_" << q << " = in" << v << "[base + off_in + (" << g.reg_offset(Lin, q) << ")];\n";
+    for (int q = 0; q < g.N; ++q)
+        for (int v = 0; v < NV; ++v)
+            o << "      r" << v << "_" << q << " = l" << v << "_" << q << ".x; i" << v << "_" << q << " = l" << v << "_" << q
+              << ".y;\n";
+    o << "    }\n" << body;
+    for (int q = 0; q < g.N; ++q)
+        for (int v = 0; v < NV; ++v)
+            o << "    out" << v << "[base + off_out + (" << g.reg_offset(Lout, q) << ")] = V{r" << v << "_" << end[q]
+              << ", i" << v << "_" << end[q] << "};\n";
+    // the next coset's first layout writes where other waves may still read, unless the wave bits agree
+    if (!std::equal(Lin.thr + 6, Lin.thr + sh.T - sh.R, Lout.thr + 6)) o << "  __syncthreads();\n";
+    o << "  }\n";
+    if (chunks) {
+        o << "  __syncthreads();\n  double* red = (double*)lds;\n";
+        for (int c = 0; c < chunks; ++c) o << "  red[(tid >> 6) * " << 64 * chunks << " + " << 64 * c << " + (tid & 63)] = acc" << c << ";\n";
+        o << "  __syncthreads();\n  if (tid < " << 64 * chunks << ") {\n    double r = red[tid];\n"
+          << "    for (int w = 1; w < " << kTileThreads / 64 << "; ++w) r += red[w * " << 64 * chunks << " + tid];\n"
+          << "    gpart[(u64)blockIdx.x * L + tid] = r;\n  }\n";
+    }
+    o << "}\n";
+    out.src = o.str();
+    return true;
+}
+
+template <typename T>
+void fill_tile_table(const TileKernel& k, const std::vector<Gate>& gates, const HalfAngle* h, int dir, T* tab) {
+    const double sign = dir ? -1.0 : 1.0;
+    double c, t;
+    for (const TileEntry& e : k.entries) {
+        T* m = tab + e.off;
+        double s = 1.0;
+        for (int g : e.rots) {
+            rot_numbers<T>(h[g], c, t);
+            s *= c;
+        }
+        switch (e.kind) {
+            case TF_ROT:
+                rot_numbers<T>(h[e.gate], c, t);
+                m[0] = (T)(sign * t);
+                break;
+            case TF_SCALE:
+                m[0] = (T)s;
+                break;
+            case TF_PHASE: {
+                // one bit after the other: RZ multiplies by e^{-i th/2} (bit clear) or e^{i th/2} (set)
+                double re[32] = {s}, im[32] = {0.0};
+                int n = 1;
+                for (int b = 0; b < 8; ++b) {
+                    if (!((e.mask >> b) & 1)) continue;
+                    double zr = 1.0, zi = 0.0;
+                    for (size_t d = 0; d < e.diag.size(); ++d) {
+                        if (gates[e.diag[d]].kind == VQE_GATE_CZ || e.diag_bits[d] != 1u << b) continue;
+                        const double gr = h[e.diag[d]].c, gi = sign * h[e.diag[d]].s, r = zr * gr - zi * gi;
+                        zi = zr * gi + zi * gr;
+                        zr = r;
+                    }
+                    for (int i = 0; i < n; ++i) {
+                        re[i + n] = re[i] * zr - im[i] * zi;
+                        im[i + n] = re[i] * zi + im[i] * zr;
+                        const double r = re[i] * zr + im[i] * zi;
+                        im[i] = im[i] * zr - re[i] * zi;
+                        re[i] = r;
+                    }
+                    n *= 2;
+                }
+                for (size_t d = 0; d < e.diag.size(); ++d) {
+                    if (gates[e.diag[d]].kind != VQE_GATE_CZ) continue;
+                    uint32_t idx = 0;  // the CZ's bits among the table's
+                    for (int b = 0, at = 0; b < 8; ++b)
+                        if ((e.mask >> b) & 1) idx |= ((e.diag_bits[d] >> b) & 1u) << at++;
+                    for (int i = 0; i < n; ++i)
+                        if (((uint32_t)i & idx) == idx) {
+                            re[i] = -re[i];
+                            im[i] = -im[i];
+                        }
+                }
+                for (int i = 0; i < n; ++i) {
+                    m[2 * i] = (T)re[i];
+                    m[2 * i + 1] = (T)im[i];
+                }
+                break;
+            }
+            case TF_R2:
+                if (gates[e.gate].kind == VQE_GATE_H) {
+                    const double r = 1.0 / std::sqrt(2.0);
+                    m[0] = m[1] = m[2] = (T)r;
+                    m[3] = (T)-r;
+                } else {  // excitations: [[c, -s], [s, c]]
+                    m[0] = m[3] = (T)h[e.gate].c;
+                    m[1] = (T)(-sign * h[e.gate].s);
+                    m[2] = (T)(sign * h[e.gate].s);
+                }
+                break;
+        }
+    }
+}
+
+template void fill_tile_table<float>(const TileKernel&, const std::vector<Gate>&, const HalfAngle*, int, float*);
+template void fill_tile_table<double>(const TileKernel&, const std::vector<Gate>&, const HalfAngle*, int, double*);
+
+}  // namespace vqe

@@ -25,7 +25,8 @@ constexpr int kBlock = 256;       // threads per block of every streaming kernel
 constexpr int kMaxBlocks = 2048;  // grid-stride kernels use at most this many blocks
 constexpr int kMaxPartBlocks = 1 << 17;  // blocks writing per-block partial sums
 constexpr int kTileBits = 10;     // amplitudes per Hamiltonian tile = 2^kTileBits
-constexpr int kMaxPlanWindow = 10;  // largest window the planner forms (mid-size tile passes)
+constexpr int kTileMaxBits = 13;      // qubits of a tile pass (specialised kernels)
+constexpr int kMaxPlanWindow = 13;  // largest window the planner forms (tile passes)
 
 // Per-pass limits of the fusion planner.
 struct PlanLimits {
@@ -430,6 +431,90 @@ struct PlannedPass {
 // lim.kmax = largest window (<= kMaxPlanWindow).
 bool plan_passes(int n, const std::vector<Gate>& gates, const PlanLimits& lim, std::vector<PlannedPass>& out,
                  std::string& msg);
+
+// Tile passes: windows of `bits` qubits that all contain qubits 0 .. low-1
+// (contiguous runs of 2^low amplitudes per load).  Unlike plan_passes, a
+// pass keeps its whole window in pos[0 .. K-1], also qubits no gate touches.
+struct TileLimits {
+    int bits, low;
+    int gates;   // gates per pass (code size of its kernel)
+    int pushes;  // parameterised gates per pass
+};
+bool plan_tiles(int n, const std::vector<Gate>& gates, const TileLimits& lim, std::vector<PlannedPass>& out,
+                std::string& msg);
+
+// ---------------------------------------------------------------- tile passes (tile.cpp)
+// One pass over a window of T = 12 or 13 qubits: a block of 256 threads holds
+// a coset (2^T amplitudes of psi, in reverse passes of lam too) in registers,
+// 2^R amplitudes per thread and vector, reads and writes the state once and
+// applies all gates of the window, in stages that each keep another R of the
+// T window bits in registers; the vectors change layout between stages
+// through LDS.  The amplitudes of a wave's access are runs of 128 bytes: the
+// 2^low lowest ones are in every window.
+struct TileShape {
+    int T, R, low;
+};
+// n < kTileBigQubits: smaller complex64 tiles, so that a 20-qubit state still
+// fills the 256 CUs.
+constexpr int kTileMinQubits = 14;
+constexpr int kTileBigQubits = 23;
+inline TileShape tile_shape(bool dbl, int n) {
+    if (dbl) return {12, 4, 3};
+    return n >= kTileBigQubits ? TileShape{13, 5, 4} : TileShape{12, 4, 3};
+}
+constexpr int kTileThreads = 256;
+constexpr int kTileMaxGates = 256;   // gates per pass (code size)
+constexpr int kTileMaxPushes = 128;  // gradient terms per pass: two per lane of a wave
+
+// Host numbers of one pass's table: for every entry what to compute from the
+// angles of an evaluation (see fill_tile_table).
+enum TileFill : uint8_t {
+    TF_ROT,    // t of an unnormalised rotation (x - t y, y + t x)
+    TF_PHASE,  // 2^m phases (re, im) of the merged diagonal gates on m bits, times the pending scale
+    TF_SCALE,  // the pending scale alone
+    TF_R2,     // a real 2x2 matrix (H, excitations): u00 u01 u10 u11
+};
+struct TileEntry {
+    TileFill kind;
+    uint32_t off;                // first scalar in the pass's table
+    int gate = -1;               // TF_ROT, TF_R2
+    uint32_t mask = 0;           // TF_PHASE: register bits of its index, ascending
+    std::vector<int> diag;       // TF_PHASE: the merged RZ / CZ gates
+    std::vector<uint32_t> diag_bits;  // ... and their register bits
+    std::vector<int> rots;       // TF_PHASE, TF_SCALE: rotations whose norms are folded in
+};
+struct TileKernel {
+    std::string src;
+    std::vector<TileEntry> entries;
+    uint32_t n_scalars = 0;
+    std::vector<int32_t> lane_param;  // reverse: parameter summed by column l of the partials (-1: none)
+};
+// Generates the kernel of one pass (dir 0 forward, 1 reverse).  Returns false
+// with msg on failure.
+bool tile_kernel(bool dbl, const TileShape& sh, const std::vector<Gate>& gates, const PlannedPass& p, int dir,
+                 TileKernel& out, std::string& msg);
+const char* tile_kernel_name(int NV, bool dbl);
+// cos and sin of half the angle of every gate.
+struct HalfAngle {
+    double c, s;
+};
+// Fills the table of one pass for the angles of an evaluation.
+template <typename T>
+void fill_tile_table(const TileKernel& k, const std::vector<Gate>& gates, const HalfAngle* h, int dir, T* tab);
+
+struct TileArgs {
+    uint64_t n_units;              // cosets of the window
+    uint32_t pos[kTileMaxBits];    // window qubits, ascending
+    uint32_t first;                // forward: stage |0...0> instead of reading the state
+};
+// L: columns per block of the gradient partials gpart (reverse passes).
+hipError_t launch_tile(void* fn, const TileArgs& a, bool reverse, const void* tab, const void* in0, void* out0,
+                       const void* in1, void* out1, double* gpart, uint32_t L, hipStream_t st);
+// Blocks of a tile pass over `units` cosets.
+uint32_t tile_blocks(uint64_t units, bool reverse);
+// out[p L + l] = sum over blocks b < nblocks of part[(p nblocks + b) L + l], p < n_pass, in a fixed order.
+hipError_t launch_tile_reduce(const double* part, uint32_t n_pass, uint32_t nblocks, uint32_t L, double* out,
+                              hipStream_t st);
 
 // ---------------------------------------------------------------- errors
 void set_error(const std::string& m);
