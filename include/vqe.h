@@ -72,10 +72,10 @@ extern "C" {
  *   SEXC on (q0, q1):          A = {q0 = 1, q1 = 0}, B = {q0 = 0, q1 = 1}
  *   DEXC on (q0, q1, q2, q3):  A = {q0 = q1 = 1, q2 = q3 = 0},
  *                              B = {q0 = q1 = 0, q2 = q3 = 1}
- * Only specialised kernels (vqe_set_specialize) and the batched small-state
- * kernel apply them; interpreted evaluations of a circuit holding one return
- * VQE_ERR_UNSUPPORTED, and the default kernel form runs such circuits
- * specialised at every size. */
+ * Specialised kernels (vqe_set_specialize) and the batched kernels apply
+ * them; interpreted evaluations of a circuit holding one return
+ * VQE_ERR_UNSUPPORTED, and the default kernel form never runs such circuits
+ * interpreted. */
 #define VQE_GATE_SEXC  7
 #define VQE_GATE_DEXC  8
 
@@ -269,7 +269,10 @@ int vqe_apply_hamiltonian(vqe_state* psi, vqe_state* lam, const vqe_hamiltonian*
                           double* energy, double* norm);
 
 /* Energy of psi(theta) = U(theta)|0...0> and its gradient dE/dtheta_k for all
- * k (grad has n_params doubles).
+ * k (grad has n_params doubles).  In the default kernel form an ADJOINT
+ * evaluation of a state that fits LDS (n <= VQE_BATCH_MAX_QUBITS_C64 /
+ * VQE_BATCH_MAX_QUBITS_C128) is one launch of the small-state kernel of the
+ * batches below, for every gate kind and with checkpoints.
  *   ADJOINT: forward sweep, lam = H psi, then one reverse sweep un-applying
  *     one gate at a time from psi and lam, with dE/dtheta_k = Im<lam|G_k|psi>
  *     / <psi|psi> just after gate k, R_k = exp(-i theta_k G_k / 2).  lam must
@@ -303,9 +306,10 @@ int vqe_energy_grad(vqe_state* psi, vqe_state* lam, const vqe_circuit* c,
  *   energy (eq. 7) and the adjoint reverse sweep.
  *   Mid-size items, above that up to VQE_BATCH_MAX_QUBITS_MID: psi and lam
  *   in device memory owned by the batch handle (2 x 2^n amplitudes per
- *   item); the gates are fused into passes over 10-qubit windows, and one
- *   launch applies pass k of every item that has one, a workgroup staging
- *   one 2^10-amplitude tile of a window in LDS at a time; then lam = H psi
+ *   item); the gates are fused into passes over 12-qubit windows that hold
+ *   qubits 0 and 1, and one launch applies pass k of every item that has
+ *   one, a workgroup staging one 2^12-amplitude tile of a window in LDS at a
+ *   time; then lam = H psi
  *   and the energy (the 13-qubit window passes of each Hamiltonian, one
  *   launch per pass index, or one tile launch for Hamiltonians without a
  *   window cover), the reverse passes likewise, and one launch reducing
@@ -359,7 +363,8 @@ int vqe_stream_destroy(void* stream);
  * method must move: 2 S per forward window pass, 4 S per reverse window
  * pass, (1 + D) S read + S written for H psi where D is the number of
  * distinct partner tiles, or 2 S (first) / 3 S (others) per window pass of H
- * psi, S per per-term sweep; S = state bytes). */
+ * psi, S per per-term sweep; S = state bytes).  A small state's evaluation in
+ * one launch counts as one reverse pass that writes 2 S. */
 #define VQE_KERNEL_WINDOW_FWD  0
 #define VQE_KERNEL_WINDOW_REV  1
 #define VQE_KERNEL_HPSI        2

@@ -95,13 +95,18 @@ struct Plan {
     int jit_dev[2] = {-1, -1};      // device they are loaded on
 };
 
-// One pass of the mid-size batched form: a window of kMidWin qubits and its
-// gates (window-local qubits) in mid_gates[gate_off, gate_off + n_gates);
-// its parameterised gates, last first, own gradient slots
-// [slot_off, slot_off + n_slots) of mid_slot_pidx.
-struct MidPlanPass {
-    uint32_t pos[kMidWin];
-    uint32_t gate_off, n_gates, slot_off, n_slots;
+// Batch programs of one amplitude type (program.cpp), made on first use: two
+// programs (forward, reverse) for a state that fits LDS, two per pass for a
+// mid-size one, a pass p as programs 2 p and 2 p + 1.  An evaluation uploads the
+// image (every program's stages, then their streams) with its numbers filled in.
+struct BatchPlan {
+    bool ready = false;
+    std::vector<PlannedPass> passes;     // mid-size: windows of kMidWin qubits
+    std::vector<Program> prog;
+    std::vector<size_t> stage_off, stream_off;  // bytes in the image
+    std::vector<char> image;             // numbers still zero
+    std::vector<size_t> slot_off;        // first gradient slot of the program (reverse ones)
+    std::vector<int32_t> slot_param;     // every reverse program's slots, in program order
 };
 
 // Tile passes of one amplitude type (tile.cpp), made on first use.
@@ -120,15 +125,10 @@ struct vqe_circuit {
     int n = 0;
     std::vector<Gate> gates;
     size_t n_params = 0;
-    std::vector<BatchGate> bgates;  // gate table of the batched small-state kernel
-    uint32_t n_mats = 0;            // matrices per evaluation (gates with a 2x2 matrix)
     Plan plan[2];  // [0]: interpreted (not built for circuits with excitation gates), [1]: specialised
     TilePlan tile[2];  // per dtype (0: complex64, 1: complex128)
     bool has_excitation = false;
-    // batched mid-size form (kMidWin < n <= kMidMaxQubits)
-    std::vector<MidPlanPass> mid;
-    std::vector<BatchGate> mid_gates;
-    std::vector<int32_t> mid_slot_pidx;
+    BatchPlan batch[2][2];  // per dtype; [1]: with the places of checkpoints (small states)
 };
 
 struct vqe_hamiltonian {
@@ -142,8 +142,15 @@ struct vqe_hamiltonian {
     // every folded coefficient real (each term has an even number of Y, as for
     // any real symmetric H): the window passes of H psi skip imaginary parts
     bool real_coeffs = true;
-    // device tables, uploaded on first use on a device (all of them, then d_ready)
+    // small states (n <= kBatchMaxQubitsC64): terms by register bucket
+    // (batch.hip), per dtype: the blocks, then their stream
+    std::vector<SmallBlock> sm_blocks[2];
+    std::vector<char> sm_stream[2];
+    SmallBlock* d_sm_blocks[2] = {nullptr, nullptr};
+    char* d_sm_stream[2] = {nullptr, nullptr};
+    // device tables, uploaded on first use on a device (in d_tables, then d_ready)
     bool d_ready = false;
+    void* d_tables = nullptr;
     GroupDesc* d_groups = nullptr;
     TermDesc<float>* d_t32 = nullptr;
     TermDesc<double>* d_t64 = nullptr;
@@ -270,56 +277,57 @@ int upload_plan(const Plan& cpl);
 bool lower_split(const std::vector<KOp>& ops, int K, int S, size_t cap, SplitOps& out);
 
 // Device copies of a Hamiltonian's tables; the handle publishes them only
-// when every one was allocated and copied (d_ready), so a failed upload
-// leaves nothing half-built behind.
+// when they were allocated and copied (d_ready), so a failed upload leaves
+// nothing half-built behind.
 void free_hamiltonian_tables(vqe_hamiltonian* h) {
-    void* ptrs[] = {h->d_groups, h->d_t32, h->d_t64, h->d_hw_groups, h->d_hw_classes, h->d_hw_t32, h->d_hw_t64};
-    for (void* p : ptrs)
-        if (p) (void)hipFree(p);
-    h->d_groups = nullptr;
-    h->d_t32 = nullptr;
-    h->d_t64 = nullptr;
-    h->d_hw_groups = nullptr;
-    h->d_hw_classes = nullptr;
-    h->d_hw_t32 = nullptr;
-    h->d_hw_t64 = nullptr;
+    if (h->d_tables) (void)hipFree(h->d_tables);
+    h->d_tables = nullptr;
     h->d_ready = false;
 }
 
-template <typename E>
-int upload_table(E** dst, const std::vector<E>& src) {
-    const size_t bytes = std::max<size_t>(src.size(), 1) * sizeof(E);
-    if (hipMalloc((void**)dst, bytes) != hipSuccess) {
-        *dst = nullptr;
-        set_error("hipMalloc of a Hamiltonian table failed");
-        return VQE_ERR_OOM;
-    }
-    if (!src.empty() && hipMemcpy(*dst, src.data(), src.size() * sizeof(E), hipMemcpyHostToDevice) != hipSuccess) {
-        set_error("hipMemcpy of a Hamiltonian table failed");
-        return VQE_ERR_DEVICE;
-    }
-    return VQE_OK;
-}
-
-// Uploads the grouped term tables to the current device (once).
+// Uploads the grouped term tables to the current device (once): one allocation
+// and one copy, which a first evaluation waits for.
 int upload_hamiltonian(const vqe_hamiltonian* ch) {
     vqe_hamiltonian* h = const_cast<vqe_hamiltonian*>(ch);
     std::lock_guard<std::mutex> g(g_upload_mu);
     if (h->d_ready) return VQE_OK;
     free_hamiltonian_tables(h);  // leftovers of an earlier failed attempt
-    int rc = upload_table(&h->d_groups, h->groups);
-    if (!rc) rc = upload_table(&h->d_t32, h->t32);
-    if (!rc) rc = upload_table(&h->d_t64, h->t64);
-    if (!rc && !h->hw_wins.empty()) {
-        rc = upload_table(&h->d_hw_groups, h->hw_groups);
-        if (!rc) rc = upload_table(&h->d_hw_classes, h->hw_classes);
-        if (!rc) rc = upload_table(&h->d_hw_t32, h->hw_t32);
-        if (!rc) rc = upload_table(&h->d_hw_t64, h->hw_t64);
+    std::vector<char> img;
+    auto each = [&](auto&& f) {
+        f(h->d_groups, h->groups);
+        f(h->d_t32, h->t32);
+        f(h->d_t64, h->t64);
+        f(h->d_hw_groups, h->hw_groups);
+        f(h->d_hw_classes, h->hw_classes);
+        f(h->d_hw_t32, h->hw_t32);
+        f(h->d_hw_t64, h->hw_t64);
+        for (int d = 0; d < 2; ++d) {
+            f(h->d_sm_blocks[d], h->sm_blocks[d]);
+            f(h->d_sm_stream[d], h->sm_stream[d]);
+        }
+    };
+    each([&](auto&, const auto& src) {
+        const size_t at = (img.size() + 255) / 256 * 256, bytes = src.size() * sizeof(src[0]);
+        img.resize(at + bytes);
+        if (bytes) std::memcpy(&img[at], src.data(), bytes);
+    });
+    img.resize(img.size() + 256);  // an empty table at the end points inside too
+    if (hipMalloc(&h->d_tables, img.size()) != hipSuccess) {
+        h->d_tables = nullptr;
+        set_error("hipMalloc of the Hamiltonian tables failed");
+        return VQE_ERR_OOM;
     }
-    if (rc) {
+    if (hipMemcpy(h->d_tables, img.data(), img.size(), hipMemcpyHostToDevice) != hipSuccess) {
+        set_error("hipMemcpy of the Hamiltonian tables failed");
         free_hamiltonian_tables(h);
-        return rc;
+        return VQE_ERR_DEVICE;
     }
+    size_t at = 0;
+    each([&](auto& dst, const auto& src) {
+        at = (at + 255) / 256 * 256;
+        dst = (std::remove_reference_t<decltype(dst)>)((char*)h->d_tables + at);
+        at += src.size() * sizeof(src[0]);
+    });
     h->d_ready = true;
     return VQE_OK;
 }
@@ -544,6 +552,51 @@ void plan_hwin(vqe_hamiltonian* h) {
     h->hw_t64.swap(ht64);
 }
 
+// Blocks of a small Hamiltonian for the whole-state-in-LDS kernel: per group its
+// terms sorted by their z bits on the kProgBits highest bits of the tile; a group
+// that a block or a count of 255 cannot hold is continued in another of the same x.
+template <typename T>
+void plan_small(vqe_hamiltonian* h, const std::vector<TermDesc<T>>& terms, std::vector<SmallBlock>& blocks,
+                std::vector<char>& stream) {
+    const int sh = batch_bits(h->n) - kProgBits;
+    auto room = [&] { return kProgBlock - blocks.back().bytes; };
+    for (const GroupDesc& g : h->groups) {
+        std::vector<uint32_t> order;
+        for (uint32_t t = g.begin; t < g.end; ++t) order.push_back(t);
+        std::stable_sort(order.begin(), order.end(), [&](uint32_t a, uint32_t b) { return (h->z[a] >> sh) < (h->z[b] >> sh); });
+        for (size_t i = 0; i < order.size();) {
+            if (blocks.empty() || room() < sizeof(SmallGroup) + sizeof(SmallTerm<T>)) {
+                SmallBlock b{};
+                stream.resize((stream.size() + 15) / 16 * 16);
+                b.off = (uint32_t)stream.size();
+                blocks.push_back(b);
+            }
+            const size_t most = (room() - sizeof(SmallGroup)) / sizeof(SmallTerm<T>);
+            SmallGroup sg{};
+            sg.x = (uint32_t)g.x;
+            const size_t at = stream.size();
+            stream.resize(at + sizeof(SmallGroup));
+            for (; i < order.size() && sg.n_terms < most; ++i) {
+                const uint32_t t = order[i], u = (uint32_t)(h->z[t] >> sh);
+                if (((sg.count[u >> 2] >> (8 * (u & 3))) & 255u) == 255u) break;
+                sg.count[u >> 2] += 1u << (8 * (u & 3));
+                SmallTerm<T> tm{};
+                tm.zt = (uint32_t)h->z[t] & ((1u << sh) - 1);
+                tm.cre = terms[t].cre;
+                tm.cim = terms[t].cim;
+                const char* raw = (const char*)&tm;
+                stream.insert(stream.end(), raw, raw + sizeof(tm));
+                ++sg.n_terms;
+            }
+            std::memcpy(&stream[at], &sg, sizeof(sg));
+            blocks.back().bytes = (uint32_t)(stream.size() - blocks.back().off);
+            ++blocks.back().n_groups;
+        }
+    }
+    // blocks are read 16 bytes at a time, the last one past its end
+    stream.resize((stream.size() + 15) / 16 * 16);
+}
+
 // Per-block partial-sum buffer of a state: room for the largest launch
 // (kMaxPartBlocks blocks x kMaxGradSlots slots).
 size_t part_doubles() { return std::max((size_t)kMaxPartBlocks * kMaxGradSlots, (size_t)kMaxBlocks * 2); }
@@ -560,6 +613,14 @@ int ensure_part(vqe_state* s) {
 
 // Angle of gate g under params.
 double angle_of(const Gate& g, const double* params) { return g.pidx >= 0 ? params[g.pidx] : g.angle; }
+
+void half_angles(const vqe_circuit* c, const double* params, std::vector<HalfAngle>& h) {
+    h.resize(c->gates.size());
+    for (size_t i = 0; i < h.size(); ++i) {
+        const double a = angle_of(c->gates[i], params) / 2;
+        h[i] = HalfAngle{std::cos(a), std::sin(a)};
+    }
+}
 
 template <typename T>
 void fill_matrix(Mat2<T>& m, const Gate& g, double th, bool inverse) {
@@ -894,11 +955,8 @@ template <typename T>
 int upload_tables(vqe_state* s, const vqe_circuit* c, const TilePlan& tp, const double* params, const T** out) {
     const size_t bytes = std::max<size_t>(tp.tab_total, 1) * sizeof(T);
     if (int rc = stage_mats(s, bytes)) return rc;
-    std::vector<HalfAngle> h(c->gates.size());
-    for (size_t i = 0; i < h.size(); ++i) {
-        const double a = angle_of(c->gates[i], params) / 2;
-        h[i] = HalfAngle{std::cos(a), std::sin(a)};
-    }
+    std::vector<HalfAngle> h;
+    half_angles(c, params, h);
     for (int dir = 0; dir < 2; ++dir)
         for (size_t p = 0; p < tp.passes.size(); ++p)
             fill_tile_table<T>(tp.k[dir][p], c->gates, h.data(), dir, (T*)s->h_mats + tp.tab_off[dir][p]);
@@ -1368,53 +1426,6 @@ void free_circuit(vqe_circuit* c) {
     delete c;
 }
 
-// Tile passes of the batched mid-size form: the planner's windows of at most
-// kMidWin qubits, each padded to kMidWin with the lowest qubits outside it,
-// and the pass's gates rewritten to window-local qubits and patterns.
-int build_mid_plan(vqe_circuit* c) {
-    if (c->n <= kMidWin || c->n > kMidMaxQubits) return VQE_OK;
-    std::vector<PlannedPass> passes;
-    std::string msg;
-    if (!plan_passes(c->n, c->gates, kMidLimits, passes, msg)) {
-        set_error("vqe_circuit_create: " + msg);
-        return VQE_ERR_STATE;
-    }
-    if (passes.empty()) passes.emplace_back();  // no gates: one pass that only prepares |0...0>
-    for (const PlannedPass& p : passes) {
-        uint64_t w = 0;
-        for (int j = 0; j < p.K; ++j) w |= 1ull << p.pos[j];
-        for (int q = 0; __builtin_popcountll(w) < kMidWin; ++q) w |= 1ull << q;
-        MidPlanPass mp{};
-        int local[64] = {0};
-        int k = 0;
-        for (int q = 0; q < c->n; ++q)
-            if ((w >> q) & 1) {
-                local[q] = k;
-                mp.pos[k++] = (uint32_t)q;
-            }
-        mp.gate_off = (uint32_t)c->mid_gates.size();
-        mp.n_gates = (uint32_t)p.gates.size();
-        mp.slot_off = (uint32_t)c->mid_slot_pidx.size();
-        for (int gi : p.gates) {
-            const Gate& g = c->gates[gi];
-            BatchGate bg = c->bgates[gi];
-            bg.q0 = (uint8_t)local[g.q0];
-            bg.q1 = (uint8_t)local[g.q1];
-            if (is_excitation(g.kind)) {
-                const bool dbl = g.kind == VQE_GATE_DEXC;
-                bg.pa = (uint16_t)(dbl ? (1u << local[g.q0]) | (1u << local[g.q1]) : (1u << local[g.q0]));
-                bg.pb = (uint16_t)(dbl ? (1u << local[g.q2]) | (1u << local[g.q3]) : (1u << local[g.q1]));
-            }
-            c->mid_gates.push_back(bg);
-        }
-        for (size_t j = p.gates.size(); j-- > 0;)
-            if (c->gates[p.gates[j]].pidx >= 0) c->mid_slot_pidx.push_back(c->gates[p.gates[j]].pidx);
-        mp.n_slots = (uint32_t)c->mid_slot_pidx.size() - mp.slot_off;
-        c->mid.push_back(mp);
-    }
-    return VQE_OK;
-}
-
 // Plans fused passes within the given limits and lowers them to kernel op
 // lists (forward, and reverse with gradient ops), per dtype also to the
 // lane-split layout.
@@ -1587,35 +1598,144 @@ int upload_plan(const Plan& cpl) {
 
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
+int max_small(int dtype) { return dtype == VQE_C64 ? kBatchMaxQubitsC64 : kBatchMaxQubitsC128; }
+
+// Plans the batch programs of c for dtype index d (once); ckpt: programs of a
+// small state that may stop at checkpoints (the forward one is the same).
+int ensure_batch(const vqe_circuit* cc, int d, bool ckpt = false) {
+    vqe_circuit* c = const_cast<vqe_circuit*>(cc);
+    BatchPlan& bp = c->batch[d][ckpt ? 1 : 0];
+    std::lock_guard<std::mutex> g(g_upload_mu);
+    if (bp.ready) return VQE_OK;
+    BatchPlan np;
+    std::string msg;
+    int local[64];
+    auto add = [&](int bits, const std::vector<int>& gates) {
+        ProgramPlan plan;
+        if (!plan_program(bits, c->gates, gates, local, plan, msg)) return false;
+        for (int dir = 0; dir < 2; ++dir) {
+            Program p;
+            if (!build_program(d == 1, bits, c->gates, plan, dir, dir == 0 || ckpt, p, msg)) return false;
+            np.slot_off.push_back(np.slot_param.size());
+            np.slot_param.insert(np.slot_param.end(), p.slot_param.begin(), p.slot_param.end());
+            np.prog.push_back(std::move(p));
+        }
+        return true;
+    };
+    bool ok = true;
+    if (c->n <= max_small(d ? VQE_C128 : VQE_C64)) {
+        std::vector<int> all(c->gates.size());
+        std::iota(all.begin(), all.end(), 0);
+        std::iota(local, local + 64, 0);
+        ok = add(batch_bits(c->n), all);
+    } else {
+        ok = plan_tiles(c->n, c->gates, TileLimits{kMidWin, kMidLow, 1 << 20, kMidMaxSlots}, np.passes, msg);
+        if (ok && np.passes.empty()) {  // no gates: one pass that only prepares |0...0>
+            np.passes.emplace_back();
+            for (int q = 0; q < kMidWin; ++q) np.passes[0].pos[np.passes[0].K++] = q;
+        }
+        for (size_t p = 0; ok && p < np.passes.size(); ++p) {
+            for (int j = 0; j < kMidWin; ++j) local[np.passes[p].pos[j]] = j;
+            ok = add(kMidWin, np.passes[p].gates);
+        }
+    }
+    if (!ok) {
+        set_error(msg);
+        return VQE_ERR_STATE;
+    }
+    size_t at = 0;
+    for (const Program& p : np.prog) {
+        np.stage_off.push_back(at);
+        at += p.stages.size() * sizeof(ProgStage);
+    }
+    for (const Program& p : np.prog) {
+        at = align_up(at, 64);
+        np.stream_off.push_back(at);
+        at += p.stream.size() * 4;
+    }
+    np.image.assign(align_up(std::max<size_t>(at, 64), 64), 0);
+    for (size_t k = 0; k < np.prog.size(); ++k) {
+        Program& p = np.prog[k];
+        if (!p.stages.empty()) std::memcpy(&np.image[np.stage_off[k]], p.stages.data(), p.stages.size() * sizeof(ProgStage));
+        if (!p.stream.empty()) std::memcpy(&np.image[np.stream_off[k]], p.stream.data(), p.stream.size() * 4);
+        std::vector<uint32_t>().swap(p.stream);
+    }
+    np.ready = true;
+    bp = std::move(np);
+    return VQE_OK;
+}
+
+// The image of a batch plan with the numbers of one evaluation, to dst.
+template <typename T>
+void fill_batch_image(const vqe_circuit* c, const BatchPlan& bp, const double* params, std::vector<HalfAngle>& h, char* dst) {
+    half_angles(c, params, h);
+    std::memcpy(dst, bp.image.data(), bp.image.size());
+    for (size_t k = 0; k < bp.prog.size(); ++k)
+        fill_tile_table<T>(bp.prog[k].table, c->gates, h.data(), (int)(k & 1), (T*)(dst + bp.stream_off[k]));
+}
+
+// Descriptor of one small evaluation; image, out and part are device addresses.
+template <typename T>
+BatchDesc<T> small_desc(const vqe_circuit* c, const BatchPlan& bp, const vqe_hamiltonian* h, const char* image,
+                        double* out, double* part) {
+    BatchDesc<T> d{};
+    d.n = c->n;
+    d.bits = batch_bits(c->n);
+    d.n_fwd = (uint32_t)bp.prog[0].stages.size();
+    d.n_rev = (uint32_t)bp.prog[1].stages.size();
+    const int dt = sizeof(T) == 8 ? 1 : 0;
+    d.n_blocks = (uint32_t)h->sm_blocks[dt].size();
+    d.n_slots = (uint32_t)bp.slot_param.size();
+    d.real = h->real_coeffs ? 1 : 0;
+    d.fwd = (const ProgStage*)(image + bp.stage_off[0]);
+    d.rev = (const ProgStage*)(image + bp.stage_off[1]);
+    d.fwd_stream = image + bp.stream_off[0];
+    d.rev_stream = image + bp.stream_off[1];
+    d.ham = h->d_sm_blocks[dt];
+    d.ham_stream = h->d_sm_stream[dt];
+    d.out = out;
+    d.part = part;
+    return d;
+}
+
+void small_results(const vqe_circuit* c, const BatchPlan& bp, const double* r, double* energy, double* grad) {
+    *energy = r[0];
+    std::fill(grad, grad + c->n_params, 0.0);
+    for (size_t s = 0; s < bp.slot_param.size(); ++s) grad[bp.slot_param[s]] += r[2 + s];
+}
+
+// Raises the dynamic LDS limit of the small-state kernels once per process.
+int small_lds_limit() {
+    static std::once_flag once;
+    static hipError_t rc = hipSuccess;
+    std::call_once(once, [] { rc = batch_set_lds_limit(); });
+    if (rc != hipSuccess) {
+        set_error(std::string("cannot raise the LDS limit: ") + hipGetErrorString(rc));
+        return VQE_ERR_DEVICE;
+    }
+    return VQE_OK;
+}
+
+// Small items: descriptors and tables in one copy, one launch, results
+// written to the pinned buffer by the kernel itself.
 template <typename T>
 int batch_impl(vqe_batch* b, size_t n_items, const vqe_batch_item* items) {
-    const int max_q = b->dtype == VQE_C64 ? kBatchMaxQubitsC64 : kBatchMaxQubitsC128;
-    size_t n_gates = 0, n_mats = 1, n_out = 0;
-    int max_n = 1;
+    const int dt = sizeof(T) == 8 ? 1 : 0;
+    size_t n_img = 0, n_out = 0, n_part = 0;
+    int max_bits = kBatchMinBits;
     for (size_t i = 0; i < n_items; ++i) {
-        const vqe_batch_item& it = items[i];
-        if (!it.circuit || !it.hamiltonian || !it.energy || (it.n_params && (!it.params || !it.grad))) {
-            set_error("vqe_batch_energy_grad: item " + std::to_string(i) + " has a null field");
-            return VQE_ERR_ARG;
-        }
-        const vqe_circuit* c = it.circuit;
-        if (c->n > max_q || it.hamiltonian->n != c->n) {
-            set_error("vqe_batch_energy_grad: item " + std::to_string(i) + " has " + std::to_string(c->n) +
-                      " qubits (limit " + std::to_string(max_q) + ") or a Hamiltonian of another size");
-            return VQE_ERR_ARG;
-        }
-        if (int rc = check_params(c, it.params, it.n_params, "vqe_batch_energy_grad")) return rc;
-        if (int rc = upload_hamiltonian(it.hamiltonian)) return rc;
-        n_gates += c->bgates.size();
-        n_mats += c->n_mats;
-        n_out += 1 + c->n_params;
-        max_n = std::max(max_n, c->n);
+        const vqe_circuit* c = items[i].circuit;
+        if (int rc = ensure_batch(c, dt)) return rc;
+        if (int rc = upload_hamiltonian(items[i].hamiltonian)) return rc;
+        n_img += c->batch[dt][0].image.size();
+        n_out += 2 + c->batch[dt][0].slot_param.size();
+        n_part += 8 * c->batch[dt][0].slot_param.size();
+        max_bits = std::max(max_bits, batch_bits(c->n));
     }
-    const size_t o_items = 0;
-    const size_t o_gates = align_up(o_items + n_items * sizeof(BatchDesc<T>), 256);
-    const size_t o_mats = align_up(o_gates + std::max<size_t>(n_gates, 1) * sizeof(BatchGate), 256);
-    const size_t o_out = align_up(o_mats + n_mats * sizeof(Mat2<T>), 256);
-    const size_t total = align_up(o_out + n_out * sizeof(double), 256);
+    const size_t o_img = align_up(n_items * sizeof(BatchDesc<T>), 256);
+    const size_t o_out = align_up(o_img + n_img, 256);  // pinned: results; device: sums per wave
+    const size_t host = o_out + n_out * sizeof(double), dev = o_out + std::max<size_t>(n_part, 1) * sizeof(double);
+    const size_t total = std::max(host, dev);
     if (total > b->d_cap) {
         VQE_HIP(hipStreamSynchronize(b->stream));
         if (b->d_buf) VQE_HIP(hipFree(b->d_buf));
@@ -1631,50 +1751,74 @@ int batch_impl(vqe_batch* b, size_t n_items, const vqe_batch_item* items) {
     }
     char* h = (char*)b->h_buf;
     char* d = (char*)b->d_buf;
-    auto* hi = (BatchDesc<T>*)(h + o_items);
-    auto* hg = (BatchGate*)(h + o_gates);
-    auto* hm = (Mat2<T>*)(h + o_mats);
-    size_t g_off = 0, m_off = 0, out_off = 0;
+    double* out = (double*)(h + o_out);
+    size_t img = o_img, o = 0, part = 0;
+    std::vector<HalfAngle> ha;
     for (size_t i = 0; i < n_items; ++i) {
         const vqe_circuit* c = items[i].circuit;
-        const vqe_hamiltonian* hh = items[i].hamiltonian;
-        BatchDesc<T> bd{};
-        bd.n = c->n;
-        bd.n_gates = (uint32_t)c->bgates.size();
-        bd.gate_off = (uint32_t)g_off;
-        bd.mat_off = (uint32_t)m_off;
-        bd.n_groups = (uint32_t)hh->groups.size();
-        bd.n_params = (uint32_t)c->n_params;
-        bd.out_off = out_off;
-        bd.groups = hh->d_groups;
-        bd.terms = terms_of<T>(hh);
-        hi[i] = bd;
-        for (size_t k = 0; k < c->bgates.size(); ++k) {
-            hg[g_off + k] = c->bgates[k];
-            const Gate& gt = c->gates[k];
-            if (c->bgates[k].type == OP_U2 || c->bgates[k].type == OP_PAIR2)
-                fill_matrix(hm[m_off + c->bgates[k].mat], gt, angle_of(gt, items[i].params), false);
-        }
-        g_off += c->bgates.size();
-        m_off += c->n_mats;
-        out_off += 1 + c->n_params;
+        const BatchPlan& bp = c->batch[dt][0];
+        ((BatchDesc<T>*)h)[i] = small_desc<T>(c, bp, items[i].hamiltonian, d + img, out + o, (double*)(d + o_out) + part);
+        fill_batch_image<T>(c, bp, items[i].params, ha, h + img);
+        img += bp.image.size();
+        o += 2 + bp.slot_param.size();
+        part += 8 * bp.slot_param.size();
     }
-    std::memset(&hm[m_off], 0, sizeof(Mat2<T>));
-    VQE_HIP(hipMemcpyAsync(d, h, o_out, hipMemcpyHostToDevice, b->stream));
-    VQE_HIP(launch_batch<T>((const BatchDesc<T>*)(d + o_items), (uint32_t)n_items, (const BatchGate*)(d + o_gates),
-                            (const Mat2<T>*)(d + o_mats), (double*)(d + o_out), max_n, b->stream));
-    VQE_HIP(hipMemcpyAsync(h + o_out, d + o_out, n_out * sizeof(double), hipMemcpyDeviceToHost, b->stream));
+    VQE_HIP(hipMemcpyAsync(d, h, o_img + n_img, hipMemcpyHostToDevice, b->stream));
+    VQE_HIP(launch_batch<T>((const BatchDesc<T>*)d, (uint32_t)n_items, max_bits, b->stream));
     VQE_HIP(hipStreamSynchronize(b->stream));
-    const double* r = (const double*)(h + o_out);
-    out_off = 0;
+    o = 0;
     for (size_t i = 0; i < n_items; ++i) {
-        const vqe_circuit* c = items[i].circuit;
-        *items[i].energy = r[out_off];
-        for (size_t k = 0; k < c->n_params; ++k) items[i].grad[k] = r[out_off + 1 + k];
-        out_off += 1 + c->n_params;
+        const BatchPlan& bp = items[i].circuit->batch[dt][0];
+        small_results(items[i].circuit, bp, out + o, items[i].energy, items[i].grad);
+        o += 2 + bp.slot_param.size();
     }
     return VQE_OK;
 }
+
+// vqe_energy_grad of one state that fits LDS: the same kernel, which also
+// leaves the state where the reverse sweep ends.
+template <typename T>
+int small_grad(vqe_state* psi, vqe_state* lam, const vqe_circuit* c, const double* params, const vqe_hamiltonian* h,
+               const vqe_grad_opts* o, double* energy, double* grad) {
+    const int dt = sizeof(T) == 8 ? 1 : 0;
+    if (int rc = small_lds_limit()) return rc;
+    const bool ckpt = o && o->n_ckpt > 0;
+    if (int rc = ensure_batch(c, dt, ckpt)) return rc;
+    const BatchPlan& bp = c->batch[dt][ckpt ? 1 : 0];
+    const size_t slots = bp.slot_param.size();
+    if (int rc = ensure_res(psi, 2 + 8 * slots)) return rc;  // device: sums per wave; pinned: results
+    // checkpoints at evenly spaced groups of stages
+    std::vector<BatchCkpt> ck;
+    const std::vector<uint32_t>&mf = bp.prog[0].mark, &mr = bp.prog[1].mark;
+    for (int k = 0, n = o ? o->n_ckpt : 0; k < n; ++k) {
+        const size_t at = (size_t)std::llround((double)(k + 1) * (double)mf.size() / (double)(n + 1));
+        if (at < 1 || at >= mf.size() || (!ck.empty() && ck.back().fwd_end == mf[at - 1])) continue;
+        if (mf[at - 1] == ~0u || mr[mf.size() - at - 1] == ~0u) continue;  // inside a stage of either program
+        ck.push_back(BatchCkpt{o->ckpt[k]->data, mf[at - 1], mr[mf.size() - at - 1]});
+    }
+    const size_t o_ck = align_up(sizeof(BatchDesc<T>), 256);
+    const size_t o_img = align_up(o_ck + ck.size() * sizeof(BatchCkpt), 256), bytes = o_img + bp.image.size();
+    if (int rc = stage_mats(psi, bytes)) return rc;
+    BatchDesc<T> d = small_desc<T>(c, bp, h, (const char*)psi->d_mats + o_img, psi->h_res, psi->d_res);
+    d.psi_out = psi->data;
+    d.lam_out = lam->data;
+    d.n_ckpt = (uint32_t)ck.size();
+    d.ckpt = (const BatchCkpt*)((char*)psi->d_mats + o_ck);
+    std::memcpy(psi->h_mats, &d, sizeof(d));
+    if (!ck.empty()) std::memcpy((char*)psi->h_mats + o_ck, ck.data(), ck.size() * sizeof(BatchCkpt));
+    std::vector<HalfAngle> ha;
+    fill_batch_image<T>(c, bp, params, ha, (char*)psi->h_mats + o_img);
+    VQE_HIP(hipMemcpyAsync(psi->d_mats, psi->h_mats, bytes, hipMemcpyHostToDevice, psi->stream));
+    {
+        ProfScope ps(VQE_KERNEL_WINDOW_REV, 2.0 * (double)psi->bytes, psi->stream);
+        VQE_HIP(launch_batch<T>((const BatchDesc<T>*)psi->d_mats, 1, d.bits, psi->stream));
+    }
+    VQE_HIP(hipEventRecord(psi->mats_ev, psi->stream));
+    VQE_HIP(hipStreamSynchronize(psi->stream));
+    small_results(c, bp, psi->h_res, energy, grad);
+    return VQE_OK;
+}
+
 // Bytes of one state of n qubits in the mid-size buffer (256-byte aligned).
 size_t st_bytes_half(int n, size_t amp) { return align_up(((size_t)1 << n) * amp, 256); }
 
@@ -1710,30 +1854,33 @@ int mid_reserve(vqe_batch* b, size_t dev, size_t host) {
     return VQE_OK;
 }
 
-// Mid-size items (LDS limit < n <= kMidMaxQubits): forward tile passes, one
-// launch per pass index over every item that has that pass; lam = H psi over
-// tiles; reverse tile passes likewise; one reduction launch; results to the
-// host.  Per item: psi and lam in the batch's device buffer, n_blk =
+// Mid-size items (LDS limit < n <= kMidMaxQubits): forward passes, one launch
+// per pass index over every item that has that pass; lam = H psi; reverse
+// passes likewise; one reduction launch that writes the results to the pinned
+// buffer.  Per item: psi and lam in the batch's device buffer, n_blk =
 // min(2^(n - kMidWin), kMidMaxBlocks) blocks per launch.
 template <typename T>
 int mid_impl(vqe_batch* b, const vqe_batch_item* items, const std::vector<size_t>& idx) {
+    const int dt = sizeof(T) == 8 ? 1 : 0;
     const size_t m = idx.size();
     const size_t amp = 2 * sizeof(T);
     // lam = H psi: window passes (hwin_batch_kernel, one launch per pass index
     // and coefficient form) where the Hamiltonian has a window cover, else the
     // tile kernel (mid_hpsi_kernel)
     std::vector<uint32_t> nblk(m), nblk_e(m);
-    std::vector<uint64_t> ncos(m), part_base(m), part_s(m), red_base(m), st_off(m), m_off(m);
+    std::vector<uint64_t> part_base(m), part_s(m), red_base(m), st_off(m), img_off(m);
     std::vector<char> use_hw(m);
-    size_t n_gates = 0, n_mats = 1, n_fwd = 0, n_part = 0, n_red = 0, st_bytes = 0, n_hw = 0, n_tile = 0;
+    size_t n_img = 0, n_pass = 0, n_part = 0, n_red = 0, st_bytes = 0, n_hw = 0, n_tile = 0;
     size_t pmax = 0, hmax = 0;
     for (size_t k = 0; k < m; ++k) {
         const vqe_circuit* c = items[idx[k]].circuit;
         const vqe_hamiltonian* hh = items[idx[k]].hamiltonian;
-        ncos[k] = 1ull << (c->n - kMidWin);
-        nblk[k] = (uint32_t)std::min<uint64_t>(ncos[k], kMidMaxBlocks);
+        if (int rc = ensure_batch(c, dt)) return rc;
+        if (int rc = upload_hamiltonian(hh)) return rc;
+        const BatchPlan& bp = c->batch[dt][0];
+        nblk[k] = (uint32_t)std::min<uint64_t>(1ull << (c->n - kMidWin), kMidMaxBlocks);
         use_hw[k] = !hh->hw_wins.empty();
-        nblk_e[k] = use_hw[k] ? (uint32_t)std::min<uint64_t>(1ull << (c->n - kHwBits), kMidMaxBlocks) : nblk[k];
+        nblk_e[k] = (uint32_t)std::min<uint64_t>(1ull << (c->n - (use_hw[k] ? kHwBits : kMidTileBits)), kMidMaxBlocks);
         if (use_hw[k]) {
             n_hw += hh->hw_wins.size();
             hmax = std::max(hmax, hh->hw_wins.size());
@@ -1742,71 +1889,64 @@ int mid_impl(vqe_batch* b, const vqe_batch_item* items, const std::vector<size_t
         }
         part_base[k] = n_part;
         part_s[k] = n_part + 2 * (size_t)nblk_e[k];
-        n_part += 2 * (size_t)nblk_e[k] + c->mid_slot_pidx.size() * (size_t)nblk[k];
+        n_part += 2 * (size_t)nblk_e[k] + bp.slot_param.size() * (size_t)nblk[k];
         red_base[k] = n_red;
-        n_red += 2 + c->mid_slot_pidx.size();
+        n_red += 2 + bp.slot_param.size();
         st_off[k] = st_bytes;
-        st_bytes += 2 * align_up(((size_t)1 << c->n) * amp, 256);
-        m_off[k] = n_mats;
-        n_gates += c->mid_gates.size();
-        n_mats += c->n_mats;
-        n_fwd += c->mid.size();
-        pmax = std::max(pmax, c->mid.size());
-        if (int rc = upload_hamiltonian(items[idx[k]].hamiltonian)) return rc;
+        st_bytes += 2 * st_bytes_half(c->n, amp);
+        img_off[k] = n_img;
+        n_img += bp.image.size();
+        n_pass += bp.passes.size();
+        pmax = std::max(pmax, bp.passes.size());
     }
-    // host-written tables | out, then (device only) partial sums | states
+    // host-written tables, then results (pinned) or partial sums | states (device)
     const size_t o_fwd = 0;
-    const size_t o_rev = align_up(o_fwd + n_fwd * sizeof(MidPass), 256);
-    const size_t o_ham = align_up(o_rev + n_fwd * sizeof(MidPass), 256);
+    const size_t o_rev = align_up(o_fwd + n_pass * sizeof(MidPass), 256);
+    const size_t o_ham = align_up(o_rev + n_pass * sizeof(MidPass), 256);
     const size_t o_hw = align_up(o_ham + std::max<size_t>(n_tile, 1) * sizeof(MidHam), 256);
     const size_t o_red = align_up(o_hw + std::max<size_t>(n_hw, 1) * sizeof(HwItem), 256);
-    const size_t o_gates = align_up(o_red + n_red * sizeof(MidRed), 256);
-    const size_t o_mats = align_up(o_gates + std::max<size_t>(n_gates, 1) * sizeof(BatchGate), 256);
-    const size_t o_out = align_up(o_mats + (n_mats + 1) * sizeof(Mat2<T>), 256);  // + a zero matrix at the end
-    const size_t o_part = align_up(o_out + n_red * sizeof(double), 256);
-    const size_t o_st = align_up(o_part + n_part * sizeof(double), 256);
-    if (int rc = mid_reserve(b, o_st + st_bytes, o_part)) return rc;
+    const size_t o_img = align_up(o_red + n_red * sizeof(MidRed), 256);
+    const size_t o_out = align_up(o_img + n_img, 256);
+    const size_t o_st = align_up(o_out + n_part * sizeof(double), 256);
+    if (int rc = mid_reserve(b, o_st + st_bytes, o_out + n_red * sizeof(double))) return rc;
     char* h = (char*)b->mh_buf;
     char* d = (char*)b->md_buf;
     auto* hf = (MidPass*)(h + o_fwd);
     auto* hr = (MidPass*)(h + o_rev);
     auto* hh = (MidHam*)(h + o_ham);
     auto* hred = (MidRed*)(h + o_red);
-    auto* hg = (BatchGate*)(h + o_gates);
-    auto* hm = (Mat2<T>*)(h + o_mats);
-    std::memset(&hm[0], 0, sizeof(Mat2<T>));
-    std::memset(&hm[n_mats], 0, sizeof(Mat2<T>));
-    double* part = (double*)(d + o_part);
-    // gates, matrices, tile-form H psi and reduction descriptors per item
     auto* hw = (HwItem*)(h + o_hw);
-    size_t g_off = 0, n_th = 0;
+    double* part = (double*)(d + o_out);
+    double* out = (double*)(h + o_out);
+    auto psi_of = [&](size_t k) { return d + o_st + st_off[k]; };
+    auto lam_of = [&](size_t k) { return d + o_st + st_off[k] + st_bytes_half(items[idx[k]].circuit->n, amp); };
+    // numbers, tile-form H psi and reduction descriptors per item
+    size_t n_th = 0;
     uint32_t hblk = 0;
+    std::vector<HalfAngle> ha;
     for (size_t k = 0; k < m; ++k) {
         const vqe_batch_item& it = items[idx[k]];
         const vqe_circuit* c = it.circuit;
-        std::copy(c->mid_gates.begin(), c->mid_gates.end(), hg + g_off);
-        for (size_t i = 0; i < c->gates.size(); ++i)
-            if (c->bgates[i].type == OP_U2 || c->bgates[i].type == OP_PAIR2)
-                fill_matrix(hm[m_off[k] + c->bgates[i].mat], c->gates[i], angle_of(c->gates[i], it.params), false);
+        const BatchPlan& bp = c->batch[dt][0];
+        fill_batch_image<T>(c, bp, it.params, ha, h + o_img + img_off[k]);
         if (!use_hw[k]) {
             MidHam mh{};
-            mh.psi = d + o_st + st_off[k];
-            mh.lam = d + o_st + st_off[k] + st_bytes_half(c->n, amp);
+            mh.psi = psi_of(k);
+            mh.lam = lam_of(k);
             mh.groups = it.hamiltonian->d_groups;
             mh.terms = terms_of<T>(it.hamiltonian);
-            mh.n_tiles = ncos[k];
+            mh.n_tiles = 1ull << (c->n - kMidTileBits);
             mh.part_off = part_base[k];
             mh.n_groups = (uint32_t)it.hamiltonian->groups.size();
             mh.blk_begin = hblk;
-            mh.n_blk = nblk[k];
+            mh.n_blk = nblk_e[k];
             hh[n_th++] = mh;
-            hblk += nblk[k];
+            hblk += nblk_e[k];
         }
         hred[red_base[k]] = MidRed{part_base[k], nblk_e[k], 0};
         hred[red_base[k] + 1] = MidRed{part_base[k] + nblk_e[k], nblk_e[k], 0};
-        for (size_t sl = 0; sl < c->mid_slot_pidx.size(); ++sl)
+        for (size_t sl = 0; sl < bp.slot_param.size(); ++sl)
             hred[red_base[k] + 2 + sl] = MidRed{part_s[k] + sl * (uint64_t)nblk[k], nblk[k], 0};
-        g_off += c->mid_gates.size();
     }
     // window-form H psi descriptors, grouped by launch: pass index, then real
     // coefficients or not
@@ -1827,8 +1967,8 @@ int mid_impl(vqe_batch* b, const vqe_batch_item* items, const std::vector<size_t
                     const vqe_circuit* c = items[idx[k]].circuit;
                     HwItem x{};
                     x.w = H->hw_wins[p];
-                    x.psi = d + o_st + st_off[k];
-                    x.lam = d + o_st + st_off[k] + st_bytes_half(c->n, amp);
+                    x.psi = psi_of(k);
+                    x.lam = lam_of(k);
                     x.groups = H->d_hw_groups;
                     x.classes = H->d_hw_classes;
                     x.terms = hw_terms_of<T>(H);
@@ -1852,61 +1992,56 @@ int mid_impl(vqe_batch* b, const vqe_batch_item* items, const std::vector<size_t
     for (size_t p = 0; p < pmax; ++p) {
         l_off[p] = e;
         uint32_t blk = 0;
-        size_t gbase = 0;
         for (size_t k = 0; k < m; ++k) {
             const vqe_circuit* c = items[idx[k]].circuit;
-            const size_t P = c->mid.size();
-            if (p < P) {
-                for (int dir = 0; dir < 2; ++dir) {
-                    const MidPlanPass& mp = c->mid[dir ? P - 1 - p : p];
-                    MidPass x{};
-                    x.psi = d + o_st + st_off[k];
-                    x.lam = d + o_st + st_off[k] + st_bytes_half(c->n, amp);
-                    x.n_cosets = ncos[k];
-                    x.part_off = part_s[k] + (uint64_t)mp.slot_off * nblk[k];
-                    for (int j = 0; j < kMidWin; ++j) x.pos[j] = mp.pos[j];
-                    x.gate_off = (uint32_t)(gbase + mp.gate_off);
-                    x.n_gates = mp.n_gates;
-                    x.mat_off = (uint32_t)m_off[k];
-                    x.n_slots = mp.n_slots;
-                    x.blk_begin = blk;
-                    x.n_blk = nblk[k];
-                    x.first = (dir == 0 && p == 0) ? 1u : 0u;
-                    (dir ? hr : hf)[e] = x;
-                }
-                blk += nblk[k];
-                ++e;
+            const BatchPlan& bp = c->batch[dt][0];
+            const size_t P = bp.passes.size();
+            if (p >= P) continue;
+            for (int dir = 0; dir < 2; ++dir) {
+                const size_t q = dir ? P - 1 - p : p, pr = 2 * q + (size_t)dir;
+                MidPass x{};
+                x.psi = psi_of(k);
+                x.lam = lam_of(k);
+                x.stages = (const ProgStage*)(d + o_img + img_off[k] + bp.stage_off[pr]);
+                x.stream = d + o_img + img_off[k] + bp.stream_off[pr];
+                x.n_cosets = 1ull << (c->n - kMidWin);
+                x.part_off = part_s[k] + (uint64_t)bp.slot_off[pr] * nblk[k];
+                for (int j = 0; j < kMidWin; ++j) x.pos[j] = (uint32_t)bp.passes[q].pos[j];
+                x.n_stages = (uint32_t)bp.prog[pr].stages.size();
+                x.n_slots = (uint32_t)bp.prog[pr].slot_param.size();
+                x.blk_begin = blk;
+                x.n_blk = nblk[k];
+                x.first = (dir == 0 && p == 0) ? 1u : 0u;
+                (dir ? hr : hf)[e] = x;
             }
-            gbase += c->mid_gates.size();
+            blk += nblk[k];
+            ++e;
         }
         l_cnt[p] = e - l_off[p];
         l_grid[p] = blk;
     }
-    VQE_HIP(hipMemcpyAsync(d, h, o_out, hipMemcpyHostToDevice, b->stream));
-    const auto* dg = (const BatchGate*)(d + o_gates);
-    const auto* dm = (const Mat2<T>*)(d + o_mats);
+    VQE_HIP(hipMemcpyAsync(d, h, o_img + n_img, hipMemcpyHostToDevice, b->stream));
     for (size_t p = 0; p < pmax; ++p)
-        VQE_HIP(launch_mid_pass<T>((const MidPass*)(d + o_fwd) + l_off[p], (uint32_t)l_cnt[p], l_grid[p], false, dg,
-                                   dm, part, b->stream));
+        VQE_HIP(launch_mid_pass<T>((const MidPass*)(d + o_fwd) + l_off[p], (uint32_t)l_cnt[p], l_grid[p], false, part,
+                                   b->stream));
     if (n_th) VQE_HIP(launch_mid_hpsi<T>((const MidHam*)(d + o_ham), (uint32_t)n_th, hblk, part, b->stream));
     for (const HwLaunch& L : hw_launch)
         VQE_HIP(launch_hwin_batch<T>((const HwItem*)(d + o_hw) + L.off, (uint32_t)L.cnt, L.grid, L.real, part,
                                      b->stream));
     for (size_t p = 0; p < pmax; ++p)
-        VQE_HIP(launch_mid_pass<T>((const MidPass*)(d + o_rev) + l_off[p], (uint32_t)l_cnt[p], l_grid[p], true, dg,
-                                   dm, part, b->stream));
-    VQE_HIP(launch_mid_reduce((const MidRed*)(d + o_red), (uint32_t)n_red, part, (double*)(d + o_out), b->stream));
-    VQE_HIP(hipMemcpyAsync(h + o_out, d + o_out, n_red * sizeof(double), hipMemcpyDeviceToHost, b->stream));
+        VQE_HIP(launch_mid_pass<T>((const MidPass*)(d + o_rev) + l_off[p], (uint32_t)l_cnt[p], l_grid[p], true, part,
+                                   b->stream));
+    VQE_HIP(launch_mid_reduce((const MidRed*)(d + o_red), (uint32_t)n_red, part, out, b->stream));
     VQE_HIP(hipStreamSynchronize(b->stream));
-    const double* r = (const double*)(h + o_out);
     for (size_t k = 0; k < m; ++k) {
         const vqe_batch_item& it = items[idx[k]];
         const vqe_circuit* c = it.circuit;
-        const double* o = r + red_base[k];
+        const std::vector<int32_t>& sp = c->batch[dt][0].slot_param;
+        const double* o = out + red_base[k];
         const double nrm = o[1];
         *it.energy = o[0] / nrm;
         for (size_t q = 0; q < c->n_params; ++q) it.grad[q] = 0.0;
-        for (size_t sl = 0; sl < c->mid_slot_pidx.size(); ++sl) it.grad[c->mid_slot_pidx[sl]] += o[2 + sl] / nrm;
+        for (size_t sl = 0; sl < sp.size(); ++sl) it.grad[sp[sl]] += o[2 + sl] / nrm;
     }
     return VQE_OK;
 }
@@ -2111,33 +2246,7 @@ int vqe_circuit_create(int n_qubits, const vqe_gate* gates, size_t n_gates, vqe_
     c->n = n_qubits;
     c->gates = std::move(gs);
     c->n_params = n_params;
-    for (size_t i = 0; i < c->gates.size(); ++i) {
-        const Gate& g = c->gates[i];
-        BatchGate bg{};
-        bg.q0 = (uint8_t)g.q0;
-        bg.q1 = (uint8_t)g.q1;
-        bg.pidx = g.pidx;
-        bg.gen = grad_op(g.kind);
-        if (g.kind == VQE_GATE_CNOT) bg.type = OP_CNOT;
-        else if (g.kind == VQE_GATE_CZ) bg.type = OP_CZ;
-        else if (g.kind == VQE_GATE_X) bg.type = OP_XFLIP;
-        else if (is_excitation(g.kind)) {
-            // pair rotation on the basis patterns A, B (batched states have n <= 13)
-            bg.type = OP_PAIR2;
-            bg.gen = OP_GPAIR2;
-            const bool dbl = g.kind == VQE_GATE_DEXC;
-            if (n_qubits <= 16) {
-                bg.pa = (uint16_t)(dbl ? (1u << g.q0) | (1u << g.q1) : (1u << g.q0));
-                bg.pb = (uint16_t)(dbl ? (1u << g.q2) | (1u << g.q3) : (1u << g.q1));
-            }
-            bg.mat = c->n_mats++;
-            c->has_excitation = true;
-        } else {
-            bg.type = OP_U2;
-            bg.mat = c->n_mats++;
-        }
-        c->bgates.push_back(bg);
-    }
+    for (const Gate& g : c->gates) c->has_excitation = c->has_excitation || is_excitation(g.kind);
     for (int v = 0; v < 2; ++v) {
         if (v == 0 && c->has_excitation) continue;  // interpreted kernels have no pair ops
         int rc = build_plan(c, v ? kJitLimits : kInterpLimits, v == 1, c->plan[v]);
@@ -2145,10 +2254,6 @@ int vqe_circuit_create(int n_qubits, const vqe_gate* gates, size_t n_gates, vqe_
             free_circuit(c);
             return rc;
         }
-    }
-    if (int rc = build_mid_plan(c)) {
-        free_circuit(c);
-        return rc;
     }
     *out = c;
     return VQE_OK;
@@ -2310,6 +2415,10 @@ int vqe_hamiltonian_create(int n_qubits, const uint64_t* x, const uint64_t* z, c
         if (y & 1) h->real_coeffs = false;
     }
     plan_hwin(h);
+    if (h->n <= kBatchMaxQubitsC64) {
+        plan_small<float>(h, h->t32, h->sm_blocks[0], h->sm_stream[0]);
+        plan_small<double>(h, h->t64, h->sm_blocks[1], h->sm_stream[1]);
+    }
     *out = h;
     return VQE_OK;
     VQE_GUARD_END
@@ -2455,6 +2564,12 @@ int vqe_energy_grad(vqe_state* psi, vqe_state* lam, const vqe_circuit* c, const 
                 }
         }
     }
+    // A state that fits LDS runs in one launch, whatever its gates, unless a
+    // kernel form was chosen.  12 qubits, 4 layers, complex128: 26 launches of 1 to 8
+    // blocks 408 us, against one of one block 188 us.
+    if (jit_mode() == VQE_SPECIALIZE_AUTO && psi->n <= max_small(psi->dtype))
+        return psi->dtype == VQE_C64 ? small_grad<float>(psi, lam, c, params, h, opts, energy, grad)
+                                     : small_grad<double>(psi, lam, c, params, h, opts, energy, grad);
     return psi->dtype == VQE_C64 ? adjoint_impl<float>(psi, lam, c, params, h, opts, energy, grad)
                                  : adjoint_impl<double>(psi, lam, c, params, h, opts, energy, grad);
     VQE_GUARD_END
@@ -2471,15 +2586,7 @@ int vqe_batch_create(int dtype, void* hip_stream, vqe_batch** out) {
         set_error("vqe_batch_create: no HIP device");
         return VQE_ERR_DEVICE;
     }
-    {
-        static std::once_flag once;
-        static hipError_t lds_rc = hipSuccess;
-        std::call_once(once, [] { lds_rc = batch_set_lds_limit(); });
-        if (lds_rc != hipSuccess) {
-            set_error(std::string("vqe_batch_create: cannot raise the LDS limit: ") + hipGetErrorString(lds_rc));
-            return VQE_ERR_DEVICE;
-        }
-    }
+    if (int rc = small_lds_limit()) return rc;
     auto* b = new vqe_batch();
     b->dtype = dtype;
     b->stream = (hipStream_t)hip_stream;
@@ -2519,7 +2626,6 @@ int vqe_batch_energy_grad(vqe_batch* b, size_t n_items, const vqe_batch_item* it
     VQE_HIP(hipSetDevice(b->device));
     // Items up to the LDS limit go to the small-state kernel, larger ones up
     // to kMidMaxQubits to the tile passes; every item is checked first.
-    const int max_small = b->dtype == VQE_C64 ? kBatchMaxQubitsC64 : kBatchMaxQubitsC128;
     std::vector<vqe_batch_item> small;
     std::vector<size_t> mid;
     for (size_t i = 0; i < n_items; ++i) {
@@ -2535,7 +2641,7 @@ int vqe_batch_energy_grad(vqe_batch* b, size_t n_items, const vqe_batch_item* it
             return VQE_ERR_ARG;
         }
         if (int rc = check_params(it.circuit, it.params, it.n_params, "vqe_batch_energy_grad")) return rc;
-        if (n <= max_small) small.push_back(it);
+        if (n <= max_small(b->dtype)) small.push_back(it);
         else mid.push_back(i);
     }
     if (!small.empty()) {

@@ -21,13 +21,17 @@
 namespace vqe {
 namespace {
 
-struct PlanState {
-    int n;
-    const PlanLimits* lim;
-    const std::vector<Gate>* gates;
-    std::vector<std::vector<int>> chain;  // per qubit, gate indices in order
-    std::vector<size_t> head;             // per qubit, position of next unscheduled gate
+struct PlanGate {
+    int q[4], nq;
+    int ops, mats, slots;  // what it counts against the limits of a pass
 };
+struct PlanState {
+    const PlanLimits* lim;
+    std::vector<PlanGate> gates;
+    std::vector<std::vector<int>> chain;  // per qubit, gate indices in order
+};
+// Per qubit, position of its next unscheduled gate.
+using Heads = std::array<uint32_t, 64>;
 
 bool is_param(const Gate& g) { return g.pidx >= 0; }
 
@@ -48,33 +52,27 @@ uint64_t gate_mask(const Gate& g) {
 // scheduled gates to `out` (if non-null) and advances `head`.  Respects the
 // per-pass op / matrix / gradient-slot limits (a repeated parameter within a
 // pass shares its slot, counted here once per gate: a safe overestimate).
-int closure(const PlanState& ps, uint64_t W, std::vector<size_t>& head, std::vector<int>* out) {
+int closure(const PlanState& ps, uint64_t W, Heads& head, std::vector<int>* out) {
     const PlanLimits& L = *ps.lim;
-    const auto& G = *ps.gates;
     int count = 0, ops_rev = 0, mats = 0, slots = 0;
     bool changed = true;
     while (changed) {
         changed = false;
-        for (int q = 0; q < ps.n; ++q) {
-            if (!((W >> q) & 1)) continue;
-            while (head[q] < ps.chain[q].size()) {
-                int gi = ps.chain[q][head[q]];
-                const Gate& g = G[gi];
-                int gq[4];
-                const int nqg = gate_qubits(g, gq);
+        for (uint64_t m = W; m; m &= m - 1) {
+            const int q = __builtin_ctzll(m);
+            const std::vector<int>& ch = ps.chain[q];
+            while (head[q] < ch.size()) {
+                const int gi = ch[head[q]];
+                const PlanGate& g = ps.gates[gi];
                 bool ready = true;
-                for (int i = 0; i < nqg && ready; ++i)
-                    ready = ((W >> gq[i]) & 1) && ps.chain[gq[i]][head[gq[i]]] == gi;
+                for (int i = 0; i < g.nq && ready; ++i)
+                    ready = ((W >> g.q[i]) & 1) && ps.chain[g.q[i]][head[g.q[i]]] == gi;
                 if (!ready) break;
-                int add_ops = 1 + (is_param(g) ? 1 : 0);
-                int add_mats = uses_matrix(g) ? 1 : 0;
-                int add_slots = is_param(g) ? 1 : 0;
-                if (ops_rev + add_ops > L.ops || mats + add_mats > L.mats || slots + add_slots > L.slots)
-                    return count;
-                ops_rev += add_ops;
-                mats += add_mats;
-                slots += add_slots;
-                for (int i = 0; i < nqg; ++i) head[gq[i]]++;
+                if (ops_rev + g.ops > L.ops || mats + g.mats > L.mats || slots + g.slots > L.slots) return count;
+                ops_rev += g.ops;
+                mats += g.mats;
+                slots += g.slots;
+                for (int i = 0; i < g.nq; ++i) head[g.q[i]]++;
                 if (out) out->push_back(gi);
                 ++count;
                 changed = true;
@@ -93,15 +91,17 @@ bool plan_passes(int n, const std::vector<Gate>& gates, const PlanLimits& lim, s
     out.clear();
     const int K = std::min(n, std::min(lim.kmax, kMaxPlanWindow));
     PlanState ps;
-    ps.n = n;
+    Heads head{};
     ps.lim = &lim;
-    ps.gates = &gates;
+    ps.gates.resize(gates.size());
     ps.chain.assign(n, {});
-    ps.head.assign(n, 0);
     for (size_t i = 0; i < gates.size(); ++i) {
-        int gq[4];
-        const int nqg = gate_qubits(gates[i], gq);
-        for (int k = 0; k < nqg; ++k) ps.chain[gq[k]].push_back((int)i);
+        PlanGate& g = ps.gates[i];
+        g.nq = gate_qubits(gates[i], g.q);
+        g.slots = is_param(gates[i]) ? 1 : 0;
+        g.ops = 1 + g.slots;
+        g.mats = uses_matrix(gates[i]) ? 1 : 0;
+        for (int k = 0; k < g.nq; ++k) ps.chain[g.q[k]].push_back((int)i);
     }
     size_t scheduled = 0;
     std::vector<char> done(gates.size(), 0);
@@ -117,7 +117,7 @@ bool plan_passes(int n, const std::vector<Gate>& gates, const PlanLimits& lim, s
                 int best_q = -1, best_c = -1;
                 for (int q = 0; q < n; ++q) {
                     if ((W >> q) & 1) continue;
-                    std::vector<size_t> h = ps.head;
+                    Heads h = head;
                     int c = closure(ps, W | (1ull << q), h, nullptr);
                     if (c > best_c) {
                         best_c = c;
@@ -132,7 +132,7 @@ bool plan_passes(int n, const std::vector<Gate>& gates, const PlanLimits& lim, s
         uint64_t bestW = 0;
         int bestC = 0;
         for (uint64_t W : cands) {
-            std::vector<size_t> h = ps.head;
+            Heads h = head;
             int c = closure(ps, W, h, nullptr);
             if (c > bestC) {
                 bestC = c;
@@ -144,7 +144,7 @@ bool plan_passes(int n, const std::vector<Gate>& gates, const PlanLimits& lim, s
             return false;
         }
         PlannedPass p;
-        closure(ps, bestW, ps.head, &p.gates);
+        closure(ps, bestW, head, &p.gates);
         // Shrink the window to the qubits actually touched.
         uint64_t used = 0;
         for (int gi : p.gates) used |= gate_mask(gates[gi]);

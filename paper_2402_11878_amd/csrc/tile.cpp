@@ -9,6 +9,15 @@
 // bit).  The state crosses HBM once per pass, so the pass count is what a
 // large state pays for: 10 passes instead of 23 at 32 qubits x 8 layers.
 //
+// Measured against the 7-qubit window passes (whole call): 30 qubits complex128
+// step 572 -> 310 ms (forward passes 6.2-7.5 ms, 4.6-5.5 TB/s; reverse 13.6-20
+// ms, 5.0-3.4 TB/s, and 38 ms for the first window with its 184 gates), 28
+// qubits complex64 93.9 -> 46.7 ms, 24 qubits complex128 7.09 -> 3.72 ms, 20
+// qubits complex64 1.14 -> 0.52 ms.  What bounds a reverse pass: up to about 50
+// gates HBM (and address translation where nine window qubits lie above a 2 MiB
+// page), beyond that vector issue (69 % busy at 184 gates) and the LDS traffic
+// between stages.
+//
 // What the generated code does about arithmetic, the second cost:
 //   * permutation gates (CNOT, X) rename registers at generation time;
 //   * RY and RX run unnormalised, R = c [[1, -t], [t, 1]] with t = tan(a/2) and
@@ -27,44 +36,21 @@
 #include <cmath>
 #include <sstream>
 
-#include "vqe_internal.h"
+#include "sched.h"
 
 namespace vqe {
 namespace {
-
-enum OpKind { K_GRAD, K_ROTY, K_ROTX, K_R2, K_CNOT, K_FLIP, K_DIAG };
-
-// One gate (or its gradient term) on the register bits of a stage.  On each of
-// its bits it acts like Z (diagonal), like X, like Y, or otherwise; two ops
-// commute if on every shared bit both act like the same Pauli.
-struct Op {
-    OpKind kind;
-    int gate;
-    int bit[4];
-    uint32_t z = 0, x = 0, y = 0, other = 0;
-};
-
-bool commute(const Op& a, const Op& b) {
-    const uint32_t ma = a.z | a.x | a.y | a.other, mb = b.z | b.x | b.y | b.other, shared = ma & mb;
-    return (shared & ~((a.z & b.z) | (a.x & b.x) | (a.y & b.y))) == 0;
-}
-
-bool is_rot(OpKind k) { return k == K_ROTY || k == K_ROTX; }
 
 struct Layout {
     int reg[8];  // tile bit of register bit i
     int thr[8];  // tile bit of thread bit i
 };
 
-struct Gen {
-    bool dbl;
+struct Gen : StageScheduler {
     TileShape sh;
     int NV, N;
-    const std::vector<Gate>* gates;
-    TileKernel* out;
     std::ostringstream o;
     std::vector<int> loc;        // variable holding register entry p
-    std::vector<int> pending;    // rotations whose factor c is still to be applied
     // gradient terms waiting at each level of the lane sums, as variables and their lane -> push map
     struct Node {
         std::string var;
@@ -76,20 +62,9 @@ struct Gen {
     std::string R(int v, int p) const { return "r" + std::to_string(v) + "_" + std::to_string(loc[p]); }
     std::string I(int v, int p) const { return "i" + std::to_string(v) + "_" + std::to_string(loc[p]); }
 
-    // ---- tables
-    uint32_t entry(TileEntry e, uint32_t scalars) {
-        e.off = out->n_scalars;
-        out->n_scalars += scalars;
-        out->entries.push_back(std::move(e));
-        return out->entries.back().off;
-    }
-
     // ---- ops
-    void rot(const Op& k) {
-        TileEntry e;
-        e.kind = TF_ROT;
-        e.gate = k.gate;
-        const uint32_t off = entry(e, 1);
+    void rot(const StageOp& k) override {
+        const uint32_t off = gate_entry(TF_ROT, k.gate, 1);
         o << "  { const T t = tab[" << off << "];\n";
         const int b = 1 << k.bit[0];
         for (int p = 0; p < N; ++p) {
@@ -110,31 +85,15 @@ struct Gen {
         pending.push_back(k.gate);
     }
 
-    void scale() {
-        if (pending.empty()) return;
-        TileEntry e;
-        e.kind = TF_SCALE;
-        e.rots.swap(pending);
-        const uint32_t off = entry(e, 1);
+    void scale_by(uint32_t off) override {
         o << "  { const T s = tab[" << off << "];\n";
         for (int p = 0; p < N; ++p)
             for (int v = 0; v < NV; ++v) o << "    " << R(v, p) << " *= s; " << I(v, p) << " *= s;\n";
         o << "  }\n";
     }
 
-    // The diagonal gates `ops` as one phase per value of their bits.
-    void phase(const std::vector<Op>& ops) {
-        TileEntry e;
-        e.kind = TF_PHASE;
-        for (const Op& k : ops) {
-            e.diag.push_back(k.gate);
-            e.diag_bits.push_back(k.z);
-            e.mask |= k.z;
-        }
-        e.rots.swap(pending);
-        const uint32_t mask = e.mask;
+    void phase_by(uint32_t off, uint32_t mask) override {
         const int m = __builtin_popcount(mask);
-        const uint32_t off = entry(e, 2u << m);
         for (uint32_t idx = 0; idx < (1u << m); ++idx) {
             o << "  { const T pr = tab[" << off + 2 * idx << "], pi = tab[" << off + 2 * idx + 1 << "];\n";
             for (int p = 0; p < N; ++p) {
@@ -151,15 +110,12 @@ struct Gen {
     }
 
     // A real 2x2 matrix between two patterns (H; excitations).
-    void matrix(const Op& k) {
-        TileEntry e;
-        e.gate = k.gate;
-        e.kind = TF_R2;
-        const uint32_t off = entry(e, 4);
+    void matrix(const StageOp& k) override {
+        const uint32_t off = gate_entry(TF_R2, k.gate, 4);
         o << "  { const T ca = tab[" << off << "], cb = tab[" << off + 1 << "], cc = tab[" << off + 2 << "], cd = tab["
           << off + 3 << "];\n";
         uint32_t mask, A, B;
-        pattern(k, mask, A, B);
+        stage_pattern((*gates)[k.gate], k, mask, A, B);
         for (int p = 0; p < N; ++p) {
             if ((p & (int)mask) != (int)A) continue;
             const int q = p ^ (int)(A ^ B);
@@ -172,23 +128,7 @@ struct Gen {
         o << "  }\n";
     }
 
-    // Patterns between which an op acts: bit clear / set, or the A and B of an excitation.
-    void pattern(const Op& k, uint32_t& mask, uint32_t& A, uint32_t& B) const {
-        const Gate& g = (*gates)[k.gate];
-        if (g.kind == VQE_GATE_SEXC) {
-            A = 1u << k.bit[0];
-            B = 1u << k.bit[1];
-        } else if (g.kind == VQE_GATE_DEXC) {
-            A = (1u << k.bit[0]) | (1u << k.bit[1]);
-            B = (1u << k.bit[2]) | (1u << k.bit[3]);
-        } else {
-            A = 0;
-            B = 1u << k.bit[0];
-        }
-        mask = A | B;
-    }
-
-    void rename(const Op& k) {
+    void rename(const StageOp& k) override {
         const int c = k.kind == K_CNOT ? 1 << k.bit[0] : 0, t = 1 << (k.kind == K_CNOT ? k.bit[1] : k.bit[0]);
         for (int p = 0; p < N; ++p)
             if ((p & c) == c && !(p & t)) std::swap(loc[p], loc[p | t]);
@@ -257,10 +197,10 @@ struct Gen {
         total(carry_n);
     }
 
-    void gradient(const Op& k) {
+    void gradient(const StageOp& k) override {
         const Gate& g = (*gates)[k.gate];
         uint32_t mask, A, B;
-        pattern(k, mask, A, B);
+        stage_pattern((*gates)[k.gate], k, mask, A, B);
         const std::string acc = fresh();
         o << "  T " << acc << " = 0;\n";
         for (int p = 0; p < N; ++p) {
@@ -280,7 +220,7 @@ struct Gen {
 
     // Im<lam|Z_b|psi> for the bits of the given RZ gates: d = Im(conj(lam) psi)
     // per entry once, then for each bit the sum of differences, passing the sums on.
-    void gradient_z(const std::vector<Op>& ops) {
+    void gradient_z(const std::vector<StageOp>& ops) override {
         std::vector<std::string> d(N);
         for (int p = 0; p < N; ++p) {
             d[p] = fresh();
@@ -288,7 +228,7 @@ struct Gen {
               << R(0, p) << ";\n";
         }
         uint32_t want = 0;
-        for (const Op& k : ops) want |= 1u << k.bit[0];
+        for (const StageOp& k : ops) want |= 1u << k.bit[0];
         for (int b = 0; b < sh.R; ++b) {
             const size_t half = d.size() / 2;  // entries are indexed by the bits b and up
             std::vector<std::string> s(half);
@@ -297,7 +237,7 @@ struct Gen {
                 for (size_t i = 0; i < half; ++i)
                     o << (i ? "  " + acc + " += " : "  T " + acc + " = ") << d[2 * i] << " - " << d[2 * i + 1] << ";\n";
                 // every parameterised gate on the bit has this term
-                for (const Op& k : ops)
+                for (const StageOp& k : ops)
                     if (k.bit[0] == b) push(acc, (*gates)[k.gate].pidx);
             }
             if (!(want >> (b + 1))) break;
@@ -306,63 +246,6 @@ struct Gen {
                 o << "  T " << s[i] << " = " << d[2 * i] << " + " << d[2 * i + 1] << ";\n";
             }
             d.swap(s);
-        }
-    }
-
-    // Emits the ops of a stage in an order that respects every pair that does
-    // not commute: gradient terms and register renames as soon as they are
-    // ready, then rotations, diagonal gates last (so that they merge).
-    // Gradient terms read normalised vectors (pending factors applied first).
-    void stage(std::vector<Op> ops) {
-        const size_t max_pending = dbl ? 14 : 4;  // each factor may be as small as 2^-60 (2^-26)
-        auto ready = [&](size_t i) {
-            for (size_t j = 0; j < i; ++j)
-                if (!commute(ops[j], ops[i])) return false;
-            return true;
-        };
-        auto z_term = [&](const Op& k) { return k.kind == K_GRAD && (*gates)[k.gate].kind == VQE_GATE_RZ; };
-        auto is_diag = [&](const Op& k) { return k.kind == K_DIAG || z_term(k); };
-        while (!ops.empty()) {
-            bool progress = false;
-            for (size_t i = 0; i < ops.size();) {
-                const Op& k = ops[i];
-                if (is_diag(k) || is_rot(k.kind) || (k.kind == K_GRAD && !pending.empty()) || !ready(i)) {
-                    ++i;
-                    continue;
-                }
-                if (k.kind == K_GRAD) gradient(k);
-                else if (k.kind == K_CNOT || k.kind == K_FLIP) rename(k);
-                else matrix(k);
-                ops.erase(ops.begin() + (long)i);
-                progress = true;
-                i = 0;
-            }
-            if (ops.empty()) break;
-            for (size_t i = 0; i < ops.size();) {
-                if (is_rot(ops[i].kind) && pending.size() < max_pending && ready(i)) {
-                    rot(ops[i]);
-                    ops.erase(ops.begin() + (long)i);
-                    progress = true;
-                } else {
-                    ++i;
-                }
-            }
-            if (progress) continue;
-            std::vector<Op> diag, zt;
-            for (size_t i = 0; i < ops.size();) {
-                if (is_diag(ops[i]) && ready(i)) {
-                    (z_term(ops[i]) ? zt : diag).push_back(ops[i]);
-                    ops.erase(ops.begin() + (long)i);
-                } else {
-                    ++i;
-                }
-            }
-            if (!diag.empty()) phase(diag);
-            if (!zt.empty()) {
-                scale();
-                gradient_z(zt);
-            }
-            if (diag.empty() && zt.empty()) scale();  // a gradient term or a rotation waits for the factors
         }
     }
 
@@ -670,35 +553,12 @@ bool tile_kernel(bool dbl, const TileShape& sh, const std::vector<Gate>& gates, 
         const std::vector<int>& r = regs[node];
         int rbit[32];
         for (int i = 0; i < sh.R; ++i) rbit[r[i]] = i;
-        std::vector<Op> ops;
+        std::vector<StageOp> ops;
         auto add = [&](int li, bool grad) {
-            const Gate& gt = lg[li];
-            Op k{};
-            k.gate = p.gates[li];
-            int q[4];
-            const int nq = gate_qubits(gt, q);
-            uint32_t all = 0;
-            for (int i = 0; i < nq; ++i) {
-                k.bit[i] = rbit[q[i]];
-                all |= 1u << k.bit[i];
-            }
-            switch (gt.kind) {
-                case VQE_GATE_RY: k.kind = K_ROTY; k.y = all; break;
-                case VQE_GATE_RX: k.kind = K_ROTX; k.x = all; break;
-                case VQE_GATE_RZ: k.kind = K_DIAG; k.z = all; break;
-                case VQE_GATE_CZ: k.kind = K_DIAG; k.z = all; break;
-                case VQE_GATE_X: k.kind = K_FLIP; k.x = all; break;
-                case VQE_GATE_CNOT:
-                    k.kind = K_CNOT;
-                    k.z = 1u << k.bit[0];
-                    k.x = 1u << k.bit[1];
-                    break;
-                case VQE_GATE_SEXC:
-                case VQE_GATE_DEXC:
-                default: k.kind = K_R2; k.other = all; break;  // excitations, H
-            }
-            if (grad) k.kind = K_GRAD;
-            ops.push_back(k);
+            int q[4], bits[4];
+            const int nq = gate_qubits(lg[li], q);
+            for (int i = 0; i < nq; ++i) bits[i] = rbit[q[i]];
+            ops.push_back(stage_op(lg[li], p.gates[li], bits, grad));
         };
         const std::vector<int>& sg = stages[si].gates;
         if (dir == 0) {

@@ -143,92 +143,6 @@ struct TermDesc {
     T cre, cim;
 };
 
-// ---------------------------------------------------------------- batched small states (batch.hip)
-constexpr int kBatchLdsBytes = 128 * 1024;  // psi + lam in LDS
-constexpr int kBatchMaxQubitsC64 = 13;
-constexpr int kBatchMaxQubitsC128 = 12;
-
-struct BatchGate {
-    uint8_t type;  // OP_U2, OP_CNOT, OP_CZ, OP_XFLIP, OP_PAIR2 (any pair rotation)
-    uint8_t q0, q1;
-    uint8_t gen;   // OP_GX / OP_GY / OP_GZ / OP_GPAIR2 for parameterised gates
-    int32_t pidx;  // parameter index or -1
-    uint32_t mat;  // matrix index within the request
-    uint16_t pa, pb;  // pair rotations: basis patterns A and B (n <= 16)
-};
-
-template <typename T>
-struct BatchDesc {
-    int32_t n;
-    uint32_t n_gates, gate_off, mat_off, n_groups, n_params;
-    uint64_t out_off;  // out[out_off] = energy, out[out_off + 1 + k] = dE/dtheta_k
-    const GroupDesc* groups;
-    const TermDesc<T>* terms;
-};
-
-template <typename T>
-hipError_t launch_batch(const BatchDesc<T>* items, uint32_t n_items, const BatchGate* gates, const Mat2<T>* mats,
-                        double* out, int max_n, hipStream_t st);
-hipError_t batch_set_lds_limit();
-
-// ---------------------------------------------------------------- batched mid-size states (batch.hip)
-// Items above the LDS limit, up to kMidMaxQubits: psi and lam stay in device
-// memory (up to 256 MiB per state in complex64, held in the last-level cache
-// between passes at the small end), and one launch applies one fused pass of
-// every item of the batch.  A pass is a window of kMidWin qubits (padded
-// with the lowest qubits outside it, so a tile's loads run over consecutive
-// amplitudes); a block stages a coset of 2^kMidWin amplitudes in LDS, applies
-// the pass's gates there one at a time and writes it back.
-constexpr int kMidWin = 10;
-constexpr int kMidMaxQubits = 24;
-constexpr int kMidMaxSlots = 64;          // parameterised gates per pass
-constexpr uint32_t kMidMaxBlocks = 1024;  // blocks per item and launch
-constexpr PlanLimits kMidLimits = {kMidWin, 1024, 1024, kMidMaxSlots};
-static_assert(kMidWin <= kMaxPlanWindow, "planner window");
-static_assert(kMidMaxQubits == VQE_BATCH_MAX_QUBITS_MID, "public and internal mid-size limits differ");
-
-// One item's pass in one launch.  Blocks [blk_begin, blk_begin + n_blk) of
-// the launch take cosets blk, blk + n_blk, ...; in a reverse pass block blk
-// writes gradient slot s (the pass's parameterised gates, last gate first)
-// to part[part_off + s n_blk + blk].
-struct MidPass {
-    void* psi;
-    void* lam;
-    uint64_t n_cosets;
-    uint64_t part_off;
-    uint32_t pos[kMidWin];  // window qubits, ascending
-    uint32_t gate_off, n_gates, mat_off, n_slots;
-    uint32_t blk_begin, n_blk;
-    uint32_t first;         // forward pass 0: stage |0...0> instead of reading psi
-    uint32_t pad;
-};
-
-// lam = H psi of one item over tiles of 2^kMidWin amplitudes; block blk
-// writes its energy and norm partials to part[part_off + blk] and
-// part[part_off + n_blk + blk].
-struct MidHam {
-    const void* psi;
-    void* lam;
-    const GroupDesc* groups;
-    const void* terms;      // TermDesc<T>
-    uint64_t n_tiles;
-    uint64_t part_off;
-    uint32_t n_groups, blk_begin, n_blk, pad;
-};
-
-// out[k] = sum of part[part_off .. part_off + count) in a fixed order.
-struct MidRed {
-    uint64_t part_off;
-    uint32_t count, pad;
-};
-
-template <typename T>
-hipError_t launch_mid_pass(const MidPass* d, uint32_t n_desc, uint32_t grid, bool rev, const BatchGate* gates,
-                           const Mat2<T>* mats, double* part, hipStream_t st);
-template <typename T>
-hipError_t launch_mid_hpsi(const MidHam* d, uint32_t n_desc, uint32_t grid, double* part, hipStream_t st);
-hipError_t launch_mid_reduce(const MidRed* r, uint32_t n, const double* part, double* out, hipStream_t st);
-
 // ---------------------------------------------------------------- launchers (kernels.hip)
 hipError_t launch_set_basis(int dtype, void* psi, uint64_t dim, uint64_t b, hipStream_t st);
 hipError_t launch_zero(double* p, uint64_t n, hipStream_t st);
@@ -502,6 +416,99 @@ struct HalfAngle {
 template <typename T>
 void fill_tile_table(const TileKernel& k, const std::vector<Gate>& gates, const HalfAngle* h, int dir, T* tab);
 
+// ---------------------------------------------------------------- batch programs (program.cpp, batch.hip)
+// A tile of 2^bits amplitudes in LDS, kProgBits of its bits in registers at a
+// time: 2^(bits - 4) threads with 16 amplitudes (per vector) each.
+constexpr int kProgBits = 4;
+// A stage is one of three kinds of records.
+//   rows   straight-line, no branch: what a layer of RY, diagonal gates and
+//          CNOTs along the register bits needs, in the order the scheduler
+//          emits it (absent parts act as the identity)
+//            forward   turns, phases, CNOTs 0-1, 1-2, 2-3
+//            reverse   CNOTs 2-3, 1-2, 0-1, phases, Z terms, Y terms, turns
+//   pairs  excitations, applied where their amplitudes lie in LDS
+//   misc   everything else, one op per record
+enum ProgKind : uint32_t { PK_ROWS, PK_PAIRS, PK_MISC };
+template <typename T>
+struct ProgRow {
+    uint32_t flags;          // bit k < 3: CNOT of control k, target k + 1; bit 4: it has more; Z mask << 8; Y mask << 12
+    uint32_t z_slot, z_off;  // gradient slot of the Z term of bit k: z_slot + byte k of z_off
+    uint32_t y_slot, y_off;
+    uint32_t pad[3];
+    T t[4];                  // RY on bit k: x - t y, y + t x
+    T ph[32];                // phase (re, im) of every register entry
+};
+template <typename T>
+struct ProgMisc {
+    uint32_t code;  // type | bit << 8; PM_PERM: control << 2 | target of a CNOT, or 5 x bit: X
+    uint32_t slot, pad[2];
+    T t[4];
+};
+enum ProgMiscType : uint32_t {
+    PM_ROTX,   // x - i t y, y - i t x, t = t[0]
+    PM_R2,     // real matrix t[0..3]
+    PM_PERM,
+    PM_GX,     // gradient slot: Im<lam|X|psi>
+};
+// An excitation: a real matrix between the tile patterns x & 0xffff and x >> 16.
+template <typename T>
+struct ProgPair {
+    uint32_t x, slot, grad, pad;  // grad = 1: first its gradient term to `slot`
+    T s[4];
+};
+// A stage's block in the program's stream: the header of the next stage, then
+// this one's records.
+struct ProgStage {
+    uint8_t pos[kProgBits];  // register bits, ascending tile bits
+    uint16_t kind;           // ProgKind
+    uint16_t n_ops;          // records
+    uint32_t off, bytes;     // in the stream, multiples of 16
+};
+static_assert(sizeof(ProgStage) == 16, "four words");
+constexpr uint32_t kProgBlock = 6144;  // longest block (two of them in LDS: one in use, one arriving)
+struct Program {
+    std::vector<ProgStage> stages;
+    std::vector<uint32_t> stream;    // the blocks, numbers still zero
+    TileKernel table;                // its entries: scalar offsets into the stream
+    std::vector<int32_t> slot_param; // reverse: parameter of every gradient slot
+    // stages emitted up to the end of every planned group: a checkpoint may
+    // stand there, unless a later group's ops joined the last stage (~0u)
+    std::vector<uint32_t> mark;
+};
+inline bool is_excitation_kind(int kind) { return kind == VQE_GATE_SEXC || kind == VQE_GATE_DEXC; }
+// The gates `list` on a tile of `bits` bits, local[q] = tile bit of qubit q,
+// grouped into stages (one plan for both directions: planning takes longer than
+// building, and a circuit's first evaluation waits for it).
+struct ProgramPlan {
+    std::vector<Gate> gates;  // on tile bits
+    std::vector<int> list;
+    std::vector<PlannedPass> stages;
+};
+bool plan_program(int bits, const std::vector<Gate>& gates, const std::vector<int>& list, const int* local,
+                  ProgramPlan& out, std::string& msg);
+// Program of a plan (dir 0 forward, or 1: un-applied in reverse with the
+// gradient terms).  flush: pending factors are applied at the end of every
+// planned group, so that the tile holds the state there.
+bool build_program(bool dbl, int bits, const std::vector<Gate>& gates, const ProgramPlan& plan, int dir, bool flush,
+                   Program& out, std::string& msg);
+
+// A small Hamiltonian as a stream of blocks of at most kProgBlock bytes, each
+// of groups: a header, then its terms.  A group's terms are sorted by their z
+// bits on the register part of the index (the kProgBits highest tile bits):
+// count[u] of them (a byte each) have the bits u.
+struct SmallGroup {
+    uint32_t x, n_terms, pad[2];
+    uint32_t count[4];
+};
+template <typename T>
+struct SmallTerm {
+    uint32_t zt, pad;  // z bits on the thread part
+    T cre, cim;
+};
+struct SmallBlock {
+    uint32_t off, bytes, n_groups, pad;
+};
+
 struct TileArgs {
     uint64_t n_units;              // cosets of the window
     uint32_t pos[kTileMaxBits];    // window qubits, ascending
@@ -515,6 +522,104 @@ uint32_t tile_blocks(uint64_t units, bool reverse);
 // out[p L + l] = sum over blocks b < nblocks of part[(p nblocks + b) L + l], p < n_pass, in a fixed order.
 hipError_t launch_tile_reduce(const double* part, uint32_t n_pass, uint32_t nblocks, uint32_t L, double* out,
                               hipStream_t st);
+
+// ---------------------------------------------------------------- batched small states (batch.hip)
+constexpr int kBatchMaxQubitsC64 = 13;
+constexpr int kBatchMaxQubitsC128 = 12;
+constexpr int kBatchLdsBytes = 128 * 1024 + 2 * (int)kProgBlock;  // psi + lam + two program blocks in LDS
+// Smaller states run as this many bits (a full wave of 16 amplitudes per
+// thread), the qubits above n idle in |0>.
+constexpr int kBatchMinBits = 10;
+inline int batch_bits(int n) { return n < kBatchMinBits ? kBatchMinBits : n; }
+
+// A checkpoint of a small state: psi is kept in buf after the forward stages
+// [0, fwd_end) and restored after the reverse stages [0, rev_end).
+struct BatchCkpt {
+    void* buf;
+    uint32_t fwd_end, rev_end;
+};
+
+template <typename T>
+struct BatchDesc {
+    int32_t n, bits;
+    uint32_t n_fwd, n_rev;      // stages
+    uint32_t n_blocks, n_slots;
+    uint32_t real;              // every folded coefficient is real
+    uint32_t n_ckpt;
+    const BatchCkpt* ckpt;      // in forward order
+    const ProgStage* fwd;
+    const ProgStage* rev;
+    const char* fwd_stream;     // this evaluation's
+    const char* rev_stream;
+    const SmallBlock* ham;      // the Hamiltonian's blocks
+    const char* ham_stream;
+    double* out;                // energy, norm, then the gradient sums by slot
+    double* part;               // n_slots x 8 doubles: sums per wave
+    void* psi_out;              // where the state ends up (nullptr: nowhere)
+    void* lam_out;
+};
+
+template <typename T>
+hipError_t launch_batch(const BatchDesc<T>* items, uint32_t n_items, int max_bits, hipStream_t st);
+hipError_t batch_set_lds_limit();
+
+// ---------------------------------------------------------------- batched mid-size states (batch.hip)
+// Items above the LDS limit, up to kMidMaxQubits: psi and lam stay in device
+// memory (held in the last-level cache between passes at the small end), and
+// one launch applies one fused pass of every item of the batch.  A pass is a
+// window of kMidWin qubits that holds the kMidLow lowest ones (plan_tiles); a
+// block stages a coset of 2^kMidWin amplitudes in LDS, runs the pass's program
+// there and writes it back.
+constexpr int kMidWin = 12;
+constexpr int kMidLow = 2;
+constexpr int kMidMaxQubits = 24;
+constexpr int kMidMaxSlots = 128;         // parameterised gates per pass
+constexpr uint32_t kMidMaxBlocks = 1024;  // blocks per item and launch
+static_assert(kMidWin <= kMaxPlanWindow, "planner window");
+static_assert(kMidMaxQubits == VQE_BATCH_MAX_QUBITS_MID, "public and internal mid-size limits differ");
+
+// One item's pass in one launch.  Blocks [blk_begin, blk_begin + n_blk) of
+// the launch take cosets blk, blk + n_blk, ...; in a reverse pass block blk
+// writes gradient slot s of the pass to part[part_off + s n_blk + blk].
+struct MidPass {
+    void* psi;
+    void* lam;
+    const ProgStage* stages;
+    const char* stream;
+    uint64_t n_cosets;
+    uint64_t part_off;
+    uint32_t pos[kMidWin];  // window qubits, ascending
+    uint32_t n_stages, n_slots;
+    uint32_t blk_begin, n_blk;
+    uint32_t first;         // forward pass 0: stage |0...0> instead of reading psi
+    uint32_t pad;
+};
+
+// lam = H psi of one item over tiles of 2^kMidTileBits amplitudes; block blk
+// writes its energy and norm partials to part[part_off + blk] and
+// part[part_off + n_blk + blk].
+constexpr int kMidTileBits = 10;
+struct MidHam {
+    const void* psi;
+    void* lam;
+    const GroupDesc* groups;
+    const void* terms;      // TermDesc<T>
+    uint64_t n_tiles;
+    uint64_t part_off;
+    uint32_t n_groups, blk_begin, n_blk, pad;
+};
+
+// out[k] = sum of part[part_off .. part_off + count) in a fixed order.
+struct MidRed {
+    uint64_t part_off;
+    uint32_t count, pad;
+};
+
+template <typename T>
+hipError_t launch_mid_pass(const MidPass* d, uint32_t n_desc, uint32_t grid, bool rev, double* part, hipStream_t st);
+template <typename T>
+hipError_t launch_mid_hpsi(const MidHam* d, uint32_t n_desc, uint32_t grid, double* part, hipStream_t st);
+hipError_t launch_mid_reduce(const MidRed* r, uint32_t n, const double* part, double* out, hipStream_t st);
 
 // ---------------------------------------------------------------- errors
 void set_error(const std::string& m);
