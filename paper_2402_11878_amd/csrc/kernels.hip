@@ -864,6 +864,29 @@ __device__ __forceinline__ void parity_sign(uint32_t cnt, double& s) {
 }
 __device__ __forceinline__ void parity_sign(uint32_t cnt, float& s) { s = __uint_as_float((cnt << 31) | 0x3f800000u); }
 
+// A group's header as a whole, in scalar registers: left to the compiler its
+// words are fetched one by one where they are used, each a wait of about 200
+// cycles in a row of up to ten per group.
+__device__ __forceinline__ HwGroup hw_load(const HwGroup* g) {
+    using W = uint32_t __attribute__((ext_vector_type(4)));
+    static_assert(sizeof(HwGroup) == 3 * sizeof(W), "three words of 16 bytes");
+    uint32_t w[12];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        const W v = reinterpret_cast<const W*>(g)[i];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) w[4 * i + k] = (uint32_t)__builtin_amdgcn_readfirstlane((int)v[k]);
+    }
+    asm volatile("" : "+s"(w[0]), "+s"(w[1]), "+s"(w[2]), "+s"(w[3]), "+s"(w[4]), "+s"(w[5]));
+    asm volatile("" : "+s"(w[6]), "+s"(w[7]), "+s"(w[8]), "+s"(w[9]), "+s"(w[10]));
+    HwGroup r{};
+    r.xl = w[0];
+#pragma unroll
+    for (int k = 0; k <= (1 << kHwRegBits); ++k) r.cb[k] = w[1 + k];
+    r.zrm = w[10];
+    return r;
+}
+
 // One group of a window pass for the patterns t + kHwThreads r of thread t:
 // bucket sums E_u over the classes (A and zt staged in LDS at local index
 // j - cbase), D_r = sum_{u in M} (-1)^{popcount(u & r)} E_u (a transform over
@@ -939,9 +962,10 @@ __device__ __forceinline__ void hw_group(const HwGroup& G, uint32_t cbase, uint3
 
 // lam_r += D_r psi[(t + kHwThreads r) ^ xl] for the R patterns of thread t
 // (one code path for every register-bit subset of the group's classes).
-template <typename T, bool REAL>
+// HALF: only the patterns r without the bits in `skip`, counted `weight` times.
+template <typename T, bool REAL, bool HALF>
 __device__ __forceinline__ void hw_apply(const HwGroup& G, uint32_t t, const typename VecOf<T>::type* sp,
-                                         const T* dr, const T* di, T* lr, T* li) {
+                                         const T* dr, const T* di, T* lr, T* li, uint32_t skip = 0, T weight = 1) {
     using V = typename VecOf<T>::type;
     constexpr int R = 1 << kHwRegBits;
     // partner of pattern t + kHwThreads r: byte offset a0 + (r ^ xr) kHwThreads sizeof(V)
@@ -950,9 +974,11 @@ __device__ __forceinline__ void hw_apply(const HwGroup& G, uint32_t t, const typ
     const char* spb = reinterpret_cast<const char*>(sp);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
+        if (HALF && (r & skip)) continue;
         const V pv = *reinterpret_cast<const V*>(spb + a0 + (r ^ xr) * (uint32_t)(kHwThreads * sizeof(V)));
-        lr[r] = fma(dr[r], pv.x, lr[r]);
-        li[r] = fma(dr[r], pv.y, li[r]);
+        const T d = HALF ? dr[r] * weight : dr[r];
+        lr[r] = fma(d, pv.x, lr[r]);
+        li[r] = fma(d, pv.y, li[r]);
         if (!REAL) {
             lr[r] = fma(-di[r], pv.y, lr[r]);
             li[r] = fma(di[r], pv.x, li[r]);
@@ -966,7 +992,9 @@ __device__ __forceinline__ void hw_apply(const HwGroup& G, uint32_t t, const typ
 // The pass for one block: cosets unit(0), ..., unit(count - 1) while below n_cosets;
 // after the last pass (or every energy-only pass) the block's energy and
 // norm partials go to *e_out and *n_out.
-template <typename T, bool EONLY, bool REAL, typename Unit>
+// LEAN: addresses are made again at each use, for the 64 registers that let two
+// blocks share a CU.  PIN: group headers by hw_load.
+template <typename T, bool EONLY, bool REAL, bool LEAN, bool PIN, typename Unit>
 __device__ __forceinline__ void hwin_body(const HwDesc& w, uint64_t n_cosets, uint32_t count, Unit unit,
                                           const typename VecOf<T>::type* __restrict__ psi,
                                           typename VecOf<T>::type* __restrict__ lam,
@@ -976,14 +1004,23 @@ __device__ __forceinline__ void hwin_body(const HwDesc& w, uint64_t n_cosets, ui
     using V = typename VecOf<T>::type;
     constexpr int R = 1 << kHwRegBits;
     constexpr int TB = kHwThreadBits;
+    // complex128 takes all of LDS for one coset, so one block has the CU to
+    // itself: the next coset's psi is on its way to registers and its class
+    // table made (in the other of two) while the groups of this one run.
+    // 26 qubits, energy only: 404 -> 307 us per pass (1 GiB; 233 without the
+    // groups, 300 without the memory); 24 qubits, 24 groups per pass, with lam:
+    // 303 -> 287 us (156 without the groups).  Complex coefficients leave no
+    // registers for it.
+    constexpr bool PIPE = sizeof(T) == 8 && REAL;
     // One LDS block, the small tables first so that their addresses fit the
     // immediate offsets of LDS reads: the class coefficients of the current
     // coset (after the last coset, the block reduction), their thread-part z
     // bits, then the psi coset.
-    constexpr size_t kTabBytes = kHwMaxClasses * sizeof(V) > 2 * (kHwThreads / 64) * sizeof(double)
-                                     ? kHwMaxClasses * sizeof(V)
-                                     : 2 * (kHwThreads / 64) * sizeof(double);
-    constexpr size_t kZtOff = kTabBytes, kSpOff = kTabBytes + kHwMaxClasses * sizeof(uint32_t);
+    constexpr size_t kTabOne = kHwMaxClasses * sizeof(V), kTabBytes = (PIPE ? 2 : 1) * kTabOne;
+    static_assert(kTabBytes >= 2 * (kHwThreads / 64) * sizeof(double), "the block reduction uses the class tables");
+    constexpr uint32_t kLdsTerms = PIPE ? 512 : 0;  // terms of the pass kept in LDS
+    constexpr size_t kZtOff = kTabBytes, kTmOff = kTabBytes + kHwMaxClasses * sizeof(uint32_t);
+    constexpr size_t kSpOff = kTmOff + kLdsTerms * sizeof(HwTerm<T>);
     static_assert(kSpOff % 16 == 0, "psi coset alignment");
     __shared__ __align__(16) unsigned char lds[kSpOff + (1 << kHwBits) * sizeof(V)];
     V* A = reinterpret_cast<V*>(lds);
@@ -999,28 +1036,73 @@ __device__ __forceinline__ void hwin_body(const HwDesc& w, uint64_t n_cosets, ui
 #pragma unroll
     for (int k = 0; k < TB; ++k)
         if ((t >> k) & 1) off_t += bitval[k];
-    double e_acc = 0.0, n_acc = 0.0;
-    for (uint32_t it = 0; it < count; ++it) {
-        const uint64_t c = unit(it);
-        if (c >= n_cosets) break;
+    auto base_of = [&](uint64_t c) {
         uint64_t base = c;
 #pragma unroll
         for (int k = 0; k < kHwBits; ++k) {
             const uint64_t low = base & (bitval[k] - 1);
             base = ((base ^ low) << 1) | low;
         }
-        auto addr = [&](int r) {
-            uint64_t idx = base + off_t;
+        return base;
+    };
+    // Index of pattern r; o: off_t, with LEAN or PIPE hidden from the compiler at each
+    // use, as the eight sums that it would keep over the loop cost 16 registers.
+    auto hidden = [&] {
+        uint64_t o = off_t;
+        if (LEAN || PIPE) asm volatile("" : "+v"(o));
+        return o;
+    };
+    auto addr = [&](uint64_t base, uint64_t o, int r) {
+        uint64_t idx = base + o;
 #pragma unroll
-            for (int k = 0; k < kHwRegBits; ++k)
-                if ((r >> k) & 1) idx += bitval[TB + k];
-            return idx;
+        for (int k = 0; k < kHwRegBits; ++k)
+            if ((r >> k) & 1) idx += bitval[TB + k];
+        return idx;
+    };
+    // PIPE: the thread's class and its coefficient for a coset.  A class of
+    // terms with no z bit in the window is long (60 terms at 24 qubits): its
+    // terms lie in LDS, or where a pass has too many, four loads are in flight.
+    HwTerm<T>* tl = reinterpret_cast<HwTerm<T>*>(lds + kTmOff);
+    HwClass C{};
+    bool in_lds = false;
+    uint32_t k0 = 0;
+    if (PIPE && nc) {
+        k0 = classes[w.c_begin].k_begin;
+        const uint32_t n = classes[w.c_end - 1].k_end - k0;
+        in_lds = n <= kLdsTerms;
+        if (in_lds && (uint32_t)t < n) tl[t] = terms[k0 + t];
+        if ((uint32_t)t < nc) {
+            C = classes[w.c_begin + t];
+            zt[t] = C.zt;
+        }
+        __syncthreads();
+    }
+    auto class_table = [&](uint64_t base, V* tab) {
+        if ((uint32_t)t >= nc) return;
+        T ar = 0;
+        auto sum = [&](const HwTerm<T>* tm, uint32_t n) {
+            for (uint32_t k = 0; k < n; k += 4) {
+                HwTerm<T> x[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) x[q] = tm[k + q < n ? k + q : k];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    T sg;
+                    parity_sign((uint32_t)__popcll(x[q].zo & base), sg);
+                    ar = fma(sg, q == 0 || k + q < n ? x[q].cre : T(0), ar);
+                }
+            }
         };
-        // All loads of the coset are issued before the first use waits.
-        V ps[R];
-#pragma unroll
-        for (int r = 0; r < R; ++r) ps[r] = psi[addr(r)];
-        T lr[R], li[R];
+        if (in_lds) sum(tl + (C.k_begin - k0), C.k_end - C.k_begin);
+        else sum(terms + C.k_begin, C.k_end - C.k_begin);
+        V a;
+        a.x = ar;
+        a.y = 0;
+        tab[t] = a;
+    };
+    double e_acc = 0.0, n_acc = 0.0;
+    T lr[R], li[R];
+    auto load_lam = [&](uint64_t base) {
         if (first || EONLY) {
 #pragma unroll
             for (int r = 0; r < R; ++r) {
@@ -1028,64 +1110,153 @@ __device__ __forceinline__ void hwin_body(const HwDesc& w, uint64_t n_cosets, ui
                 li[r] = 0;
             }
         } else {
+            const uint64_t o = hidden();
 #pragma unroll
             for (int r = 0; r < R; ++r) {
-                const V l = lam[addr(r)];
+                const V l = lam[addr(base, o, r)];
                 lr[r] = l.x;
                 li[r] = l.y;
             }
         }
-        if ((uint32_t)t < nc) {
-            const HwClass C = classes[w.c_begin + t];
-            T ar = 0, ai = 0;
-            for (uint32_t k = C.k_begin; k < C.k_end; ++k) {
-                const HwTerm<T> tm = terms[k];
-                T sg;
-                parity_sign((uint32_t)__popcll(tm.zo & base), sg);
-                ar = fma(sg, tm.cre, ar);
-                if (!REAL) ai = fma(sg, tm.cim, ai);
-            }
-            V a;
-            a.x = ar;
-            a.y = ai;
-            A[t] = a;
-            zt[t] = C.zt;
-        }
+    };
+    auto store_lam = [&](uint64_t base) {
+        if (EONLY) return;
+        const uint64_t o = hidden();
 #pragma unroll
-        for (int r = 0; r < R; ++r) sp[t + kHwThreads * r] = ps[r];
-        __syncthreads();
+        for (int r = 0; r < R; ++r) {
+            V l;
+            l.x = lr[r];
+            l.y = li[r];
+            lam[addr(base, o, r)] = l;
+        }
+    };
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(t >> 6);
+    auto run_groups = [&](const V* Ac) {
         for (uint32_t g = w.g_begin; g < w.g_end; ++g) {
-            const HwGroup& G = groups[g];
+            const HwGroup G = PIN ? hw_load(groups + g) : groups[g];
             static_assert(kHwRegBits == 3, "one case per register-bit subset");
+            // Energy of a real H: D_x(j) = D_x(j ^ x), so the pairs (j, j ^ x) give
+            // the same twice and one of them does, chosen by one bit of x: a bit
+            // of the wave's number (half of the waves skip the group; of those
+            // bits the ones that leave every SIMD some waves first, the others
+            // in turns), else a register bit.  It takes 7 % off a pass of 8 groups.
+            constexpr bool HALF = EONLY && REAL;
+            uint32_t skip = 0;
+            T weight = 1;
+            if (HALF) {
+                const uint32_t xl = G.xl, xw = (xl >> 6) & ((kHwThreads >> 6) - 1);
+                if (xw) {
+                    const int top = 31 - __builtin_clz(xw);
+                    if (((wave >> top) ^ (top < 2 ? g : 0)) & 1) continue;
+                    weight = 2;
+                } else if (xl >> TB) {
+                    skip = 1u << (31 - __builtin_clz(xl >> TB));
+                    weight = 2;
+                }
+            }
             T dr[R], di[R];
             switch (G.zrm) {
-                case 0: hw_group<T, 0, REAL>(G, w.c_begin, t, A, zt, dr, di); break;
-                case 1: hw_group<T, 1, REAL>(G, w.c_begin, t, A, zt, dr, di); break;
-                case 2: hw_group<T, 2, REAL>(G, w.c_begin, t, A, zt, dr, di); break;
-                case 3: hw_group<T, 3, REAL>(G, w.c_begin, t, A, zt, dr, di); break;
-                case 4: hw_group<T, 4, REAL>(G, w.c_begin, t, A, zt, dr, di); break;
-                case 5: hw_group<T, 5, REAL>(G, w.c_begin, t, A, zt, dr, di); break;
-                case 6: hw_group<T, 6, REAL>(G, w.c_begin, t, A, zt, dr, di); break;
-                default: hw_group<T, 7, REAL>(G, w.c_begin, t, A, zt, dr, di); break;
+                case 0: hw_group<T, 0, REAL>(G, w.c_begin, t, Ac, zt, dr, di); break;
+                case 1: hw_group<T, 1, REAL>(G, w.c_begin, t, Ac, zt, dr, di); break;
+                case 2: hw_group<T, 2, REAL>(G, w.c_begin, t, Ac, zt, dr, di); break;
+                case 3: hw_group<T, 3, REAL>(G, w.c_begin, t, Ac, zt, dr, di); break;
+                case 4: hw_group<T, 4, REAL>(G, w.c_begin, t, Ac, zt, dr, di); break;
+                case 5: hw_group<T, 5, REAL>(G, w.c_begin, t, Ac, zt, dr, di); break;
+                case 6: hw_group<T, 6, REAL>(G, w.c_begin, t, Ac, zt, dr, di); break;
+                default: hw_group<T, 7, REAL>(G, w.c_begin, t, Ac, zt, dr, di); break;
             }
-            hw_apply<T, REAL>(G, t, sp, dr, di, lr, li);
+            hw_apply<T, REAL, HALF>(G, t, sp, dr, di, lr, li, skip, weight);
         }
         T e_t = 0, n_t = 0;
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            if (!EONLY) {
-                V o;
-                o.x = lr[r];
-                o.y = li[r];
-                lam[addr(r)] = o;
-            }
             const V pv = sp[t + kHwThreads * r];
             e_t += pv.x * lr[r] + pv.y * li[r];
             n_t += pv.x * pv.x + pv.y * pv.y;
         }
         if (EONLY || last) e_acc += (double)e_t;
         if (EONLY ? first : last) n_acc += (double)n_t;
-        __syncthreads();  // the next coset overwrites both LDS tables
+    };
+    if constexpr (PIPE) {
+        T nr[R], ni[R];  // the next coset of psi
+        auto load_next = [&](uint64_t base) {
+            const uint64_t o = hidden();
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const V v = psi[addr(base, o, r)];
+                nr[r] = v.x;
+                ni[r] = v.y;
+            }
+        };
+        auto stage_next = [&] {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                V v;
+                v.x = nr[r];
+                v.y = ni[r];
+                sp[t + kHwThreads * r] = v;
+            }
+        };
+        // base of the block's coset it; past the last one, of coset 0: the loads
+        // then have no branch around them, whose merge would wait for them
+        auto next_base = [&](uint32_t it) {
+            const uint64_t c = it < count ? unit(it) : n_cosets;
+            return base_of(c < n_cosets ? c : 0);
+        };
+        uint64_t base = next_base(0);
+        load_next(base);
+        class_table(base, A);
+        stage_next();
+        load_lam(base);
+        for (uint32_t it = 0; it < count; ++it) {
+            if (unit(it) >= n_cosets) break;
+            __syncthreads();
+            const uint64_t nb = next_base(it + 1);
+            load_next(nb);
+            class_table(nb, A + ((it + 1) & 1) * kHwMaxClasses);
+            run_groups(A + (it & 1) * kHwMaxClasses);
+            __syncthreads();  // the psi coset is done with
+            // before lam is stored, so that only the loads are waited for
+            stage_next();
+            store_lam(base);
+            base = nb;
+            load_lam(base);
+        }
+        __syncthreads();
+    } else {
+        for (uint32_t it = 0; it < count; ++it) {
+            const uint64_t c = unit(it);
+            if (c >= n_cosets) break;
+            const uint64_t base = base_of(c);
+            // All loads of the coset are issued before the first use waits.
+            V ps[R];
+            const uint64_t o = hidden();
+#pragma unroll
+            for (int r = 0; r < R; ++r) ps[r] = psi[addr(base, o, r)];
+            load_lam(base);
+            if ((uint32_t)t < nc) {
+                const HwClass K = classes[w.c_begin + t];
+                T ar = 0, ai = 0;
+                for (uint32_t k = K.k_begin; k < K.k_end; ++k) {
+                    const HwTerm<T> tm = terms[k];
+                    T sg;
+                    parity_sign((uint32_t)__popcll(tm.zo & base), sg);
+                    ar = fma(sg, tm.cre, ar);
+                    if (!REAL) ai = fma(sg, tm.cim, ai);
+                }
+                V a;
+                a.x = ar;
+                a.y = ai;
+                A[t] = a;
+                zt[t] = K.zt;
+            }
+#pragma unroll
+            for (int r = 0; r < R; ++r) sp[t + kHwThreads * r] = ps[r];
+            __syncthreads();
+            run_groups(A);
+            store_lam(base);
+            __syncthreads();  // the next coset overwrites both LDS tables
+        }
     }
     if (!EONLY && !last) return;
     block_sum2<kHwThreads>(e_acc, n_acc, red);  // the loop's last barrier freed the class table
@@ -1095,14 +1266,14 @@ __device__ __forceinline__ void hwin_body(const HwDesc& w, uint64_t n_cosets, ui
     }
 }
 
-template <typename T, bool EONLY, bool REAL>
-__global__ void __launch_bounds__(kHwThreads)
+template <typename T, bool EONLY, bool REAL, bool LEAN>
+__global__ void __launch_bounds__(kHwThreads, (LEAN && !EONLY ? 8 : 4))
 hwin_kernel(const HwDesc w, uint64_t n_cosets, uint32_t cpt, uint32_t mlog,
             const typename VecOf<T>::type* __restrict__ psi, typename VecOf<T>::type* __restrict__ lam,
             const HwGroup* __restrict__ groups, const HwClass* __restrict__ classes,
             const HwTerm<T>* __restrict__ terms, int first, int last, double* __restrict__ part) {
     const uint64_t b = blockIdx.x;
-    hwin_body<T, EONLY, REAL>(
+    hwin_body<T, EONLY, REAL, LEAN, false>(
         w, n_cosets, cpt, [=](uint32_t it) { return xcd_unit(b, it, cpt, mlog); }, psi, lam, groups, classes, terms,
         first, last, part + 2 * b, part + 2 * b + 1);
 }
@@ -1123,7 +1294,7 @@ hwin_batch_kernel(const HwItem* __restrict__ d, uint32_t n_desc, double* __restr
     const HwItem& x = d[lo];
     const uint64_t blk = blockIdx.x - x.blk_begin, nb = x.n_blk;
     const uint32_t count = (uint32_t)((x.n_cosets - blk + nb - 1) / nb);
-    hwin_body<T, false, REAL>(
+    hwin_body<T, false, REAL, false, true>(
         x.w, x.n_cosets, count, [=](uint32_t it) { return blk + (uint64_t)it * nb; }, (const V*)x.psi, (V*)x.lam,
         x.groups,
         x.classes, (const HwTerm<T>*)x.terms, (int)x.first, (int)x.last, part + x.part_off + blk,
@@ -1289,11 +1460,15 @@ struct WinShape {
 // Reverse passes (with per-block gradient partials) use a persistent grid of
 // at most kRevBlocks blocks; forward passes a one-shot grid.
 constexpr uint64_t kRevBlocks = 2048;
+// H psi window passes of complex128: one block per CU, which goes on from coset
+// to coset (with 2048 blocks of few cosets each, and nothing to go on to, 26
+// qubits energy only 1100 us for three passes against 920).
+constexpr uint64_t kHwBlocksC128 = 256;
 
-void grid_for_units(uint64_t units, bool persistent, WinShape& w) {
+void grid_for_units(uint64_t units, bool persistent, WinShape& w, uint64_t most = kRevBlocks) {
     w.mlog = log2_pow2(units);
     if (persistent) {
-        const uint64_t g = units < kRevBlocks ? units : kRevBlocks;
+        const uint64_t g = units < most ? units : most;
         w.grid = (uint32_t)(g ? g : 1);
         w.cpt = (uint32_t)((units + w.grid - 1) / w.grid);
     } else {
@@ -1457,16 +1632,23 @@ hipError_t launch_hwin(int n, const HwDesc& w, const void* psi, void* lam, const
     if (n < kHwBits || w.c_end < w.c_begin || w.c_end - w.c_begin > (uint32_t)kHwMaxClasses)
         return hipErrorInvalidValue;
     WinShape ws{};
-    grid_for_units(1ull << (n - kHwBits), true, ws);
+    grid_for_units(1ull << (n - kHwBits), true, ws, sizeof(T) == 8 ? kHwBlocksC128 : kRevBlocks);
     *nblocks = ws.grid;
-#define VQE_HWIN(EO, RE)                                                                                      \
-    hipLaunchKernelGGL((hwin_kernel<T, EO, RE>), dim3(ws.grid), dim3(kHwThreads), 0, st, w, 1ull << (n - kHwBits), \
+#define VQE_HWIN(EO, RE, LE)                                                                                  \
+    hipLaunchKernelGGL((hwin_kernel<T, EO, RE, LE>), dim3(ws.grid), dim3(kHwThreads), 0, st, w, 1ull << (n - kHwBits), \
                        ws.cpt, ws.mlog, (const V*)psi, (V*)lam, groups, classes, terms, first ? 1 : 0, last ? 1 : 0, \
                        part)
+    // complex64: two blocks per CU where there are cosets for both (28 qubits, three
+    // passes: 4.8 ms against 5.7 with the registers of one); below, one with more
+    // registers (20 qubits, five passes of 128 cosets: 157 us against 180)
+    const bool lean = sizeof(T) == 4 && ws.grid > 256;
     if (lam) {
-        if (real) VQE_HWIN(false, true); else VQE_HWIN(false, false);
+        if (!real) VQE_HWIN(false, false, false);
+        else if (lean) VQE_HWIN(false, true, (sizeof(T) == 4));
+        else VQE_HWIN(false, true, false);
     } else {
-        if (real) VQE_HWIN(true, true); else VQE_HWIN(true, false);
+        if (real) VQE_HWIN(true, true, true);
+        else VQE_HWIN(true, false, false);
     }
 #undef VQE_HWIN
     return hipGetLastError();
