@@ -372,9 +372,11 @@ std::string jit_source(bool dbl, int K, int S, int NV, const std::vector<KOp>& o
     // Reverse kernels ask for two blocks per CU: unconstrained they take 256 VGPRs plus a few
     // AGPRs, one wave per SIMD; at two waves the compiler spills a few dwords (complex64
     // reverse pass 37.9 -> 36.4 ms at 32 qubits, complex128 unchanged).
+    // in and out may be the same state: not __restrict__, or a pass of renames
+    // alone may store an amplitude before another one's place is read.
     o << "extern \"C\" __global__ void __launch_bounds__(" << kBlock << (NV == 2 ? ", 2" : "") << ")\n"
       << jit_kernel_name(NV, dbl) << "(const JitArgs a, const Mat2* __restrict__ mats, u32 cpt, u32 mlog, "
-         "const V* __restrict__ in0, V* __restrict__ out0, const V* __restrict__ in1, V* __restrict__ out1, "
+         "const V* in0, V* out0, const V* in1, V* out1, "
          "double* __restrict__ gpart) {\n"
       << "  const int tid = threadIdx.x;\n  const int lane = tid & 63;\n"
       << "  const int sub = (tid >> 6) * " << CPW << " + (lane & " << (CPW - 1) << ");\n"
