@@ -272,7 +272,9 @@ int vqe_apply_hamiltonian(vqe_state* psi, vqe_state* lam, const vqe_hamiltonian*
  * k (grad has n_params doubles).  In the default kernel form an ADJOINT
  * evaluation of a state that fits LDS (n <= VQE_BATCH_MAX_QUBITS_C64 /
  * VQE_BATCH_MAX_QUBITS_C128) is one launch of the small-state kernel of the
- * batches below, for every gate kind and with checkpoints.
+ * batches below, for every gate kind and with checkpoints; above that and
+ * below VQE_SPECIALIZE_AUTO_MIN_QUBITS it runs the passes of mid-size batch
+ * items on psi and lam.
  *   ADJOINT: forward sweep, lam = H psi, then one reverse sweep un-applying
  *     one gate at a time from psi and lam, with dE/dtheta_k = Im<lam|G_k|psi>
  *     / <psi|psi> just after gate k, R_k = exp(-i theta_k G_k / 2).  lam must

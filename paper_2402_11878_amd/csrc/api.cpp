@@ -6,6 +6,7 @@
 #include <cmath>
 #include <cstring>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <numeric>
 
@@ -61,6 +62,7 @@ struct vqe_state {
     std::vector<int8_t> rev_flip;
     size_t mats_cap = 0;
     hipEvent_t mats_ev = nullptr;  // completion of the last upload from h_mats
+    vqe_batch* mid = nullptr;      // buffers of evaluations by batch programs (made on first use)
 };
 
 // Physical op list of a pass in the lane-split layout with S split bits.
@@ -1629,7 +1631,7 @@ int ensure_batch(const vqe_circuit* cc, int d, bool ckpt = false) {
         std::iota(local, local + 64, 0);
         ok = add(batch_bits(c->n), all);
     } else {
-        ok = plan_tiles(c->n, c->gates, TileLimits{kMidWin, kMidLow, 1 << 20, kMidMaxSlots}, np.passes, msg);
+        ok = plan_tiles(c->n, c->gates, TileLimits{kMidWin, kMidLow, 1 << 20, kMidMaxSlots, kMidPlanWidth}, np.passes, msg);
         if (ok && np.passes.empty()) {  // no gates: one pass that only prepares |0...0>
             np.passes.emplace_back();
             for (int q = 0; q < kMidWin; ++q) np.passes[0].pos[np.passes[0].K++] = q;
@@ -1858,9 +1860,14 @@ int mid_reserve(vqe_batch* b, size_t dev, size_t host) {
 // per pass index over every item that has that pass; lam = H psi; reverse
 // passes likewise; one reduction launch that writes the results to the pinned
 // buffer.  Per item: psi and lam in the batch's device buffer, n_blk =
-// min(2^(n - kMidWin), kMidMaxBlocks) blocks per launch.
+// min(2^(n - kMidWin), kMidMaxBlocks) blocks per launch.  own: one item, on the
+// states of an evaluation instead of the batch's buffer, with its options.
+struct MidOwn {
+    vqe_state *psi, *lam;
+    const vqe_grad_opts* opts;
+};
 template <typename T>
-int mid_impl(vqe_batch* b, const vqe_batch_item* items, const std::vector<size_t>& idx) {
+int mid_impl(vqe_batch* b, const vqe_batch_item* items, const std::vector<size_t>& idx, const MidOwn* own = nullptr) {
     const int dt = sizeof(T) == 8 ? 1 : 0;
     const size_t m = idx.size();
     const size_t amp = 2 * sizeof(T);
@@ -1893,7 +1900,7 @@ int mid_impl(vqe_batch* b, const vqe_batch_item* items, const std::vector<size_t
         red_base[k] = n_red;
         n_red += 2 + bp.slot_param.size();
         st_off[k] = st_bytes;
-        st_bytes += 2 * st_bytes_half(c->n, amp);
+        if (!own) st_bytes += 2 * st_bytes_half(c->n, amp);
         img_off[k] = n_img;
         n_img += bp.image.size();
         n_pass += bp.passes.size();
@@ -1918,8 +1925,10 @@ int mid_impl(vqe_batch* b, const vqe_batch_item* items, const std::vector<size_t
     auto* hw = (HwItem*)(h + o_hw);
     double* part = (double*)(d + o_out);
     double* out = (double*)(h + o_out);
-    auto psi_of = [&](size_t k) { return d + o_st + st_off[k]; };
-    auto lam_of = [&](size_t k) { return d + o_st + st_off[k] + st_bytes_half(items[idx[k]].circuit->n, amp); };
+    auto psi_of = [&](size_t k) { return own ? (char*)own->psi->data : d + o_st + st_off[k]; };
+    auto lam_of = [&](size_t k) {
+        return own ? (char*)own->lam->data : d + o_st + st_off[k] + st_bytes_half(items[idx[k]].circuit->n, amp);
+    };
     // numbers, tile-form H psi and reduction descriptors per item
     size_t n_th = 0;
     uint32_t hblk = 0;
@@ -2021,16 +2030,48 @@ int mid_impl(vqe_batch* b, const vqe_batch_item* items, const std::vector<size_t
         l_grid[p] = blk;
     }
     VQE_HIP(hipMemcpyAsync(d, h, o_img + n_img, hipMemcpyHostToDevice, b->stream));
+    const double S = own ? (double)own->psi->bytes : 0.0;
+    auto prof = [&](int kind, double bytes) {  // only evaluations of a state are traced
+        return own ? std::make_unique<ProfScope>(kind, bytes, b->stream) : nullptr;
+    };
+    // own: after that many passes psi is copied to a checkpoint, and from it before they are un-applied
+    std::vector<size_t> bounds;
+    std::vector<void*> ck;
+    for (int k = 0, n = own && own->opts ? own->opts->n_ckpt : 0; k < n; ++k) {
+        const size_t at = (size_t)std::llround((double)(k + 1) * (double)pmax / (double)(n + 1));
+        if (at < 1 || at >= pmax || (!bounds.empty() && bounds.back() == at)) continue;
+        bounds.push_back(at);
+        ck.push_back(own->opts->ckpt[k]->data);
+    }
+    const size_t chunk = own && own->opts && own->opts->chunk_passes > 0 ? (size_t)own->opts->chunk_passes : 0;
+    auto launch = [&](size_t p, bool rev) {
+        const size_t done = rev ? pmax - p : p + 1;  // passes applied: before a reverse pass, after a forward one
+        const auto at = std::find(bounds.begin(), bounds.end(), done);
+        void* c = at == bounds.end() ? nullptr : ck[(size_t)(at - bounds.begin())];
+        if (c && rev) VQE_HIP(hipMemcpyAsync(own->psi->data, c, own->psi->bytes, hipMemcpyDeviceToDevice, b->stream));
+        {
+            auto ps = prof(rev ? VQE_KERNEL_WINDOW_REV : VQE_KERNEL_WINDOW_FWD, (rev ? 4.0 : 2.0) * S);
+            VQE_HIP(launch_mid_pass<T>((const MidPass*)(d + (rev ? o_rev : o_fwd)) + l_off[p], (uint32_t)l_cnt[p],
+                                       l_grid[p], rev, part, b->stream));
+        }
+        if (c && !rev) VQE_HIP(hipMemcpyAsync(c, own->psi->data, own->psi->bytes, hipMemcpyDeviceToDevice, b->stream));
+        if (chunk && (p + 1) % chunk == 0 && (!rev || p + 1 < pmax)) VQE_HIP(hipStreamSynchronize(b->stream));
+        return (int)VQE_OK;
+    };
     for (size_t p = 0; p < pmax; ++p)
-        VQE_HIP(launch_mid_pass<T>((const MidPass*)(d + o_fwd) + l_off[p], (uint32_t)l_cnt[p], l_grid[p], false, part,
-                                   b->stream));
-    if (n_th) VQE_HIP(launch_mid_hpsi<T>((const MidHam*)(d + o_ham), (uint32_t)n_th, hblk, part, b->stream));
-    for (const HwLaunch& L : hw_launch)
+        if (int rc = launch(p, false)) return rc;
+    if (n_th) {
+        auto ps = prof(VQE_KERNEL_HPSI, own ? hpsi_bytes(items[idx[0]].hamiltonian, own->psi, true) : 0.0);
+        VQE_HIP(launch_mid_hpsi<T>((const MidHam*)(d + o_ham), (uint32_t)n_th, hblk, part, b->stream));
+    }
+    for (size_t l = 0; l < hw_launch.size(); ++l) {
+        const HwLaunch& L = hw_launch[l];
+        auto ps = prof(VQE_KERNEL_HPSI, (l ? 3.0 : 2.0) * S);
         VQE_HIP(launch_hwin_batch<T>((const HwItem*)(d + o_hw) + L.off, (uint32_t)L.cnt, L.grid, L.real, part,
                                      b->stream));
+    }
     for (size_t p = 0; p < pmax; ++p)
-        VQE_HIP(launch_mid_pass<T>((const MidPass*)(d + o_rev) + l_off[p], (uint32_t)l_cnt[p], l_grid[p], true, part,
-                                   b->stream));
+        if (int rc = launch(p, true)) return rc;
     VQE_HIP(launch_mid_reduce((const MidRed*)(d + o_red), (uint32_t)n_red, part, out, b->stream));
     VQE_HIP(hipStreamSynchronize(b->stream));
     for (size_t k = 0; k < m; ++k) {
@@ -2135,6 +2176,7 @@ int vqe_state_free(vqe_state* s) {
     if (s->d_mats) (void)hipFree(s->d_mats);
     if (s->h_mats) (void)hipHostFree(s->h_mats);
     if (s->mats_ev) (void)hipEventDestroy(s->mats_ev);
+    (void)vqe_batch_free(s->mid);
     delete s;
     return VQE_OK;
 }
@@ -2570,6 +2612,23 @@ int vqe_energy_grad(vqe_state* psi, vqe_state* lam, const vqe_circuit* c, const 
     if (jit_mode() == VQE_SPECIALIZE_AUTO && psi->n <= max_small(psi->dtype))
         return psi->dtype == VQE_C64 ? small_grad<float>(psi, lam, c, params, h, opts, energy, grad)
                                      : small_grad<double>(psi, lam, c, params, h, opts, energy, grad);
+    // Above that, where specialised kernels are not worth compiling, the batch
+    // programs of mid-size items on the caller's states: 2 to 4 passes over
+    // 12-qubit windows instead of 10 to 30 over 5 qubits.  4 / 12 layers, interpreted
+    // window passes against these: complex64 14 qubits 478 / 1247 us, 209 / 498;
+    // 19 qubits 666 / 1784, 326 / 782; complex128 13 qubits 441 / 1179, 249 / 626; 19
+    // qubits 752 / 1963, 405 / 1010.
+    if (jit_mode() == VQE_SPECIALIZE_AUTO && psi->n < VQE_SPECIALIZE_AUTO_MIN_QUBITS && !use_tiles(c)) {
+        if (!psi->mid) {
+            psi->mid = new vqe_batch();
+            psi->mid->dtype = psi->dtype;
+            psi->mid->stream = psi->stream;
+            psi->mid->device = psi->device;
+        }
+        const vqe_batch_item it{c, h, params, n_params, energy, grad};
+        const MidOwn own{psi, lam, opts};
+        return psi->dtype == VQE_C64 ? mid_impl<float>(psi->mid, &it, {0}, &own) : mid_impl<double>(psi->mid, &it, {0}, &own);
+    }
     return psi->dtype == VQE_C64 ? adjoint_impl<float>(psi, lam, c, params, h, opts, energy, grad)
                                  : adjoint_impl<double>(psi, lam, c, params, h, opts, energy, grad);
     VQE_GUARD_END

@@ -160,11 +160,11 @@ bool plan_passes(int n, const std::vector<Gate>& gates, const PlanLimits& lim, s
 
 // Tile passes (see plan_tiles in vqe_internal.h): beam search over the order
 // of the windows.  A state is the head of every qubit's chain; a step takes a
-// candidate window to its closure.  After each depth the `kWidth` states with
+// candidate window to its closure.  After each depth the lim.width states with
 // the most scheduled gates live on; the first to schedule every gate wins.
 // Greedy (width 1) leaves the ends of the CNOT ladders to passes of their
 // own: 13 passes at 32 qubits x 8 layers (12-qubit tiles, 3 low qubits)
-// against 10 with this width.
+// against 10 with 48.
 bool plan_tiles(int n, const std::vector<Gate>& gates, const TileLimits& lim, std::vector<PlannedPass>& out,
                 std::string& msg) {
     out.clear();
@@ -216,7 +216,7 @@ bool plan_tiles(int n, const std::vector<Gate>& gates, const TileLimits& lim, st
         int parent;
         uint64_t W;
     };
-    constexpr size_t kWidth = 48, kWorkBudget = 4000000;  // steps of `close`, about 20 ms of planning
+    constexpr size_t kWorkBudget = 4000000;  // steps of `close`, about 20 ms of planning
     std::vector<std::vector<Node>> depth(1);
     depth[0].push_back(Node{Head(n, 0), 0, -1, 0});
     int goal = -1;
@@ -265,7 +265,7 @@ bool plan_tiles(int n, const std::vector<Gate>& gates, const TileLimits& lim, st
         }
         if (goal < 0) {
             std::stable_sort(next.begin(), next.end(), [](const Node& a, const Node& b) { return a.count > b.count; });
-            if (next.size() > kWidth) next.resize(kWidth);
+            if (next.size() > (size_t)lim.width) next.resize((size_t)lim.width);
         }
         depth.push_back(std::move(next));
     }
