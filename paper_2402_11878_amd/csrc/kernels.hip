@@ -859,10 +859,17 @@ constexpr int kHwThreads = 1 << kHwThreadBits;  // 16 waves per CU at one block
 
 // (-1)^cnt as a floating-point factor: the sign bit set from the low bit of
 // cnt on the bit pattern of 1.0.
-__device__ __forceinline__ void parity_sign(uint32_t cnt, double& s) {
-    s = __hiloint2double((int)((cnt << 31) | 0x3ff00000u), 0);
+// Or of another unit, given as the high bits of its pattern.
+__device__ __forceinline__ constexpr uint32_t hw_one(double) { return 0x3ff00000u; }
+__device__ __forceinline__ constexpr uint32_t hw_one(float) { return 0x3f800000u; }
+__device__ __forceinline__ constexpr uint32_t hw_two(double) { return 0x40000000u; }
+__device__ __forceinline__ constexpr uint32_t hw_two(float) { return 0x40000000u; }
+__device__ __forceinline__ void parity_sign(uint32_t cnt, double& s, uint32_t unit = 0x3ff00000u) {
+    s = __hiloint2double((int)((cnt << 31) | unit), 0);
 }
-__device__ __forceinline__ void parity_sign(uint32_t cnt, float& s) { s = __uint_as_float((cnt << 31) | 0x3f800000u); }
+__device__ __forceinline__ void parity_sign(uint32_t cnt, float& s, uint32_t unit = 0x3f800000u) {
+    s = __uint_as_float((cnt << 31) | unit);
+}
 
 // A group's header as a whole, in scalar registers: left to the compiler its
 // words are fetched one by one where they are used, each a wait of about 200
@@ -897,7 +904,7 @@ __device__ __forceinline__ HwGroup hw_load(const HwGroup* g) {
 // imaginary halves of the class sums, the transform and the update vanish.
 template <typename T, int M, bool REAL>
 __device__ __forceinline__ void hw_group(const HwGroup& G, uint32_t cbase, uint32_t t,
-                                         const typename VecOf<T>::type* A, const uint32_t* zt, T* dr, T* di) {
+                                         const typename VecOf<T>::type* A, const uint32_t* zt, uint32_t unit, T* dr, T* di) {
     using V = typename VecOf<T>::type;
     constexpr int R = 1 << kHwRegBits;
     T er[R], ei[R];
@@ -922,14 +929,14 @@ __device__ __forceinline__ void hw_group(const HwGroup& G, uint32_t cbase, uint3
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 T sg;
-                parity_sign((uint32_t)__popc(z[q] & t), sg);
+                parity_sign((uint32_t)__popc(z[q] & t), sg, unit);
                 sr = fma(sg, a[q].x, sr);
                 if (!REAL) si = fma(sg, a[q].y, si);
             }
         }
         for (; j < e; ++j, ++jv) {
             T sg;
-            parity_sign((uint32_t)__popc(zt[jv] & t), sg);
+            parity_sign((uint32_t)__popc(zt[jv] & t), sg, unit);
             const V a = A[jv];
             sr = fma(sg, a.x, sr);
             if (!REAL) si = fma(sg, a.y, si);
@@ -962,10 +969,9 @@ __device__ __forceinline__ void hw_group(const HwGroup& G, uint32_t cbase, uint3
 
 // lam_r += D_r psi[(t + kHwThreads r) ^ xl] for the R patterns of thread t
 // (one code path for every register-bit subset of the group's classes).
-// HALF: only the patterns r without the bits in `skip`, counted `weight` times.
-template <typename T, bool REAL, bool HALF>
+template <typename T, bool REAL>
 __device__ __forceinline__ void hw_apply(const HwGroup& G, uint32_t t, const typename VecOf<T>::type* sp,
-                                         const T* dr, const T* di, T* lr, T* li, uint32_t skip = 0, T weight = 1) {
+                                         const T* dr, const T* di, T* lr, T* li) {
     using V = typename VecOf<T>::type;
     constexpr int R = 1 << kHwRegBits;
     // partner of pattern t + kHwThreads r: byte offset a0 + (r ^ xr) kHwThreads sizeof(V)
@@ -974,11 +980,9 @@ __device__ __forceinline__ void hw_apply(const HwGroup& G, uint32_t t, const typ
     const char* spb = reinterpret_cast<const char*>(sp);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        if (HALF && (r & skip)) continue;
         const V pv = *reinterpret_cast<const V*>(spb + a0 + (r ^ xr) * (uint32_t)(kHwThreads * sizeof(V)));
-        const T d = HALF ? dr[r] * weight : dr[r];
-        lr[r] = fma(d, pv.x, lr[r]);
-        li[r] = fma(d, pv.y, li[r]);
+        lr[r] = fma(dr[r], pv.x, lr[r]);
+        li[r] = fma(dr[r], pv.y, li[r]);
         if (!REAL) {
             lr[r] = fma(-di[r], pv.y, lr[r]);
             li[r] = fma(di[r], pv.x, li[r]);
@@ -992,9 +996,10 @@ __device__ __forceinline__ void hw_apply(const HwGroup& G, uint32_t t, const typ
 // The pass for one block: cosets unit(0), ..., unit(count - 1) while below n_cosets;
 // after the last pass (or every energy-only pass) the block's energy and
 // norm partials go to *e_out and *n_out.
-// LEAN: addresses are made again at each use, for the 64 registers that let two
-// blocks share a CU.  PIN: group headers by hw_load.
-template <typename T, bool EONLY, bool REAL, bool LEAN, bool PIN, typename Unit>
+// MANY: blocks go on from coset to coset (complex128, real coefficients: PIPE), or
+// share a CU in pairs (complex64: addresses made again at each use, for 64
+// registers).  PIN: group headers by hw_load.
+template <typename T, bool EONLY, bool REAL, bool MANY, bool PIN, typename Unit>
 __device__ __forceinline__ void hwin_body(const HwDesc& w, uint64_t n_cosets, uint32_t count, Unit unit,
                                           const typename VecOf<T>::type* __restrict__ psi,
                                           typename VecOf<T>::type* __restrict__ lam,
@@ -1007,11 +1012,11 @@ __device__ __forceinline__ void hwin_body(const HwDesc& w, uint64_t n_cosets, ui
     // complex128 takes all of LDS for one coset, so one block has the CU to
     // itself: the next coset's psi is on its way to registers and its class
     // table made (in the other of two) while the groups of this one run.
-    // 26 qubits, energy only: 404 -> 307 us per pass (1 GiB; 233 without the
+    // 26 qubits, energy only: 404 -> 305 us per pass (1 GiB; 233 without the
     // groups, 300 without the memory); 24 qubits, 24 groups per pass, with lam:
     // 303 -> 287 us (156 without the groups).  Complex coefficients leave no
     // registers for it.
-    constexpr bool PIPE = sizeof(T) == 8 && REAL;
+    constexpr bool PIPE = sizeof(T) == 8 && REAL && MANY;
     // One LDS block, the small tables first so that their addresses fit the
     // immediate offsets of LDS reads: the class coefficients of the current
     // coset (after the last coset, the block reduction), their thread-part z
@@ -1045,11 +1050,11 @@ __device__ __forceinline__ void hwin_body(const HwDesc& w, uint64_t n_cosets, ui
         }
         return base;
     };
-    // Index of pattern r; o: off_t, with LEAN or PIPE hidden from the compiler at each
+    // Index of pattern r; o: off_t, with MANY hidden from the compiler at each
     // use, as the eight sums that it would keep over the loop cost 16 registers.
     auto hidden = [&] {
         uint64_t o = off_t;
-        if (LEAN || PIPE) asm volatile("" : "+v"(o));
+        if (MANY) asm volatile("" : "+v"(o));
         return o;
     };
     auto addr = [&](uint64_t base, uint64_t o, int r) {
@@ -1133,40 +1138,40 @@ __device__ __forceinline__ void hwin_body(const HwDesc& w, uint64_t n_cosets, ui
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(t >> 6);
     auto run_groups = [&](const V* Ac) {
         for (uint32_t g = w.g_begin; g < w.g_end; ++g) {
-            const HwGroup G = PIN ? hw_load(groups + g) : groups[g];
+            HwGroup pinned;
+            if (PIN) pinned = hw_load(groups + g);
+            const HwGroup& G = PIN ? pinned : groups[g];
             static_assert(kHwRegBits == 3, "one case per register-bit subset");
             // Energy of a real H: D_x(j) = D_x(j ^ x), so the pairs (j, j ^ x) give
-            // the same twice and one of them does, chosen by one bit of x: a bit
-            // of the wave's number (half of the waves skip the group; of those
-            // bits the ones that leave every SIMD some waves first, the others
-            // in turns), else a register bit.  It takes 7 % off a pass of 8 groups.
-            constexpr bool HALF = EONLY && REAL;
-            uint32_t skip = 0;
-            T weight = 1;
-            if (HALF) {
-                const uint32_t xl = G.xl, xw = (xl >> 6) & ((kHwThreads >> 6) - 1);
+            // the same twice: where x has bits of the wave's number, one of them
+            // tells the half of the waves that do the group, at twice the weight
+            // (a bit that leaves every SIMD some waves, or the others in turns).
+            // A register bit would do too, but the branches part the LDS reads:
+            // 23 qubits complex64 189 us per energy against 174 without any halves.
+            uint32_t unit = hw_one(T(0));
+            if (EONLY && REAL) {
+                const uint32_t xw = (G.xl >> 6) & ((kHwThreads >> 6) - 1);
                 if (xw) {
                     const int top = 31 - __builtin_clz(xw);
                     if (((wave >> top) ^ (top < 2 ? g : 0)) & 1) continue;
-                    weight = 2;
-                } else if (xl >> TB) {
-                    skip = 1u << (31 - __builtin_clz(xl >> TB));
-                    weight = 2;
+                    unit = hw_two(T(0));
                 }
             }
             T dr[R], di[R];
             switch (G.zrm) {
-                case 0: hw_group<T, 0, REAL>(G, w.c_begin, t, Ac, zt, dr, di); break;
-                case 1: hw_group<T, 1, REAL>(G, w.c_begin, t, Ac, zt, dr, di); break;
-                case 2: hw_group<T, 2, REAL>(G, w.c_begin, t, Ac, zt, dr, di); break;
-                case 3: hw_group<T, 3, REAL>(G, w.c_begin, t, Ac, zt, dr, di); break;
-                case 4: hw_group<T, 4, REAL>(G, w.c_begin, t, Ac, zt, dr, di); break;
-                case 5: hw_group<T, 5, REAL>(G, w.c_begin, t, Ac, zt, dr, di); break;
-                case 6: hw_group<T, 6, REAL>(G, w.c_begin, t, Ac, zt, dr, di); break;
-                default: hw_group<T, 7, REAL>(G, w.c_begin, t, Ac, zt, dr, di); break;
+                case 0: hw_group<T, 0, REAL>(G, w.c_begin, t, Ac, zt, unit, dr, di); break;
+                case 1: hw_group<T, 1, REAL>(G, w.c_begin, t, Ac, zt, unit, dr, di); break;
+                case 2: hw_group<T, 2, REAL>(G, w.c_begin, t, Ac, zt, unit, dr, di); break;
+                case 3: hw_group<T, 3, REAL>(G, w.c_begin, t, Ac, zt, unit, dr, di); break;
+                case 4: hw_group<T, 4, REAL>(G, w.c_begin, t, Ac, zt, unit, dr, di); break;
+                case 5: hw_group<T, 5, REAL>(G, w.c_begin, t, Ac, zt, unit, dr, di); break;
+                case 6: hw_group<T, 6, REAL>(G, w.c_begin, t, Ac, zt, unit, dr, di); break;
+                default: hw_group<T, 7, REAL>(G, w.c_begin, t, Ac, zt, unit, dr, di); break;
             }
-            hw_apply<T, REAL, HALF>(G, t, sp, dr, di, lr, li, skip, weight);
+            hw_apply<T, REAL>(G, t, sp, dr, di, lr, li);
         }
+    };
+    auto add_energy = [&] {
         T e_t = 0, n_t = 0;
 #pragma unroll
         for (int r = 0; r < R; ++r) {
@@ -1215,6 +1220,7 @@ __device__ __forceinline__ void hwin_body(const HwDesc& w, uint64_t n_cosets, ui
             load_next(nb);
             class_table(nb, A + ((it + 1) & 1) * kHwMaxClasses);
             run_groups(A + (it & 1) * kHwMaxClasses);
+            add_energy();
             __syncthreads();  // the psi coset is done with
             // before lam is stored, so that only the loads are waited for
             stage_next();
@@ -1255,6 +1261,7 @@ __device__ __forceinline__ void hwin_body(const HwDesc& w, uint64_t n_cosets, ui
             __syncthreads();
             run_groups(A);
             store_lam(base);
+            add_energy();
             __syncthreads();  // the next coset overwrites both LDS tables
         }
     }
@@ -1266,14 +1273,14 @@ __device__ __forceinline__ void hwin_body(const HwDesc& w, uint64_t n_cosets, ui
     }
 }
 
-template <typename T, bool EONLY, bool REAL, bool LEAN>
-__global__ void __launch_bounds__(kHwThreads, (LEAN && !EONLY ? 8 : 4))
+template <typename T, bool EONLY, bool REAL, bool MANY>
+__global__ void __launch_bounds__(kHwThreads, (MANY && sizeof(T) == 4 && !EONLY ? 8 : 4))
 hwin_kernel(const HwDesc w, uint64_t n_cosets, uint32_t cpt, uint32_t mlog,
             const typename VecOf<T>::type* __restrict__ psi, typename VecOf<T>::type* __restrict__ lam,
             const HwGroup* __restrict__ groups, const HwClass* __restrict__ classes,
             const HwTerm<T>* __restrict__ terms, int first, int last, double* __restrict__ part) {
     const uint64_t b = blockIdx.x;
-    hwin_body<T, EONLY, REAL, LEAN, false>(
+    hwin_body<T, EONLY, REAL, MANY, false>(
         w, n_cosets, cpt, [=](uint32_t it) { return xcd_unit(b, it, cpt, mlog); }, psi, lam, groups, classes, terms,
         first, last, part + 2 * b, part + 2 * b + 1);
 }
@@ -1464,6 +1471,7 @@ constexpr uint64_t kRevBlocks = 2048;
 // to coset (with 2048 blocks of few cosets each, and nothing to go on to, 26
 // qubits energy only 1100 us for three passes against 920).
 constexpr uint64_t kHwBlocksC128 = 256;
+constexpr uint32_t kHwManyLog = 8;  // 2^8 cosets: one per CU
 
 void grid_for_units(uint64_t units, bool persistent, WinShape& w, uint64_t most = kRevBlocks) {
     w.mlog = log2_pow2(units);
@@ -1638,17 +1646,21 @@ hipError_t launch_hwin(int n, const HwDesc& w, const void* psi, void* lam, const
     hipLaunchKernelGGL((hwin_kernel<T, EO, RE, LE>), dim3(ws.grid), dim3(kHwThreads), 0, st, w, 1ull << (n - kHwBits), \
                        ws.cpt, ws.mlog, (const V*)psi, (V*)lam, groups, classes, terms, first ? 1 : 0, last ? 1 : 0, \
                        part)
-    // complex64: two blocks per CU where there are cosets for both (28 qubits, three
-    // passes: 4.8 ms against 5.7 with the registers of one); below, one with more
-    // registers (20 qubits, five passes of 128 cosets: 157 us against 180)
-    const bool lean = sizeof(T) == 4 && ws.grid > 256;
+    // More than one coset per CU.  complex64: two blocks per CU (28 qubits, three
+    // passes: 4.8 ms against 5.7 with the registers of one; 20 qubits, 128 cosets,
+    // 180 us against 157 for five).  complex128: one block per CU that goes on (24
+    // qubits, eight cosets per block: 2780 us against 2980 for ten passes; 22 qubits,
+    // two, 78 us against 74 with lam, but 126 against 144 energy only; 14 qubits, one,
+    // 51 us against 43).
+    const bool many = ws.mlog > kHwManyLog + (sizeof(T) == 8 && lam ? 1 : 0);
     if (lam) {
         if (!real) VQE_HWIN(false, false, false);
-        else if (lean) VQE_HWIN(false, true, (sizeof(T) == 4));
+        else if (many) VQE_HWIN(false, true, true);
         else VQE_HWIN(false, true, false);
     } else {
-        if (real) VQE_HWIN(true, true, true);
-        else VQE_HWIN(true, false, false);
+        if (!real) VQE_HWIN(true, false, false);
+        else if (many) VQE_HWIN(true, true, true);
+        else VQE_HWIN(true, true, false);
     }
 #undef VQE_HWIN
     return hipGetLastError();
