@@ -141,6 +141,7 @@ struct vqe_hamiltonian {
     std::vector<TermDesc<float>> t32;
     std::vector<TermDesc<double>> t64;
     double identity = 0.0;
+    double norm1 = 0.0;  // sum of |w|: bounds the 2-norm of H psi for a normalised psi
     // every folded coefficient real (each term has an even number of Y, as for
     // any real symmetric H): the window passes of H psi skip imaginary parts
     bool real_coeffs = true;
@@ -952,16 +953,17 @@ bool shear_coefficients(double a, Mat2<T>& m) {
 }
 
 // Fills the tables of a circuit's tile passes (both directions) for these
-// parameters and uploads them on the state's stream.
+// parameters and uploads them on the state's stream; norm: see turn_limit().
 template <typename T>
-int upload_tables(vqe_state* s, const vqe_circuit* c, const TilePlan& tp, const double* params, const T** out) {
+int upload_tables(vqe_state* s, const vqe_circuit* c, const TilePlan& tp, const double* params, double norm, const T** out) {
     const size_t bytes = std::max<size_t>(tp.tab_total, 1) * sizeof(T);
     if (int rc = stage_mats(s, bytes)) return rc;
     std::vector<HalfAngle> h;
     half_angles(c, params, h);
+    const double limit = turn_limit(sizeof(T) == 8, norm);
     for (int dir = 0; dir < 2; ++dir)
         for (size_t p = 0; p < tp.passes.size(); ++p)
-            fill_tile_table<T>(tp.k[dir][p], c->gates, h.data(), dir, (T*)s->h_mats + tp.tab_off[dir][p]);
+            fill_tile_table<T>(tp.k[dir][p], c->gates, h.data(), limit, dir, (T*)s->h_mats + tp.tab_off[dir][p]);
     VQE_HIP(hipMemcpyAsync(s->d_mats, s->h_mats, bytes, hipMemcpyHostToDevice, s->stream));
     VQE_HIP(hipEventRecord(s->mats_ev, s->stream));
     *out = (const T*)s->d_mats;
@@ -1033,11 +1035,11 @@ void tile_args(const PlannedPass& p, int n, TileArgs& a) {
 
 template <typename T>
 int forward_tiles(vqe_state* s, const vqe_circuit* c, const double* params, const std::vector<size_t>& bounds,
-                  const std::vector<void*>& ckpt_ptr, bool zero, int chunk) {
+                  const std::vector<void*>& ckpt_ptr, bool zero, double norm, int chunk) {
     const int d = sizeof(T) == 8 ? 1 : 0;
     const TilePlan& tp = c->tile[d];
     const T* tab = nullptr;
-    if (int rc = upload_tables<T>(s, c, tp, params, &tab)) return rc;
+    if (int rc = upload_tables<T>(s, c, tp, params, norm, &tab)) return rc;
     if (zero && tp.passes.empty()) VQE_HIP(launch_set_basis(s->dtype, s->data, 1ull << s->n, 0, s->stream));
     void* cur = s->data;
     TileArgs a;
@@ -1059,14 +1061,15 @@ int forward_tiles(vqe_state* s, const vqe_circuit* c, const double* params, cons
 }
 
 // Forward passes from |0...0> (zero) or in place on the current state.
-// ckpt_ptr[k] receives the state at boundary bounds[k] (pass index + 1).
+// ckpt_ptr[k] receives the state at boundary bounds[k] (pass index + 1); norm:
+// bound on the 2-norms of the vectors of this evaluation (turn_limit()).
 template <typename T>
 int forward(vqe_state* s, const vqe_circuit* c, const double* params, const std::vector<size_t>& bounds,
-            const std::vector<void*>& ckpt_ptr, bool zero, int chunk = 0) {
+            const std::vector<void*>& ckpt_ptr, bool zero, double norm, int chunk = 0) {
     const int d = sizeof(T) == 8 ? 1 : 0;
     if (use_tiles(c)) {
         if (int rc = ensure_tiles(c, d)) return rc;
-        return forward_tiles<T>(s, c, params, bounds, ckpt_ptr, zero, chunk);
+        return forward_tiles<T>(s, c, params, bounds, ckpt_ptr, zero, norm, chunk);
     }
     const Plan& pl = plan_now(c);
     void* cur = s->data;
@@ -1296,7 +1299,7 @@ int adjoint_impl(vqe_state* psi, vqe_state* lam, const vqe_circuit* c, const dou
     double* d_g = psi->d_res + 2;
     hipStream_t st = psi->stream;
     const int chunk = o && o->chunk_passes > 0 ? o->chunk_passes : 0;
-    rc = forward<T>(psi, c, params, bounds, ck, true, chunk);
+    rc = forward<T>(psi, c, params, bounds, ck, true, h->norm1, chunk);
     if (rc) return rc;
     rc = apply_h<T>(psi, lam->data, h, d_e);
     if (rc) return rc;
@@ -1386,7 +1389,7 @@ int param_shift_impl(vqe_state* psi, const vqe_circuit* c, const double* params,
     for (size_t e = n_eval; e-- > 0;) {
         std::copy(params, params + P, th.begin());
         if (e > 0) th[shifts[e - 1].first] += shifts[e - 1].second;
-        rc = forward<T>(psi, c, th.data(), nob, nock, true);
+        rc = forward<T>(psi, c, th.data(), nob, nock, true, 1.0);
         if (rc) return rc;
         rc = mode == VQE_EXPECT_PER_TERM ? energy_per_term<T>(psi, h, e * per)
                                          : energy_grouped<T>(psi, h, psi->d_part, psi->d_res + e * per);
@@ -1669,11 +1672,13 @@ int ensure_batch(const vqe_circuit* cc, int d, bool ckpt = false) {
 
 // The image of a batch plan with the numbers of one evaluation, to dst.
 template <typename T>
-void fill_batch_image(const vqe_circuit* c, const BatchPlan& bp, const double* params, std::vector<HalfAngle>& h, char* dst) {
+void fill_batch_image(const vqe_circuit* c, const BatchPlan& bp, const double* params, double norm,
+                      std::vector<HalfAngle>& h, char* dst) {
     half_angles(c, params, h);
+    const double limit = turn_limit(sizeof(T) == 8, norm);
     std::memcpy(dst, bp.image.data(), bp.image.size());
     for (size_t k = 0; k < bp.prog.size(); ++k)
-        fill_tile_table<T>(bp.prog[k].table, c->gates, h.data(), (int)(k & 1), (T*)(dst + bp.stream_off[k]));
+        fill_tile_table<T>(bp.prog[k].table, c->gates, h.data(), limit, (int)(k & 1), (T*)(dst + bp.stream_off[k]));
 }
 
 // Descriptor of one small evaluation; image, out and part are device addresses.
@@ -1760,7 +1765,7 @@ int batch_impl(vqe_batch* b, size_t n_items, const vqe_batch_item* items) {
         const vqe_circuit* c = items[i].circuit;
         const BatchPlan& bp = c->batch[dt][0];
         ((BatchDesc<T>*)h)[i] = small_desc<T>(c, bp, items[i].hamiltonian, d + img, out + o, (double*)(d + o_out) + part);
-        fill_batch_image<T>(c, bp, items[i].params, ha, h + img);
+        fill_batch_image<T>(c, bp, items[i].params, items[i].hamiltonian->norm1, ha, h + img);
         img += bp.image.size();
         o += 2 + bp.slot_param.size();
         part += 8 * bp.slot_param.size();
@@ -1809,7 +1814,7 @@ int small_grad(vqe_state* psi, vqe_state* lam, const vqe_circuit* c, const doubl
     std::memcpy(psi->h_mats, &d, sizeof(d));
     if (!ck.empty()) std::memcpy((char*)psi->h_mats + o_ck, ck.data(), ck.size() * sizeof(BatchCkpt));
     std::vector<HalfAngle> ha;
-    fill_batch_image<T>(c, bp, params, ha, (char*)psi->h_mats + o_img);
+    fill_batch_image<T>(c, bp, params, h->norm1, ha, (char*)psi->h_mats + o_img);
     VQE_HIP(hipMemcpyAsync(psi->d_mats, psi->h_mats, bytes, hipMemcpyHostToDevice, psi->stream));
     {
         ProfScope ps(VQE_KERNEL_WINDOW_REV, 2.0 * (double)psi->bytes, psi->stream);
@@ -1937,7 +1942,7 @@ int mid_impl(vqe_batch* b, const vqe_batch_item* items, const std::vector<size_t
         const vqe_batch_item& it = items[idx[k]];
         const vqe_circuit* c = it.circuit;
         const BatchPlan& bp = c->batch[dt][0];
-        fill_batch_image<T>(c, bp, it.params, ha, h + o_img + img_off[k]);
+        fill_batch_image<T>(c, bp, it.params, it.hamiltonian->norm1, ha, h + o_img + img_off[k]);
         if (!use_hw[k]) {
             MidHam mh{};
             mh.psi = psi_of(k);
@@ -2356,8 +2361,9 @@ int vqe_apply_circuit(vqe_state* s, const vqe_circuit* c, const double* params, 
     VQE_HIP(hipSetDevice(s->device));
     const std::vector<size_t> nob;
     const std::vector<void*> nock;
-    return s->dtype == VQE_C64 ? forward<float>(s, c, params, nob, nock, false)
-                               : forward<double>(s, c, params, nob, nock, false);
+    // any state whose norm square is in range
+    return s->dtype == VQE_C64 ? forward<float>(s, c, params, nob, nock, false, 0x1p64)
+                               : forward<double>(s, c, params, nob, nock, false, 0x1p512);
     VQE_GUARD_END
 }
 
@@ -2439,6 +2445,7 @@ int vqe_hamiltonian_create(int n_qubits, const uint64_t* x, const uint64_t* z, c
     t64.resize(h->w.size());
     for (size_t t = 0; t < h->w.size(); ++t) {
         if (h->x[t] == 0 && h->z[t] == 0) h->identity += h->w[t];
+        h->norm1 += std::fabs(h->w[t]);
         if (h->groups.empty() || h->groups.back().x != h->x[t]) {
             GroupDesc g{};
             g.x = h->x[t];

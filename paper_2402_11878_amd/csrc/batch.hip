@@ -31,6 +31,8 @@
 // Rows without a branch beat a switch per op (156 against 240 us at 12 qubits:
 // the arms of a switch cost copies of the 64 registers of psi and lam); rows of
 // CNOTs alone leave early (136).
+#include <type_traits>
+
 #include "vqe_internal.h"
 
 namespace vqe {
@@ -108,6 +110,34 @@ __device__ __forceinline__ double row_sums(const double (&g)[4]) {
 }
 
 // ------------------------------------------------------------------ ops on 16 register entries
+__device__ __forceinline__ void swap_regs(float& a, float& b) { asm("v_swap_b32 %0, %1" : "+v"(a), "+v"(b)); }
+__device__ __forceinline__ void swap_regs(double& a, double& b) {
+    unsigned long long x = __double_as_longlong(a), y = __double_as_longlong(b);
+    unsigned xl = (unsigned)x, xh = (unsigned)(x >> 32), yl = (unsigned)y, yh = (unsigned)(y >> 32);
+    asm("v_swap_b32 %0, %1" : "+v"(xl), "+v"(yl));
+    asm("v_swap_b32 %0, %1" : "+v"(xh), "+v"(yh));
+    a = __longlong_as_double((long long)(((unsigned long long)xh << 32) | xl));
+    b = __longlong_as_double((long long)(((unsigned long long)yh << 32) | yl));
+}
+
+// RY by half a turn, (x, y) -> (-y, x); X: RX, (-i y, -i x).  Only rotations
+// beyond turn_limit() take it.
+template <int B, bool X, int NV, typename T>
+__device__ __forceinline__ void half_turn(T (&re)[NV][kN], T (&im)[NV][kN]) {
+#pragma unroll
+    for (int v = 0; v < NV; ++v)
+#pragma unroll
+        for (int p = 0; p < kN; ++p) {
+            if (p & (1 << B)) continue;
+            const int q = p | (1 << B);
+            swap_regs(re[v][p], X ? im[v][q] : re[v][q]);
+            swap_regs(im[v][p], X ? re[v][q] : im[v][q]);
+            im[v][p] = -im[v][p];
+            if (X) im[v][q] = -im[v][q];
+            else re[v][p] = -re[v][p];
+        }
+}
+
 template <int B, int NV, typename T>
 __device__ __forceinline__ void rot_y(T (&re)[NV][kN], T (&im)[NV][kN], T t) {
 #pragma unroll
@@ -124,9 +154,10 @@ __device__ __forceinline__ void rot_y(T (&re)[NV][kN], T (&im)[NV][kN], T t) {
         }
 }
 
-// x - i t y, y - i t x
+// x - i t y, y - i t x; half: after a half turn
 template <int B, int NV, typename T>
-__device__ __forceinline__ void rot_x(T (&re)[NV][kN], T (&im)[NV][kN], T t) {
+__device__ __forceinline__ void rot_x(T (&re)[NV][kN], T (&im)[NV][kN], T t, bool half) {
+    if (__builtin_expect(half, 0)) half_turn<B, true, NV, T>(re, im);
 #pragma unroll
     for (int v = 0; v < NV; ++v)
 #pragma unroll
@@ -155,16 +186,6 @@ __device__ __forceinline__ void mat_r2(T (&re)[NV][kN], T (&im)[NV][kN], T ca, T
             re[v][q] = cc * ar + cd * br;
             im[v][q] = cc * ai + cd * bi;
         }
-}
-
-__device__ __forceinline__ void swap_regs(float& a, float& b) { asm("v_swap_b32 %0, %1" : "+v"(a), "+v"(b)); }
-__device__ __forceinline__ void swap_regs(double& a, double& b) {
-    unsigned long long x = __double_as_longlong(a), y = __double_as_longlong(b);
-    unsigned xl = (unsigned)x, xh = (unsigned)(x >> 32), yl = (unsigned)y, yh = (unsigned)(y >> 32);
-    asm("v_swap_b32 %0, %1" : "+v"(xl), "+v"(yl));
-    asm("v_swap_b32 %0, %1" : "+v"(xh), "+v"(yh));
-    a = __longlong_as_double((long long)(((unsigned long long)xh << 32) | xl));
-    b = __longlong_as_double((long long)(((unsigned long long)yh << 32) | yl));
 }
 
 // Swaps the entries with target bit Tg clear and set where bit C is set (C = Tg: all).
@@ -376,75 +397,87 @@ __device__ __forceinline__ void run_program(char* psi, char* lam, char* blk, uin
                 if ((lane & 15) == 0 && ((mask >> row) & 1)) emit(slot + ((off >> (8 * row)) & 255u), r);
             };
             if (st.kind == PK_ROWS) {
-                T re[NV][kN], im[NV][kN];
-                load(re, im);
-                for (uint32_t i = 0; i < st.n_ops; ++i) {
-                    const ProgRow<T>& o = *(const ProgRow<T>*)(cur + 16 + i * sizeof(ProgRow<T>));
-                    const uint32_t fl = uni(o.flags);
-                    auto turns = [&] {
-                        rot_y<0, NV, T>(re, im, o.t[0]);
-                        rot_y<1, NV, T>(re, im, o.t[1]);
-                        rot_y<2, NV, T>(re, im, o.t[2]);
-                        rot_y<3, NV, T>(re, im, o.t[3]);
-                    };
-                    auto phases = [&] {
-#pragma unroll
-                        for (int p = 0; p < kN; ++p) {
-                            const T pr = o.ph[2 * p], pi = o.ph[2 * p + 1];
-#pragma unroll
-                            for (int v = 0; v < NV; ++v) {
-                                const T ar = re[v][p], ai = im[v][p];
-                                re[v][p] = pr * ar - pi * ai;
-                                im[v][p] = pr * ai + pi * ar;
+                // HALF: with the half turns that the rows' flags ask for; a loop of its own, as a branch
+                // in the other costs it registers (12 qubits, complex128: 201 us per call, 188 with two loops)
+                auto rows = [&](auto HALF) {
+                    T re[NV][kN], im[NV][kN];
+                    load(re, im);
+                    for (uint32_t i = 0; i < st.n_ops; ++i) {
+                        const ProgRow<T>& o = *(const ProgRow<T>*)(cur + 16 + i * sizeof(ProgRow<T>));
+                        const uint32_t fl = uni(o.flags);
+                        auto turns = [&] {
+                            if constexpr (decltype(HALF)::value) {
+                                if (fl & 0x10000u) half_turn<0, false, NV, T>(re, im);
+                                if (fl & 0x20000u) half_turn<1, false, NV, T>(re, im);
+                                if (fl & 0x40000u) half_turn<2, false, NV, T>(re, im);
+                                if (fl & 0x80000u) half_turn<3, false, NV, T>(re, im);
                             }
-                        }
-                    };
-                    if constexpr (NV == 1) {
-                        turns();
-                        phases();
-                        cnot_if<0, NV, T>(fl & 1, re, im);
-                        cnot_if<1, NV, T>(fl & 2, re, im);
-                        cnot_if<2, NV, T>(fl & 4, re, im);
-                    } else {
-                        cnot_if<2, NV, T>(fl & 4, re, im);
-                        cnot_if<1, NV, T>(fl & 2, re, im);
-                        cnot_if<0, NV, T>(fl & 1, re, im);
-                        if (!(fl & 16)) continue;  // CNOTs alone
-                        phases();
-                        // Z: d = Im(conj(lam) psi) once; per bit the sum of differences, the sums passed on
-                        double gz[4];
-                        {
-                            T d[kN];
+                            rot_y<0, NV, T>(re, im, o.t[0]);
+                            rot_y<1, NV, T>(re, im, o.t[1]);
+                            rot_y<2, NV, T>(re, im, o.t[2]);
+                            rot_y<3, NV, T>(re, im, o.t[3]);
+                        };
+                        auto phases = [&] {
 #pragma unroll
-                            for (int p = 0; p < kN; ++p) d[p] = re[1][p] * im[0][p] - im[1][p] * re[0][p];
+                            for (int p = 0; p < kN; ++p) {
+                                const T pr = o.ph[2 * p], pi = o.ph[2 * p + 1];
 #pragma unroll
-                            for (int q = 0; q < kProgBits; ++q) {
-                                T acc = 0;
-#pragma unroll
-                                for (int p = 0; p < (kN >> (q + 1)); ++p) {
-                                    acc += d[2 * p] - d[2 * p + 1];
-                                    d[p] = d[2 * p] + d[2 * p + 1];
+                                for (int v = 0; v < NV; ++v) {
+                                    const T ar = re[v][p], ai = im[v][p];
+                                    re[v][p] = pr * ar - pi * ai;
+                                    im[v][p] = pr * ai + pi * ar;
                                 }
-                                gz[q] = (double)acc;
                             }
+                        };
+                        if constexpr (NV == 1) {
+                            turns();
+                            phases();
+                            cnot_if<0, NV, T>(fl & 1, re, im);
+                            cnot_if<1, NV, T>(fl & 2, re, im);
+                            cnot_if<2, NV, T>(fl & 4, re, im);
+                        } else {
+                            cnot_if<2, NV, T>(fl & 4, re, im);
+                            cnot_if<1, NV, T>(fl & 2, re, im);
+                            cnot_if<0, NV, T>(fl & 1, re, im);
+                            if (!(fl & 16)) continue;  // CNOTs alone
+                            phases();
+                            // Z: d = Im(conj(lam) psi) once; per bit the sum of differences, the sums passed on
+                            double gz[4];
+                            {
+                                T d[kN];
+#pragma unroll
+                                for (int p = 0; p < kN; ++p) d[p] = re[1][p] * im[0][p] - im[1][p] * re[0][p];
+#pragma unroll
+                                for (int q = 0; q < kProgBits; ++q) {
+                                    T acc = 0;
+#pragma unroll
+                                    for (int p = 0; p < (kN >> (q + 1)); ++p) {
+                                        acc += d[2 * p] - d[2 * p + 1];
+                                        d[p] = d[2 * p] + d[2 * p + 1];
+                                    }
+                                    gz[q] = (double)acc;
+                                }
+                            }
+                            const double gy[4] = {(double)grad_xy<0, true, T>(re, im), (double)grad_xy<1, true, T>(re, im),
+                                                  (double)grad_xy<2, true, T>(re, im), (double)grad_xy<3, true, T>(re, im)};
+                            turns();
+                            emit4(gz, (fl >> 8) & 15u, o.z_slot, o.z_off);
+                            emit4(gy, (fl >> 12) & 15u, o.y_slot, o.y_off);
                         }
-                        const double gy[4] = {(double)grad_xy<0, true, T>(re, im), (double)grad_xy<1, true, T>(re, im),
-                                              (double)grad_xy<2, true, T>(re, im), (double)grad_xy<3, true, T>(re, im)};
-                        turns();
-                        emit4(gz, (fl >> 8) & 15u, o.z_slot, o.z_off);
-                        emit4(gy, (fl >> 12) & 15u, o.y_slot, o.y_off);
                     }
-                }
-                save(re, im);
+                    save(re, im);
+                };
+                if (__builtin_expect(uni(((const ProgRow<T>*)(cur + 16))->flags) & kRowHalf, 0)) rows(std::true_type{});
+                else rows(std::false_type{});
             } else {
                 T re[NV][kN], im[NV][kN];
                 load(re, im);
                 for (uint32_t i = 0; i < st.n_ops; ++i) {
                     const ProgMisc<T>& o = *(const ProgMisc<T>*)(cur + 16 + i * sizeof(ProgMisc<T>));
-                    const uint32_t code = uni(o.code), a = code >> 8;
+                    const uint32_t code = uni(o.code), a = (code >> 8) & 0xffu;
                     switch (code & 255u) {
                         case PM_ROTX:
-                            switch (a) { VQE_BITS((rot_x<B, NV, T>(re, im, o.t[0]))) }
+                            switch (a) { VQE_BITS((rot_x<B, NV, T>(re, im, o.t[0], code >> 31))) }
                             break;
                         case PM_R2:
                             switch (a) { VQE_BITS((mat_r2<B, NV, T>(re, im, o.t[0], o.t[1], o.t[2], o.t[3]))) }

@@ -70,8 +70,16 @@ struct Builder : StageScheduler {
             const Rec& r = recs[i];
             const uint32_t where = s.off + 16 + (at + i) * size, num = where + hd;
             std::copy(r.w, r.w + hd / 4, &prog->stream[where / 4]);
-            for (int k = 0; k < 4; ++k)
-                if (r.num[k] >= 0) out->entries[r.num[k]].off = num / scalar() + (uint32_t)k;
+            for (int k = 0; k < 4; ++k) {
+                if (r.num[k] < 0) continue;
+                TileEntry& e = out->entries[r.num[k]];
+                e.off = num / scalar() + (uint32_t)k;
+                if (e.kind != TF_ROT) continue;
+                e.flag_word = where / 4;
+                e.flag_bit = cur.kind == PK_ROWS ? 16 + (uint32_t)k : 31;
+                e.any_word = (s.off + 16) / 4;
+                e.any = cur.kind == PK_ROWS ? kRowHalf : 0;
+            }
             if (cur.kind != PK_ROWS) continue;
             if (r.phase >= 0) out->entries[r.phase].off = num / scalar() + 4;
             for (uint32_t p = 0; p < 16; ++p) {  // no phases: ones

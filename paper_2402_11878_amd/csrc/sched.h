@@ -72,11 +72,14 @@ inline void stage_pattern(const Gate& g, const StageOp& k, uint32_t& mask, uint3
     mask = A | B;
 }
 
+// Rotations that may wait for their factors at a time (turn_limit()).
+inline int max_pending(bool dbl) { return dbl ? 14 : 4; }
+
 struct StageScheduler {
     bool dbl = false;
     const std::vector<Gate>* gates = nullptr;
     TileKernel* out = nullptr;
-    std::vector<int> pending;  // rotations whose factor c is still to be applied
+    std::vector<int> pending;  // rotations whose factor is still to be applied
 
     virtual ~StageScheduler() = default;
     virtual void rot(const StageOp& k) = 0;                          // unnormalised RY / RX
@@ -131,7 +134,7 @@ struct StageScheduler {
     // ready, then rotations, diagonal gates last (so that they merge).
     // Gradient terms read normalised vectors (pending factors applied first).
     void stage(std::vector<StageOp> ops) {
-        const size_t max_pending = dbl ? 14 : 4;  // each factor may be as small as 2^-60 (2^-26)
+        const size_t most = (size_t)max_pending(dbl);
         auto ready = [&](size_t i) {
             for (size_t j = 0; j < i; ++j)
                 if (!commute(ops[j], ops[i])) return false;
@@ -156,7 +159,7 @@ struct StageScheduler {
             }
             if (ops.empty()) break;
             for (size_t i = 0; i < ops.size();) {
-                if (is_rot(ops[i].kind) && pending.size() < max_pending && ready(i)) {
+                if (is_rot(ops[i].kind) && pending.size() < most && ready(i)) {
                     rot(ops[i]);
                     ops.erase(ops.begin() + (long)i);
                     progress = true;

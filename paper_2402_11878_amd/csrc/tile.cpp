@@ -23,7 +23,8 @@
 //   * RY and RX run unnormalised, R = c [[1, -t], [t, 1]] with t = tan(a/2) and
 //     c = cos(a/2): two fused multiply-adds per amplitude instead of four
 //     operations (three as shears); the factors c wait until the next
-//     multiplication of the whole vector;
+//     multiplication of the whole vector; near half a turn the half turn is made
+//     first, by moves behind a branch on the table (the same for the whole launch);
 //   * all diagonal gates (RZ, CZ) of a stage that can stand together are one
 //     multiplication by a phase from a host-made table of 2^m entries, which
 //     also carries the pending factors c;
@@ -34,6 +35,8 @@
 //     six values per thread wait and one lane ends up with each total.
 #include <algorithm>
 #include <cmath>
+#include <cstring>
+#include <map>
 #include <sstream>
 
 #include "sched.h"
@@ -63,29 +66,70 @@ struct Gen : StageScheduler {
     std::string I(int v, int p) const { return "i" + std::to_string(v) + "_" + std::to_string(loc[p]); }
 
     // ---- ops
+    // c [[1, -t], [t, 1]] (RX: -i t for both signs), after a half turn if the
+    // gate's flag is set.  Rotations of different bits are emitted together,
+    // with one branch around all their half turns.
+    struct Turn {
+        StageOp k;
+        uint32_t off, flag;
+    };
+    std::vector<Turn> turns;
     void rot(const StageOp& k) override {
-        const uint32_t off = gate_entry(TF_ROT, k.gate, 1);
-        o << "  { const T t = tab[" << off << "];\n";
-        const int b = 1 << k.bit[0];
-        for (int p = 0; p < N; ++p) {
-            if (p & b) continue;
-            const int q = p | b;
-            for (int v = 0; v < NV; ++v) {
-                o << "    { const T xr = " << R(v, p) << ", xi = " << I(v, p) << ", yr = " << R(v, q) << ", yi = "
-                  << I(v, q) << ";\n      ";
-                if (k.kind == K_ROTY)
-                    o << R(v, p) << " = xr - t * yr; " << I(v, p) << " = xi - t * yi; " << R(v, q)
-                      << " = yr + t * xr; " << I(v, q) << " = yi + t * xi; }\n";
-                else  // [[1, -i t], [-i t, 1]]
-                    o << R(v, p) << " = xr + t * yi; " << I(v, p) << " = xi - t * yr; " << R(v, q)
-                      << " = yr + t * xi; " << I(v, q) << " = yi - t * xr; }\n";
+        for (const Turn& t : turns)
+            if (t.k.bit[0] == k.bit[0]) {
+                turn();
+                break;
             }
+        const uint32_t off = gate_entry(TF_ROT, k.gate, 1), flag = out->n_flags++;
+        out->entries.back().flag_word = flag / 32;
+        out->entries.back().flag_bit = flag % 32;
+        turns.push_back(Turn{k, off, flag});
+        pending.push_back(k.gate);
+    }
+    template <typename F>
+    void pairs(const StageOp& k, F emit) {
+        const int b = 1 << k.bit[0];
+        for (int p = 0; p < N; ++p)
+            if (!(p & b))
+                for (int v = 0; v < NV; ++v) emit(R(v, p), I(v, p), R(v, p | b), I(v, p | b));
+    }
+    void turn() {
+        if (turns.empty()) return;
+        using S = const std::string&;
+        std::map<uint32_t, uint32_t> mask;  // flag word -> bits
+        for (const Turn& t : turns) mask[t.flag / 32] |= 1u << (t.flag % 32);
+        o << "  if (__builtin_expect(0";  // rare: out of the line of the instruction cache
+        for (const auto& [w, m] : mask) o << " | flags(half" << w << ", " << m << "u)";
+        o << ", 0)) {\n";
+        for (const Turn& t : turns) {
+            o << "   if (flags(half" << t.flag / 32 << ", " << (1u << (t.flag % 32)) << "u)) {\n";
+            pairs(t.k, [&](S xr, S xi, S yr, S yi) {
+                if (t.k.kind == K_ROTY)
+                    o << "    half_turn(" << xr << ", " << yr << "); half_turn(" << xi << ", " << yi << ");\n";
+                else
+                    o << "    half_turn(" << yi << ", " << xr << "); half_turn(" << xi << ", " << yr << ");\n";
+            });
+            o << "   }\n";
         }
         o << "  }\n";
-        pending.push_back(k.gate);
+        for (const Turn& t : turns) {
+            o << "  { const T t = tab[" << t.off << "];\n";
+            pairs(t.k, [&](S xr, S xi, S yr, S yi) {
+                o << "    { const T xr = " << xr << ", xi = " << xi << ", yr = " << yr << ", yi = " << yi << ";\n      ";
+                if (t.k.kind == K_ROTY)
+                    o << xr << " = xr - t * yr; " << xi << " = xi - t * yi; " << yr << " = yr + t * xr; " << yi
+                      << " = yi + t * xi; }\n";
+                else
+                    o << xr << " = xr + t * yi; " << xi << " = xi - t * yr; " << yr << " = yr + t * xi; " << yi
+                      << " = yi - t * xr; }\n";
+            });
+            o << "  }\n";
+        }
+        turns.clear();
     }
 
     void scale_by(uint32_t off) override {
+        turn();
         o << "  { const T s = tab[" << off << "];\n";
         for (int p = 0; p < N; ++p)
             for (int v = 0; v < NV; ++v) o << "    " << R(v, p) << " *= s; " << I(v, p) << " *= s;\n";
@@ -93,6 +137,7 @@ struct Gen : StageScheduler {
     }
 
     void phase_by(uint32_t off, uint32_t mask) override {
+        turn();
         const int m = __builtin_popcount(mask);
         for (uint32_t idx = 0; idx < (1u << m); ++idx) {
             o << "  { const T pr = tab[" << off + 2 * idx << "], pi = tab[" << off + 2 * idx + 1 << "];\n";
@@ -111,6 +156,7 @@ struct Gen : StageScheduler {
 
     // A real 2x2 matrix between two patterns (H; excitations).
     void matrix(const StageOp& k) override {
+        turn();
         const uint32_t off = gate_entry(TF_R2, k.gate, 4);
         o << "  { const T ca = tab[" << off << "], cb = tab[" << off + 1 << "], cc = tab[" << off + 2 << "], cd = tab["
           << off + 3 << "];\n";
@@ -129,6 +175,7 @@ struct Gen : StageScheduler {
     }
 
     void rename(const StageOp& k) override {
+        turn();
         const int c = k.kind == K_CNOT ? 1 << k.bit[0] : 0, t = 1 << (k.kind == K_CNOT ? k.bit[1] : k.bit[0]);
         for (int p = 0; p < N; ++p)
             if ((p & c) == c && !(p & t)) std::swap(loc[p], loc[p | t]);
@@ -198,6 +245,7 @@ struct Gen : StageScheduler {
     }
 
     void gradient(const StageOp& k) override {
+        turn();
         const Gate& g = (*gates)[k.gate];
         uint32_t mask, A, B;
         stage_pattern((*gates)[k.gate], k, mask, A, B);
@@ -221,6 +269,7 @@ struct Gen : StageScheduler {
     // Im<lam|Z_b|psi> for the bits of the given RZ gates: d = Im(conj(lam) psi)
     // per entry once, then for each bit the sum of differences, passing the sums on.
     void gradient_z(const std::vector<StageOp>& ops) override {
+        turn();
         std::vector<std::string> d(N);
         for (int p = 0; p < N; ++p) {
             d[p] = fresh();
@@ -399,6 +448,10 @@ std::string prelude(bool dbl) {
     o << "typedef unsigned long long u64;\ntypedef unsigned int u32;\ntypedef " << T << " T;\n"
       << "struct __attribute__((aligned(" << (dbl ? 16 : 8) << "))) V { T x, y; };\n"
       << "struct TileArgs { u64 n_units; u32 pos[" << kTileMaxBits << "]; u32 first; };\n"
+      // not taken out of the loop over cosets, where every test would keep its own registers
+      << "__device__ __forceinline__ u32 flags(u32 w, u32 m) { asm volatile(\"\" : \"+s\"(w)); return w & m; }\n"
+      // (x, y) -> (-y, x)
+      << "__device__ __forceinline__ void half_turn(T& x, T& y) { const T w = x; x = -y; y = w; }\n"
       << "__device__ __forceinline__ void wave_sync() {\n"
       << "  __builtin_amdgcn_fence(__ATOMIC_RELEASE, \"wavefront\");\n  __builtin_amdgcn_wave_barrier();\n"
       << "  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, \"wavefront\");\n}\n"
@@ -426,13 +479,16 @@ std::string prelude(bool dbl) {
     return o.str();
 }
 
-// c = cos(a/2) of an unnormalised rotation, kept away from zero (below the
-// rounding of sin(a/2) ~ 1 in either type), and t = tan(a/2).
-template <typename T>
-void rot_numbers(const HalfAngle& h, double& c, double& t) {
-    const double cmin = sizeof(T) == 8 ? 0x1p-60 : 0x1p-26;
-    c = std::fabs(h.c) < cmin ? std::copysign(cmin, h.c) : h.c;
-    t = h.s / c;
+// Factor f and number t of an unnormalised rotation f [[1, -t], [t, 1]]: f =
+// cos(a/2) and t = tan(a/2), or where that is beyond `limit` (returns true)
+// those of the rotation by a - pi that is left after (x, y) -> (-y, x): f =
+// sin(a/2), t = -cot(a/2).
+bool rot_numbers(const HalfAngle& h, double sign, double limit, double& f, double& t) {
+    const double s = sign * h.s;
+    const bool half = std::fabs(s) > limit * std::fabs(h.c);
+    f = half ? s : h.c;
+    t = half ? -h.c / s : s / h.c;
+    return half;
 }
 
 }  // namespace
@@ -473,6 +529,7 @@ bool tile_kernel(bool dbl, const TileShape& sh, const std::vector<Gate>& gates, 
     g.loc.resize(g.N);
     for (int i = 0; i < g.N; ++i) g.loc[i] = i;
     out = TileKernel();
+    out.n_scalars = kTileFlagBytes / (dbl ? 8 : 4);  // the flags of half turns come first
 
     if (dir == 1) std::reverse(stages.begin(), stages.end());
 
@@ -570,6 +627,7 @@ bool tile_kernel(bool dbl, const TileShape& sh, const std::vector<Gate>& gates, 
             }
         }
         g.stage(std::move(ops));
+        g.turn();
     }
     g.scale();
     go_to(nodes.size() - 1);
@@ -593,6 +651,7 @@ bool tile_kernel(bool dbl, const TileShape& sh, const std::vector<Gate>& gates, 
     g.thread_offset("off_in", Lin);
     g.thread_offset("off_out", Lout);
     for (int c = 0; c < chunks; ++c) o << "  double acc" << c << " = 0.0;\n";
+    for (uint32_t w = 0; 32 * w < out.n_flags; ++w) o << "  const u32 half" << w << " = ((const u32*)tab)[" << w << "];\n";
     // Work order: blocks are dispatched round-robin over the 8 XCDs; XCD x
     // takes the eighth x of the cosets, and gs consecutive blocks of it walk a
     // contiguous run side by side (neighbouring cosets share pages).
@@ -638,22 +697,34 @@ bool tile_kernel(bool dbl, const TileShape& sh, const std::vector<Gate>& gates, 
     return true;
 }
 
+double turn_limit(bool dbl, double norm) {
+    const double room = (dbl ? 1000.0 : 120.0) - std::log2(std::max(norm, 1.0));
+    return std::max(1.0, std::exp2(std::floor(room / max_pending(dbl))));
+}
+
 template <typename T>
-void fill_tile_table(const TileKernel& k, const std::vector<Gate>& gates, const HalfAngle* h, int dir, T* tab) {
+void fill_tile_table(const TileKernel& k, const std::vector<Gate>& gates, const HalfAngle* h, double limit, int dir,
+                     T* tab) {
     const double sign = dir ? -1.0 : 1.0;
-    double c, t;
+    double f, t;
+    if (k.n_flags) std::memset(tab, 0, kTileFlagBytes);
     for (const TileEntry& e : k.entries) {
         T* m = tab + e.off;
         double s = 1.0;
         for (int g : e.rots) {
-            rot_numbers<T>(h[g], c, t);
-            s *= c;
+            rot_numbers(h[g], sign, limit, f, t);
+            s *= f;
         }
         switch (e.kind) {
-            case TF_ROT:
-                rot_numbers<T>(h[e.gate], c, t);
-                m[0] = (T)(sign * t);
+            case TF_ROT: {
+                const bool half = rot_numbers(h[e.gate], sign, limit, f, t);
+                m[0] = (T)t;
+                if (half) {
+                    ((uint32_t*)tab)[e.flag_word] |= 1u << e.flag_bit;
+                    ((uint32_t*)tab)[e.any_word] |= e.any;
+                }
                 break;
+            }
             case TF_SCALE:
                 m[0] = (T)s;
                 break;
@@ -711,7 +782,7 @@ void fill_tile_table(const TileKernel& k, const std::vector<Gate>& gates, const 
     }
 }
 
-template void fill_tile_table<float>(const TileKernel&, const std::vector<Gate>&, const HalfAngle*, int, float*);
-template void fill_tile_table<double>(const TileKernel&, const std::vector<Gate>&, const HalfAngle*, int, double*);
+template void fill_tile_table<float>(const TileKernel&, const std::vector<Gate>&, const HalfAngle*, double, int, float*);
+template void fill_tile_table<double>(const TileKernel&, const std::vector<Gate>&, const HalfAngle*, double, int, double*);
 
 }  // namespace vqe

@@ -379,12 +379,13 @@ inline TileShape tile_shape(bool dbl, int n) {
 }
 constexpr int kTileThreads = 256;
 constexpr int kTileMaxGates = 256;   // gates per pass (code size)
+constexpr int kTileFlagBytes = kTileMaxGates / 8;
 constexpr int kTileMaxPushes = 128;  // gradient terms per pass: two per lane of a wave
 
 // Host numbers of one pass's table: for every entry what to compute from the
 // angles of an evaluation (see fill_tile_table).
 enum TileFill : uint8_t {
-    TF_ROT,    // t of an unnormalised rotation (x - t y, y + t x)
+    TF_ROT,    // t of an unnormalised rotation, and a flag: a half turn (x, y) -> (-y, x) comes first
     TF_PHASE,  // 2^m phases (re, im) of the merged diagonal gates on m bits, times the pending scale
     TF_SCALE,  // the pending scale alone
     TF_R2,     // a real 2x2 matrix (H, excitations): u00 u01 u10 u11
@@ -393,6 +394,8 @@ struct TileEntry {
     TileFill kind;
     uint32_t off;                // first scalar in the pass's table
     int gate = -1;               // TF_ROT, TF_R2
+    uint32_t flag_word = 0, flag_bit = 0;  // TF_ROT: the flag, in the table as 32-bit words
+    uint32_t any_word = 0, any = 0;        // ... and a word with bits to be set if it is
     uint32_t mask = 0;           // TF_PHASE: register bits of its index, ascending
     std::vector<int> diag;       // TF_PHASE: the merged RZ / CZ gates
     std::vector<uint32_t> diag_bits;  // ... and their register bits
@@ -402,6 +405,7 @@ struct TileKernel {
     std::string src;
     std::vector<TileEntry> entries;
     uint32_t n_scalars = 0;
+    uint32_t n_flags = 0;        // flags of half turns at the front of the table
     std::vector<int32_t> lane_param;  // reverse: parameter summed by column l of the partials (-1: none)
 };
 // Generates the kernel of one pass (dir 0 forward, 1 reverse).  Returns false
@@ -413,9 +417,20 @@ const char* tile_kernel_name(int NV, bool dbl);
 struct HalfAngle {
     double c, s;
 };
+// Largest tan(a/2) that an unnormalised rotation may have in an evaluation
+// whose vectors have 2-norms up to `norm`: while max_pending() of them wait for
+// their factors a vector grows by that much to the power of their number, which
+// must leave the type's range (2^120, 2^1000) to the vector itself.  Rotations
+// beyond it, by angles next to an odd multiple of pi, make a half turn by moves
+// first.  Ordinary weights leave 2^27 and more.  With one limit of 2^26 for all,
+// |lam| of 2^24 overflowed in complex64; with one of 4, every sixth angle took the
+// half turn, whose moves cost about what the rotation does: 28 qubits complex64
+// 49.9 ms against 46.7.
+double turn_limit(bool dbl, double norm);
 // Fills the table of one pass for the angles of an evaluation.
 template <typename T>
-void fill_tile_table(const TileKernel& k, const std::vector<Gate>& gates, const HalfAngle* h, int dir, T* tab);
+void fill_tile_table(const TileKernel& k, const std::vector<Gate>& gates, const HalfAngle* h, double limit, int dir,
+                     T* tab);
 
 // ---------------------------------------------------------------- batch programs (program.cpp, batch.hip)
 // A tile of 2^bits amplitudes in LDS, kProgBits of its bits in registers at a
@@ -430,9 +445,12 @@ constexpr int kProgBits = 4;
 //   pairs  excitations, applied where their amplitudes lie in LDS
 //   misc   everything else, one op per record
 enum ProgKind : uint32_t { PK_ROWS, PK_PAIRS, PK_MISC };
+constexpr uint32_t kRowHalf = 1u << 20;
 template <typename T>
 struct ProgRow {
-    uint32_t flags;          // bit k < 3: CNOT of control k, target k + 1; bit 4: it has more; Z mask << 8; Y mask << 12
+    uint32_t flags;          // bit k < 3: CNOT of control k, target k + 1; bit 4: it has more; Z mask << 8; Y mask << 12;
+                             // bit 16 + k: a half turn before the turn of bit k; kRowHalf in a stage's first row: one of its
+                             // rows has such a bit (both filled in with the numbers)
     uint32_t z_slot, z_off;  // gradient slot of the Z term of bit k: z_slot + byte k of z_off
     uint32_t y_slot, y_off;
     uint32_t pad[3];
@@ -441,7 +459,7 @@ struct ProgRow {
 };
 template <typename T>
 struct ProgMisc {
-    uint32_t code;  // type | bit << 8; PM_PERM: control << 2 | target of a CNOT, or 5 x bit: X
+    uint32_t code;  // type | bit << 8; PM_PERM: control << 2 | target of a CNOT, or 5 x bit: X; bit 31: PM_ROTX after a half turn
     uint32_t slot, pad[2];
     T t[4];
 };
