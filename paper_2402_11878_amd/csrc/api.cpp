@@ -783,24 +783,27 @@ int check_params(const vqe_circuit* c, const double* params, size_t n_params, co
 
 std::mutex g_jit_plan_mu;
 
-// True if evaluations of c run the specialised plan (see vqe_set_specialize).
-bool use_specialised(const vqe_circuit* c) {
-    const int mode = jit_mode();
-    return mode == VQE_SPECIALIZE_ALWAYS ||
-           (mode == VQE_SPECIALIZE_AUTO && (c->n >= VQE_SPECIALIZE_AUTO_MIN_QUBITS || c->has_excitation));
+// The kernel form is process-wide and may change at any time: every entry point
+// reads it once (jit_mode()) and hands it down, so that one evaluation keeps to
+// one plan.
+
+// True if an evaluation of c runs the specialised plan (see vqe_set_specialize).
+bool use_specialised(const vqe_circuit* c, int form) {
+    return form == VQE_SPECIALIZE_ALWAYS ||
+           (form == VQE_SPECIALIZE_AUTO && (c->n >= VQE_SPECIALIZE_AUTO_MIN_QUBITS || c->has_excitation));
 }
 
-// VQE_OK if the current kernel form can evaluate c (interpreted kernels have
-// no excitation gates).
-int check_form(const vqe_circuit* c, const char* fn) {
-    if (c->has_excitation && !use_specialised(c)) {
+// VQE_OK if the kernel form can evaluate c (interpreted kernels have no
+// excitation gates).
+int check_form(const vqe_circuit* c, int form, const char* fn) {
+    if (c->has_excitation && !use_specialised(c, form)) {
         set_error(std::string(fn) + ": excitation gates need specialised kernels (vqe_set_specialize)");
         return VQE_ERR_UNSUPPORTED;
     }
     return VQE_OK;
 }
 
-const Plan& plan_now(const vqe_circuit* c) { return c->plan[use_specialised(c) ? 1 : 0]; }
+const Plan& plan_of(const vqe_circuit* c, int form) { return c->plan[use_specialised(c, form) ? 1 : 0]; }
 
 // Physical ops, lane-split bits and slot positions of one specialised pass.
 const std::vector<KOp>& jit_ops(const Plan& pl, size_t pi, int d, bool reverse, int* S, JitArgs* a, int n) {
@@ -858,10 +861,10 @@ int ensure_jit(const vqe_circuit* c, const Plan& cpl, int d) {
     return VQE_OK;
 }
 
-// True if evaluations of c run tile passes: the specialised form from
+// True if an evaluation of c runs tile passes: the specialised form from
 // kTileMinQubits qubits on (below, a tile would leave most of the chip idle;
 // the 7-qubit window passes remain).
-bool use_tiles(const vqe_circuit* c) { return use_specialised(c) && c->n >= kTileMinQubits; }
+bool use_tiles(const vqe_circuit* c, int form) { return use_specialised(c, form) && c->n >= kTileMinQubits; }
 
 // Plans the tile passes of c for dtype index d, generates their kernels and
 // loads them on the current device (once).
@@ -1064,14 +1067,14 @@ int forward_tiles(vqe_state* s, const vqe_circuit* c, const double* params, cons
 // ckpt_ptr[k] receives the state at boundary bounds[k] (pass index + 1); norm:
 // bound on the 2-norms of the vectors of this evaluation (turn_limit()).
 template <typename T>
-int forward(vqe_state* s, const vqe_circuit* c, const double* params, const std::vector<size_t>& bounds,
+int forward(vqe_state* s, const vqe_circuit* c, int form, const double* params, const std::vector<size_t>& bounds,
             const std::vector<void*>& ckpt_ptr, bool zero, double norm, int chunk = 0) {
     const int d = sizeof(T) == 8 ? 1 : 0;
-    if (use_tiles(c)) {
+    if (use_tiles(c, form)) {
         if (int rc = ensure_tiles(c, d)) return rc;
         return forward_tiles<T>(s, c, params, bounds, ckpt_ptr, zero, norm, chunk);
     }
-    const Plan& pl = plan_now(c);
+    const Plan& pl = plan_of(c, form);
     void* cur = s->data;
     const Mat2<T>* mats = nullptr;
     if (pl.jit) {
@@ -1274,12 +1277,12 @@ int reverse_tiles(vqe_state* psi, vqe_state* lam, const TilePlan& tp, const std:
 }
 
 template <typename T>
-int adjoint_impl(vqe_state* psi, vqe_state* lam, const vqe_circuit* c, const double* params,
+int adjoint_impl(vqe_state* psi, vqe_state* lam, const vqe_circuit* c, int form, const double* params,
                  const vqe_hamiltonian* h, const vqe_grad_opts* o, double* energy, double* grad) {
     const int d = sizeof(T) == 8 ? 1 : 0;
-    const bool tiles = use_tiles(c);
-    if (int rc0 = tiles ? ensure_tiles(c, d) : upload_plan(plan_now(c))) return rc0;
-    const Plan& pl = plan_now(c);
+    const bool tiles = use_tiles(c, form);
+    const Plan& pl = plan_of(c, form);
+    if (int rc0 = tiles ? ensure_tiles(c, d) : upload_plan(pl)) return rc0;
     const TilePlan& tp = c->tile[d];
     const size_t P = tiles ? tp.passes.size() : pl.passes.size();
     std::vector<size_t> bounds;
@@ -1299,7 +1302,7 @@ int adjoint_impl(vqe_state* psi, vqe_state* lam, const vqe_circuit* c, const dou
     double* d_g = psi->d_res + 2;
     hipStream_t st = psi->stream;
     const int chunk = o && o->chunk_passes > 0 ? o->chunk_passes : 0;
-    rc = forward<T>(psi, c, params, bounds, ck, true, h->norm1, chunk);
+    rc = forward<T>(psi, c, form, params, bounds, ck, true, h->norm1, chunk);
     if (rc) return rc;
     rc = apply_h<T>(psi, lam->data, h, d_e);
     if (rc) return rc;
@@ -1359,7 +1362,7 @@ int adjoint_impl(vqe_state* psi, vqe_state* lam, const vqe_circuit* c, const dou
 }
 
 template <typename T>
-int param_shift_impl(vqe_state* psi, const vqe_circuit* c, const double* params, const vqe_hamiltonian* h,
+int param_shift_impl(vqe_state* psi, const vqe_circuit* c, int form, const double* params, const vqe_hamiltonian* h,
                      int mode, double* energy, double* grad) {
     // Shift rule per parameter: two runs at +-pi/2 for the rotations (their
     // generators square to one); four runs at +-pi/2 and +-3pi/2 for the
@@ -1389,7 +1392,7 @@ int param_shift_impl(vqe_state* psi, const vqe_circuit* c, const double* params,
     for (size_t e = n_eval; e-- > 0;) {
         std::copy(params, params + P, th.begin());
         if (e > 0) th[shifts[e - 1].first] += shifts[e - 1].second;
-        rc = forward<T>(psi, c, th.data(), nob, nock, true, 1.0);
+        rc = forward<T>(psi, c, form, th.data(), nob, nock, true, 1.0);
         if (rc) return rc;
         rc = mode == VQE_EXPECT_PER_TERM ? energy_per_term<T>(psi, h, e * per)
                                          : energy_grouped<T>(psi, h, psi->d_part, psi->d_res + e * per);
@@ -2318,7 +2321,7 @@ int vqe_circuit_info(const vqe_circuit* c, size_t* n_params, size_t* n_passes) {
         return VQE_ERR_ARG;
     }
     if (n_params) *n_params = c->n_params;
-    if (n_passes) *n_passes = plan_now(c).passes.size();
+    if (n_passes) *n_passes = plan_of(c, jit_mode()).passes.size();
     return VQE_OK;
 }
 
@@ -2328,8 +2331,9 @@ int vqe_circuit_pass(const vqe_circuit* c, int dtype, size_t pass, int* window, 
         set_error("vqe_circuit_pass: null circuit or bad dtype");
         return VQE_ERR_ARG;
     }
-    if (int rc = check_form(c, "vqe_circuit_pass")) return rc;
-    const Plan& pl = plan_now(c);
+    const int form = jit_mode();
+    if (int rc = check_form(c, form, "vqe_circuit_pass")) return rc;
+    const Plan& pl = plan_of(c, form);
     if (pass >= pl.passes.size()) {
         set_error("vqe_circuit_pass: pass index out of range");
         return VQE_ERR_ARG;
@@ -2357,13 +2361,14 @@ int vqe_apply_circuit(vqe_state* s, const vqe_circuit* c, const double* params, 
         return VQE_ERR_ARG;
     }
     if (int rc = check_params(c, params, n_params, "vqe_apply_circuit")) return rc;
-    if (int rc = check_form(c, "vqe_apply_circuit")) return rc;
+    const int form = jit_mode();
+    if (int rc = check_form(c, form, "vqe_apply_circuit")) return rc;
     VQE_HIP(hipSetDevice(s->device));
     const std::vector<size_t> nob;
     const std::vector<void*> nock;
     // any state whose norm square is in range
-    return s->dtype == VQE_C64 ? forward<float>(s, c, params, nob, nock, false, 0x1p64)
-                               : forward<double>(s, c, params, nob, nock, false, 0x1p512);
+    return s->dtype == VQE_C64 ? forward<float>(s, c, form, params, nob, nock, false, 0x1p64)
+                               : forward<double>(s, c, form, params, nob, nock, false, 0x1p512);
     VQE_GUARD_END
 }
 
@@ -2566,7 +2571,8 @@ int vqe_energy_grad(vqe_state* psi, vqe_state* lam, const vqe_circuit* c, const 
         return VQE_ERR_ARG;
     }
     if (int rc = check_params(c, params, n_params, "vqe_energy_grad")) return rc;
-    if (int rc = check_form(c, "vqe_energy_grad")) return rc;
+    const int form = jit_mode();
+    if (int rc = check_form(c, form, "vqe_energy_grad")) return rc;
     const int method = opts ? opts->method : VQE_GRAD_ADJOINT;
     VQE_HIP(hipSetDevice(psi->device));
     if (int rc = upload_hamiltonian(h)) return rc;
@@ -2577,8 +2583,8 @@ int vqe_energy_grad(vqe_state* psi, vqe_state* lam, const vqe_circuit* c, const 
             set_error("vqe_energy_grad: unknown expect_mode");
             return VQE_ERR_ARG;
         }
-        return psi->dtype == VQE_C64 ? param_shift_impl<float>(psi, c, params, h, mode, energy, grad)
-                                     : param_shift_impl<double>(psi, c, params, h, mode, energy, grad);
+        return psi->dtype == VQE_C64 ? param_shift_impl<float>(psi, c, form, params, h, mode, energy, grad)
+                                     : param_shift_impl<double>(psi, c, form, params, h, mode, energy, grad);
     }
     if (method != VQE_GRAD_ADJOINT) {
         set_error("vqe_energy_grad: unknown method");
@@ -2616,7 +2622,7 @@ int vqe_energy_grad(vqe_state* psi, vqe_state* lam, const vqe_circuit* c, const 
     // A state that fits LDS runs in one launch, whatever its gates, unless a
     // kernel form was chosen.  12 qubits, 4 layers, complex128: 26 launches of 1 to 8
     // blocks 408 us, against one of one block 188 us.
-    if (jit_mode() == VQE_SPECIALIZE_AUTO && psi->n <= max_small(psi->dtype))
+    if (form == VQE_SPECIALIZE_AUTO && psi->n <= max_small(psi->dtype))
         return psi->dtype == VQE_C64 ? small_grad<float>(psi, lam, c, params, h, opts, energy, grad)
                                      : small_grad<double>(psi, lam, c, params, h, opts, energy, grad);
     // Above that, where specialised kernels are not worth compiling, the batch
@@ -2625,7 +2631,7 @@ int vqe_energy_grad(vqe_state* psi, vqe_state* lam, const vqe_circuit* c, const 
     // window passes against these: complex64 14 qubits 478 / 1247 us, 209 / 498;
     // 19 qubits 666 / 1784, 326 / 782; complex128 13 qubits 441 / 1179, 249 / 626; 19
     // qubits 752 / 1963, 405 / 1010.
-    if (jit_mode() == VQE_SPECIALIZE_AUTO && psi->n < VQE_SPECIALIZE_AUTO_MIN_QUBITS && !use_tiles(c)) {
+    if (form == VQE_SPECIALIZE_AUTO && psi->n < VQE_SPECIALIZE_AUTO_MIN_QUBITS && !use_tiles(c, form)) {
         if (!psi->mid) {
             psi->mid = new vqe_batch();
             psi->mid->dtype = psi->dtype;
@@ -2636,8 +2642,8 @@ int vqe_energy_grad(vqe_state* psi, vqe_state* lam, const vqe_circuit* c, const 
         const MidOwn own{psi, lam, opts};
         return psi->dtype == VQE_C64 ? mid_impl<float>(psi->mid, &it, {0}, &own) : mid_impl<double>(psi->mid, &it, {0}, &own);
     }
-    return psi->dtype == VQE_C64 ? adjoint_impl<float>(psi, lam, c, params, h, opts, energy, grad)
-                                 : adjoint_impl<double>(psi, lam, c, params, h, opts, energy, grad);
+    return psi->dtype == VQE_C64 ? adjoint_impl<float>(psi, lam, c, form, params, h, opts, energy, grad)
+                                 : adjoint_impl<double>(psi, lam, c, form, params, h, opts, energy, grad);
     VQE_GUARD_END
 }
 
@@ -2726,9 +2732,10 @@ int vqe_circuit_prepare(const vqe_circuit* c, int dtype) {
         set_error("vqe_circuit_prepare: null circuit or bad dtype");
         return VQE_ERR_ARG;
     }
-    if (int rc = check_form(c, "vqe_circuit_prepare")) return rc;
-    if (use_tiles(c)) return ensure_tiles(c, dtype == VQE_C128 ? 1 : 0);
-    const Plan& pl = plan_now(c);
+    const int form = jit_mode();
+    if (int rc = check_form(c, form, "vqe_circuit_prepare")) return rc;
+    if (use_tiles(c, form)) return ensure_tiles(c, dtype == VQE_C128 ? 1 : 0);
+    const Plan& pl = plan_of(c, form);
     if (!pl.jit) return VQE_OK;
     return ensure_jit(c, pl, dtype == VQE_C128 ? 1 : 0);
     VQE_GUARD_END

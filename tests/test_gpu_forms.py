@@ -1,0 +1,72 @@
+"""The kernel form (vqe_set_specialize) is process-wide and may be changed by any
+thread at any time: an evaluation reads it once and keeps to one plan."""
+import threading
+
+import numpy as np
+import pytest
+
+from oracle import grad as ogr, hamiltonian as oham
+from paper_2402_11878_amd import _lib, ansatz
+
+from gpu_util import Dev, oracle_gates, rel_err, say
+
+pytestmark = pytest.mark.gpu
+
+DT = {"c64": _lib.VQE_C64, "c128": _lib.VQE_C128}
+FORMS = {"never": _lib.SPECIALIZE_NEVER, "auto": _lib.SPECIALIZE_AUTO, "always": _lib.SPECIALIZE_ALWAYS}
+E_TOL = {_lib.VQE_C64: 1e-5, _lib.VQE_C128: 1e-10}
+GRAD_TOL = {_lib.VQE_C64: 1e-4, _lib.VQE_C128: 1e-9}
+
+
+def _problem(n, layers, seed):
+    rng = np.random.default_rng(seed)
+    x = np.array([0, 1, 6, 1 << (n - 1), 3 << (n - 2), 5], np.uint64)
+    z = rng.choice(1 << n, size=len(x), replace=False).astype(np.uint64)
+    w = rng.normal(size=len(x))
+    arr = ansatz.layered(n, layers)
+    th = rng.uniform(-np.pi, np.pi, size=2 * n * layers)
+    ref = ogr.adjoint(n, oracle_gates(arr), th, oham.from_masks(n, x, z, w))
+    return _lib.vqe_circuit_create(n, arr), _lib.vqe_hamiltonian_create(n, x, z, w), th, ref
+
+
+@pytest.mark.parametrize("n,dt", [(12, "c64"), (14, "c64"), (14, "c128")])
+def test_form_changed_by_another_thread(n, dt):
+    """Evaluations while another thread goes through the forms: every one
+    gives the gradient, by whichever form it began with."""
+    dtype = DT[dt]
+    say(f"case forms race n={n} {dt}")
+    c, h, th, (E_ref, g_ref) = _problem(n, 3, n)
+    d = [Dev(n, dtype) for _ in range(3)]
+    old = _lib.vqe_set_specialize(_lib.SPECIALIZE_AUTO)
+    stop = threading.Event()
+
+    def flip():
+        while not stop.is_set():
+            for f in (_lib.SPECIALIZE_ALWAYS, _lib.SPECIALIZE_NEVER, _lib.SPECIALIZE_AUTO, _lib.SPECIALIZE_NEVER):
+                _lib.vqe_set_specialize(f)
+
+    def check(E, g):
+        assert rel_err(E, E_ref) <= E_TOL[dtype]
+        assert np.max(np.abs(g - g_ref)) / max(np.max(np.abs(g_ref)), 1) <= GRAD_TOL[dtype]
+
+    try:
+        for f in FORMS.values():  # compiles the kernels of every form
+            _lib.vqe_set_specialize(f)
+            check(*_lib.vqe_energy_grad(d[0].h, d[1].h, c, th, h))
+        t = threading.Thread(target=flip)
+        t.start()
+        try:
+            for k in range(200):
+                check(*_lib.vqe_energy_grad(d[0].h, d[1].h, c, th, h, ckpt=[d[2].h] if k % 2 else []))
+                _lib.vqe_state_set_basis(d[0].h, 0)
+                _lib.vqe_apply_circuit(d[0].h, c, th)
+                assert rel_err(_lib.vqe_expect_pauli(d[0].h, h)[0], E_ref) <= E_TOL[dtype]
+        finally:
+            stop.set()
+            t.join()
+    finally:
+        _lib.vqe_set_specialize(old)
+        for s in d:
+            s.free()
+        _lib.vqe_circuit_free(c)
+        _lib.vqe_hamiltonian_free(h)
