@@ -1,5 +1,6 @@
 """The kernel form (vqe_set_specialize) is process-wide and may be changed by any
-thread at any time: an evaluation reads it once and keeps to one plan."""
+thread at any time: an evaluation reads it once and keeps to one plan.
+Checkpoints and chunked submission in every form."""
 import threading
 
 import numpy as np
@@ -68,5 +69,42 @@ def test_form_changed_by_another_thread(n, dt):
         _lib.vqe_set_specialize(old)
         for s in d:
             s.free()
+        _lib.vqe_circuit_free(c)
+        _lib.vqe_hamiltonian_free(h)
+
+
+@pytest.mark.parametrize("dt", ["c64", "c128"])
+@pytest.mark.parametrize("form,n", [("never", 13), ("never", 14), ("always", 11), ("always", 13), ("always", 14),
+                                    ("auto", 13), ("auto", 15)])
+def test_checkpoints_and_chunks(form, n, dt):
+    """Checkpoints and chunked submission in every kernel form: interpreted and
+    specialised windows, tile passes, one launch, mid-size passes.  Chunks give
+    the bits of the unchunked sweep, checkpoints the energy's bits and the
+    gradient up to the rounding of un-applying fewer gates."""
+    dtype = DT[dt]
+    say(f"case forms checkpoints {form} n={n} {dt}")
+    c, h, th, (E_ref, g_ref) = _problem(n, 5, n)
+    d = [Dev(n, dtype) for _ in range(5)]
+    s, l, cks = d[0], d[1], d[2:]
+    old = _lib.vqe_set_specialize(FORMS[form])
+    try:
+        E0, g0 = _lib.vqe_energy_grad(s.h, l.h, c, th, h)
+        assert rel_err(E0, E_ref) <= E_TOL[dtype]
+        assert np.max(np.abs(g0 - g_ref)) / max(np.max(np.abs(g_ref)), 1) <= GRAD_TOL[dtype]
+        passes = _lib.vqe_circuit_info(c)[1]
+        for chunk in (1, 2, 3, passes, passes + 5):
+            E1, g1 = _lib.vqe_energy_grad(s.h, l.h, c, th, h, chunk_passes=chunk)
+            assert E1 == E0 and np.array_equal(g1, g0), chunk
+        for k in (1, 3):
+            ck = [b.h for b in cks[:k]]
+            E1, g1 = _lib.vqe_energy_grad(s.h, l.h, c, th, h, ckpt=ck)
+            assert rel_err(E1, E0) <= E_TOL[dtype]
+            assert np.max(np.abs(g1 - g_ref)) / max(np.max(np.abs(g_ref)), 1) <= GRAD_TOL[dtype]
+            E2, g2 = _lib.vqe_energy_grad(s.h, l.h, c, th, h, ckpt=ck, chunk_passes=2)
+            assert E2 == E1 and np.array_equal(g2, g1)
+    finally:
+        _lib.vqe_set_specialize(old)
+        for b in d:
+            b.free()
         _lib.vqe_circuit_free(c)
         _lib.vqe_hamiltonian_free(h)
