@@ -362,11 +362,12 @@ int vqe_stream_destroy(void* stream);
  * the stream it runs on; vqe_profile_read synchronises those events and
  * returns, for one kernel kind, the number of launches, their summed device
  * time in milliseconds and their summed algorithmic bytes (the bytes the
- * method must move: 2 S per forward window pass, 4 S per reverse window
- * pass, (1 + D) S read + S written for H psi where D is the number of
- * distinct partner tiles, or 2 S (first) / 3 S (others) per window pass of H
- * psi, S per per-term sweep; S = state bytes).  A small state's evaluation in
- * one launch counts as one reverse pass that writes 2 S. */
+ * method must move: 2 S per forward window pass (S where a tile or mid-size
+ * pass starts from |0...0> and reads nothing), 4 S per reverse window pass,
+ * (1 + D) S read + S written for H psi where D is the number of distinct
+ * partner tiles, or 2 S (first) / 3 S (others) per window pass of H psi, S per
+ * per-term sweep; S = state bytes).  A small state's evaluation in one launch
+ * counts as one reverse pass that writes 2 S. */
 #define VQE_KERNEL_WINDOW_FWD  0
 #define VQE_KERNEL_WINDOW_REV  1
 #define VQE_KERNEL_HPSI        2

@@ -2058,7 +2058,8 @@ int mid_impl(vqe_batch* b, const vqe_batch_item* items, const std::vector<size_t
         void* c = at == bounds.end() ? nullptr : ck[(size_t)(at - bounds.begin())];
         if (c && rev) VQE_HIP(hipMemcpyAsync(own->psi->data, c, own->psi->bytes, hipMemcpyDeviceToDevice, b->stream));
         {
-            auto ps = prof(rev ? VQE_KERNEL_WINDOW_REV : VQE_KERNEL_WINDOW_FWD, (rev ? 4.0 : 2.0) * S);
+            // the first pass stages |0...0> and only writes
+            auto ps = prof(rev ? VQE_KERNEL_WINDOW_REV : VQE_KERNEL_WINDOW_FWD, (rev ? 4.0 : p ? 2.0 : 1.0) * S);
             VQE_HIP(launch_mid_pass<T>((const MidPass*)(d + (rev ? o_rev : o_fwd)) + l_off[p], (uint32_t)l_cnt[p],
                                        l_grid[p], rev, part, b->stream));
         }
