@@ -1881,7 +1881,11 @@ int mid_impl(vqe_batch* b, const vqe_batch_item* items, const std::vector<size_t
     const size_t amp = 2 * sizeof(T);
     // lam = H psi: window passes (hwin_batch_kernel, one launch per pass index
     // and coefficient form) where the Hamiltonian has a window cover, else the
-    // tile kernel (mid_hpsi_kernel)
+    // tile kernel (mid_hpsi_kernel).  A state of its own keeps to the form that
+    // moves fewer bytes, and to the tile kernel of large states, which reads a
+    // term once for several amplitudes: 101 X groups of 8 terms, no cover, 4
+    // layers, per call: 14 qubits complex64 362 us (573 by mid_hpsi_kernel), 19
+    // qubits complex128 583 (1041)
     std::vector<uint32_t> nblk(m), nblk_e(m);
     std::vector<uint64_t> part_base(m), part_s(m), red_base(m), st_off(m), img_off(m);
     std::vector<char> use_hw(m);
@@ -1894,8 +1898,9 @@ int mid_impl(vqe_batch* b, const vqe_batch_item* items, const std::vector<size_t
         if (int rc = upload_hamiltonian(hh)) return rc;
         const BatchPlan& bp = c->batch[dt][0];
         nblk[k] = (uint32_t)std::min<uint64_t>(1ull << (c->n - kMidWin), kMidMaxBlocks);
-        use_hw[k] = !hh->hw_wins.empty();
+        use_hw[k] = own ? hh->hw_lam : !hh->hw_wins.empty();
         nblk_e[k] = (uint32_t)std::min<uint64_t>(1ull << (c->n - (use_hw[k] ? kHwBits : kMidTileBits)), kMidMaxBlocks);
+        if (own && !use_hw[k]) nblk_e[k] = 1;  // apply_h() leaves the sums
         if (use_hw[k]) {
             n_hw += hh->hw_wins.size();
             hmax = std::max(hmax, hh->hw_wins.size());
@@ -1946,7 +1951,7 @@ int mid_impl(vqe_batch* b, const vqe_batch_item* items, const std::vector<size_t
         const vqe_circuit* c = it.circuit;
         const BatchPlan& bp = c->batch[dt][0];
         fill_batch_image<T>(c, bp, it.params, it.hamiltonian->norm1, ha, h + o_img + img_off[k]);
-        if (!use_hw[k]) {
+        if (!use_hw[k] && !own) {
             MidHam mh{};
             mh.psi = psi_of(k);
             mh.lam = lam_of(k);
@@ -2069,10 +2074,9 @@ int mid_impl(vqe_batch* b, const vqe_batch_item* items, const std::vector<size_t
     };
     for (size_t p = 0; p < pmax; ++p)
         if (int rc = launch(p, false)) return rc;
-    if (n_th) {
-        auto ps = prof(VQE_KERNEL_HPSI, own ? hpsi_bytes(items[idx[0]].hamiltonian, own->psi, true) : 0.0);
-        VQE_HIP(launch_mid_hpsi<T>((const MidHam*)(d + o_ham), (uint32_t)n_th, hblk, part, b->stream));
-    }
+    if (n_th) VQE_HIP(launch_mid_hpsi<T>((const MidHam*)(d + o_ham), (uint32_t)n_th, hblk, part, b->stream));
+    if (own && !use_hw[0])
+        if (int rc = apply_h<T>(own->psi, own->lam->data, items[idx[0]].hamiltonian, part + part_base[0])) return rc;
     for (size_t l = 0; l < hw_launch.size(); ++l) {
         const HwLaunch& L = hw_launch[l];
         auto ps = prof(VQE_KERNEL_HPSI, (l ? 3.0 : 2.0) * S);

@@ -1,6 +1,7 @@
-"""Single evaluations above the LDS limit and below the specialised sizes: the
-trace counts the bytes that a pass must move (the first forward pass stages
-|0...0> and only writes).  Energies and gradients against the oracle."""
+"""Single evaluations above the LDS limit and below the specialised sizes: lam =
+H psi runs in the form that vqe_hamiltonian_plan reports, and the trace counts
+the bytes that a pass must move (the first forward pass stages |0...0> and only
+writes).  Energies and gradients against the oracle."""
 import numpy as np
 import pytest
 
@@ -46,9 +47,11 @@ def test_form_and_traced_bytes(kind, n, dt):
         _lib.vqe_profile_enable(True)
         _lib.vqe_profile_reset()
         E, g = _lib.vqe_energy_grad(s.h, l.h, c, th, h)
-        fwd, rev = (_lib.vqe_profile_read(k) for k in (0, 1))
+        fwd, rev, hp = (_lib.vqe_profile_read(k) for k in (0, 1, 2))
         assert fwd[2] == (2 * fwd[0] - 1) * S
         assert rev[2] == 4 * rev[0] * S and rev[0] == fwd[0]
+        D = len({int(v) >> 10 for v in x} - {0})
+        assert (hp[0], hp[2]) == ((m, (3 * m - 1) * S) if m else (1, (D + 2) * S))
         E_ref, g_ref = ogr.adjoint(n, oracle_gates(arr), th, oham.from_masks(n, x, z, w))
         assert rel_err(E, E_ref) <= E_TOL[dtype]
         assert np.max(np.abs(g - g_ref)) / max(np.max(np.abs(g_ref)), 1) <= GRAD_TOL[dtype]
