@@ -622,8 +622,8 @@ def main():
     ap.add_argument("--mid-batch-n-max", type=int, default=16,
                     help="serving with --mid-batch 1: largest qubit count batched (larger mid-size requests go "
                          "to the mid-size workers; 0: all of them batched)")
-    ap.add_argument("--chunk-passes", type=int, default=3,
-                    help="serving: submit large evaluations in chunks of this many window passes (0: at once)")
+    ap.add_argument("--chunk-passes", type=int, default=1,
+                    help="serving: submit large evaluations in chunks of this many passes (0: at once)")
     ap.add_argument("--batch-sizes", default="1,4,16", help="batch mode: items per call")
     ap.add_argument("--batch-qubits", default="14,16,20,24", help="batch mode: qubit counts")
     ap.add_argument("--batch-masked", type=int, default=0,

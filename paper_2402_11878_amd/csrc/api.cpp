@@ -1125,8 +1125,13 @@ double hpsi_bytes(const vqe_hamiltonian* h, const vqe_state* s, bool write);
 
 // lam = H psi with the energy partials reduced into d_out[0..1]
 // (Re<psi|lam>, <psi|psi>): window passes when planned, else the tile kernel.
+// chunk > 0: waits for the stream after that many window passes, as the sweeps
+// do.  A molecule-shaped Hamiltonian of 28 qubits runs tens of them, two blocks
+// on every CU: queued at once they held the small requests of the served stream
+// back for all of their time (12 qubits p99 29 ms at 58.6 requests/s, 16 qubits
+// 53; 6 and 14 with one pass at a time here too).
 template <typename T>
-int apply_h(vqe_state* psi, void* lam, const vqe_hamiltonian* h, double* d_out) {
+int apply_h(vqe_state* psi, void* lam, const vqe_hamiltonian* h, double* d_out, int chunk = 0) {
     hipStream_t st = psi->stream;
     uint32_t nb = 0;
     if (h->hw_lam) {
@@ -1136,6 +1141,8 @@ int apply_h(vqe_state* psi, void* lam, const vqe_hamiltonian* h, double* d_out) 
             VQE_HIP(launch_hwin<T>(psi->n, h->hw_wins[wi], psi->data, lam, h->d_hw_groups, h->d_hw_classes,
                                    hw_terms_of<T>(h), h->real_coeffs,
                                    wi == 0, wi + 1 == m, psi->d_part, &nb, st));
+            ps.end();
+            if (chunk > 0 && (wi + 1) % (size_t)chunk == 0 && wi + 1 < m) VQE_HIP(hipStreamSynchronize(st));
         }
     } else {
         ProfScope ps(VQE_KERNEL_HPSI, hpsi_bytes(h, psi, true), st);
@@ -1304,8 +1311,10 @@ int adjoint_impl(vqe_state* psi, vqe_state* lam, const vqe_circuit* c, int form,
     const int chunk = o && o->chunk_passes > 0 ? o->chunk_passes : 0;
     rc = forward<T>(psi, c, form, params, bounds, ck, true, h->norm1, chunk);
     if (rc) return rc;
-    rc = apply_h<T>(psi, lam->data, h, d_e);
+    if (chunk) VQE_HIP(hipStreamSynchronize(st));
+    rc = apply_h<T>(psi, lam->data, h, d_e, chunk);
     if (rc) return rc;
+    if (chunk) VQE_HIP(hipStreamSynchronize(st));
     if (tiles) {
         rc = reverse_tiles<T>(psi, lam, tp, bounds, ck, d_g, chunk);
         if (rc) return rc;
@@ -2069,7 +2078,8 @@ int mid_impl(vqe_batch* b, const vqe_batch_item* items, const std::vector<size_t
                                        l_grid[p], rev, part, b->stream));
         }
         if (c && !rev) VQE_HIP(hipMemcpyAsync(c, own->psi->data, own->psi->bytes, hipMemcpyDeviceToDevice, b->stream));
-        if (chunk && (p + 1) % chunk == 0 && (!rev || p + 1 < pmax)) VQE_HIP(hipStreamSynchronize(b->stream));
+        const bool end = p + 1 == pmax;
+        if (chunk && ((p + 1) % chunk == 0 || end) && !(rev && end)) VQE_HIP(hipStreamSynchronize(b->stream));
         return (int)VQE_OK;
     };
     for (size_t p = 0; p < pmax; ++p)
@@ -2082,6 +2092,7 @@ int mid_impl(vqe_batch* b, const vqe_batch_item* items, const std::vector<size_t
         auto ps = prof(VQE_KERNEL_HPSI, (l ? 3.0 : 2.0) * S);
         VQE_HIP(launch_hwin_batch<T>((const HwItem*)(d + o_hw) + L.off, (uint32_t)L.cnt, L.grid, L.real, part,
                                      b->stream));
+        if (chunk && ((l + 1) % chunk == 0 || l + 1 == hw_launch.size())) VQE_HIP(hipStreamSynchronize(b->stream));
     }
     for (size_t p = 0; p < pmax; ++p)
         if (int rc = launch(p, true)) return rc;

@@ -291,8 +291,8 @@ class GpuExecutor:
     streams restricted to the others (vqe_stream_create with a CU mask).
     Batched mid-size requests (run_mid_batch) have a batch handle and stream
     of their own.  chunk_passes > 0 submits the evaluations of instances
-    above mid_n_max qubits in chunks of that many window passes (about one
-    ansatz layer at 3), waiting for each chunk before queueing the next, so
+    above mid_n_max qubits in chunks of that many passes (a tile pass is about
+    one ansatz layer), waiting for each chunk before queueing the next, so
     that kernels of other lanes start between chunks."""
 
     def __init__(self, dtype="c64", n_ckpt=0, small_n_max=None, reserve_cus=0, mid_n_max=20, big_streams=3,

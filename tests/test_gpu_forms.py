@@ -108,3 +108,35 @@ def test_checkpoints_and_chunks(form, n, dt):
             b.free()
         _lib.vqe_circuit_free(c)
         _lib.vqe_hamiltonian_free(h)
+
+
+@pytest.mark.parametrize("dt", ["c64", "c128"])
+@pytest.mark.parametrize("form,n", [("never", 16), ("auto", 16), ("auto", 20)])
+def test_chunks_of_h_psi(form, n, dt):
+    """chunk_passes over a Hamiltonian of several window passes, waiting within
+    H psi too: the bits of the unchunked evaluation."""
+    dtype = DT[dt]
+    say(f"case forms chunks of H psi {form} n={n} {dt}")
+    rng = np.random.default_rng(n)
+    x = np.array([0] + [3 << a for a in range(n - 1)] + [(1 << a) | (1 << b) for a in range(n) for b in range(a)],
+                 np.uint64)
+    h = _lib.vqe_hamiltonian_create(n, x, rng.integers(0, 1 << n, size=len(x)).astype(np.uint64),
+                                    rng.normal(size=len(x)))
+    m = len(_lib.vqe_hamiltonian_plan(h))
+    assert m > 2
+    c = _lib.vqe_circuit_create(n, ansatz.layered(n, 2))
+    th = rng.uniform(-np.pi, np.pi, size=4 * n)
+    s, l, ck = Dev(n, dtype), Dev(n, dtype), Dev(n, dtype)
+    old = _lib.vqe_set_specialize(FORMS[form])
+    try:
+        for ckpt in ([], [ck.h]):
+            E0, g0 = _lib.vqe_energy_grad(s.h, l.h, c, th, h, ckpt=ckpt)
+            for chunk in (1, 2, m, 100):
+                E1, g1 = _lib.vqe_energy_grad(s.h, l.h, c, th, h, ckpt=ckpt, chunk_passes=chunk)
+                assert E1 == E0 and np.array_equal(g1, g0), chunk
+    finally:
+        _lib.vqe_set_specialize(old)
+        for b in (s, l, ck):
+            b.free()
+        _lib.vqe_circuit_free(c)
+        _lib.vqe_hamiltonian_free(h)
