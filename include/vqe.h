@@ -424,11 +424,14 @@ int vqe_set_specialize(int mode);
 
 /* Compiles and loads, on the calling thread's current HIP device, the
  * specialised kernels that an evaluation of `dtype` (VQE_C64 / VQE_C128)
- * would use under the current kernel form; returns VQE_OK at once when that
- * form is interpreted or the kernels are already loaded.  Evaluations do this
+ * would use under the current kernel form, and in the default form plans the
+ * programs of the batch kernels (up to VQE_BATCH_MAX_QUBITS_MID qubits; those
+ * with places for checkpoints are planned on first use); returns VQE_OK at
+ * once when that form is interpreted or all this is done.  Evaluations do this
  * themselves on first use: call it to keep compilation (about a second per
- * distinct pass, in parallel) out of a latency-sensitive first evaluation,
- * e.g. when a served instance is registered.  Errors as for evaluations. */
+ * distinct pass, in parallel) and planning (up to about a millisecond) out of a
+ * latency-sensitive first evaluation, e.g. when a served instance is
+ * registered.  Errors as for evaluations. */
 int vqe_circuit_prepare(const vqe_circuit* c, int dtype);
 
 /* ------------------------------------------------------------------ slimming

@@ -2750,10 +2750,14 @@ int vqe_circuit_prepare(const vqe_circuit* c, int dtype) {
     }
     const int form = jit_mode();
     if (int rc = check_form(c, form, "vqe_circuit_prepare")) return rc;
-    if (use_tiles(c, form)) return ensure_tiles(c, dtype == VQE_C128 ? 1 : 0);
+    const int d = dtype == VQE_C128 ? 1 : 0;
+    // the programs of batches and of single evaluations in the default form
+    if (form == VQE_SPECIALIZE_AUTO && c->n <= kMidMaxQubits)
+        if (int rc = ensure_batch(c, d)) return rc;
+    if (use_tiles(c, form)) return ensure_tiles(c, d);
     const Plan& pl = plan_of(c, form);
     if (!pl.jit) return VQE_OK;
-    return ensure_jit(c, pl, dtype == VQE_C128 ? 1 : 0);
+    return ensure_jit(c, pl, d);
     VQE_GUARD_END
 }
 
