@@ -1274,7 +1274,7 @@ __device__ __forceinline__ void hwin_body(const HwDesc& w, uint64_t n_cosets, ui
 }
 
 template <typename T, bool EONLY, bool REAL, bool MANY>
-__global__ void __launch_bounds__(kHwThreads, (MANY && sizeof(T) == 4 && !EONLY ? 8 : 4))
+__global__ void __launch_bounds__(kHwThreads, (MANY && sizeof(T) == 4 ? 8 : 4))
 hwin_kernel(const HwDesc w, uint64_t n_cosets, uint32_t cpt, uint32_t mlog,
             const typename VecOf<T>::type* __restrict__ psi, typename VecOf<T>::type* __restrict__ lam,
             const HwGroup* __restrict__ groups, const HwClass* __restrict__ classes,
@@ -1647,7 +1647,8 @@ hipError_t launch_hwin(int n, const HwDesc& w, const void* psi, void* lam, const
                        ws.cpt, ws.mlog, (const V*)psi, (V*)lam, groups, classes, terms, first ? 1 : 0, last ? 1 : 0, \
                        part)
     // More than one coset per CU.  complex64: two blocks per CU (28 qubits, three
-    // passes: 4.8 ms against 5.7 with the registers of one; 20 qubits, 128 cosets,
+    // passes: 4.8 ms against 5.7 with the registers of one, energy only 2.09
+    // against 2.93, as half the waves leave out a group; 20 qubits, 128 cosets,
     // 180 us against 157 for five).  complex128: one block per CU that goes on (24
     // qubits, eight cosets per block: 2780 us against 2980 for ten passes; 22 qubits,
     // two, 78 us against 74 with lam, but 126 against 144 energy only; 14 qubits, one,
