@@ -382,7 +382,9 @@ int vqe_profile_reset(void);
 int vqe_profile_read(int kind, uint64_t* launches, double* total_ms, double* bytes);
 
 /* Inspection of how lam = H psi (vqe_apply_hamiltonian, the adjoint of
- * vqe_energy_grad) runs for this Hamiltonian.  Host only.
+ * vqe_energy_grad) runs for this Hamiltonian.  Host only.  Evaluations in one
+ * launch do not use it; those by mid-size passes take the window form in more
+ * cases, wherever windows hold every group and groups have many terms.
  *   Tile form (*n_windows = 0): one sweep over tiles of 1024 amplitudes that
  *     reads the partner tile of every distinct out-of-tile x: (1 + D) S read,
  *     S written (D = distinct non-zero x >> 10, S = state bytes).

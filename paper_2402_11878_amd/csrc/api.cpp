@@ -1890,11 +1890,15 @@ int mid_impl(vqe_batch* b, const vqe_batch_item* items, const std::vector<size_t
     const size_t amp = 2 * sizeof(T);
     // lam = H psi: window passes (hwin_batch_kernel, one launch per pass index
     // and coefficient form) where the Hamiltonian has a window cover, else the
-    // tile kernel (mid_hpsi_kernel).  A state of its own keeps to the form that
-    // moves fewer bytes, and to the tile kernel of large states, which reads a
-    // term once for several amplitudes: 101 X groups of 8 terms, no cover, 4
-    // layers, per call: 14 qubits complex64 362 us (573 by mid_hpsi_kernel), 19
-    // qubits complex128 583 (1041)
+    // tile kernel (mid_hpsi_kernel; for a state of its own that of large states,
+    // which reads a term once for several amplitudes: 101 X groups of 8 terms, no
+    // cover, 4 layers, per call: 14 qubits complex64 362 us against 573, 19 qubits
+    // complex128 583 against 1041).  A state of its own takes tiles also where the
+    // plan of large states counts fewer bytes for them and groups have six terms or
+    // less.  With more, windows, which sum a group's terms once per class: the
+    // bytes come from the cache.  13 qubits complex128, groups x terms each, tiles
+    // against windows: 4000 x 1 2450 us, 3860; 500 x 4 760, 872; 500 x 6 952, 970;
+    // 500 x 10 1340, 1120; 60 x 30 516, 341; 1 x 2000 480, 250
     std::vector<uint32_t> nblk(m), nblk_e(m);
     std::vector<uint64_t> part_base(m), part_s(m), red_base(m), st_off(m), img_off(m);
     std::vector<char> use_hw(m);
@@ -1907,7 +1911,7 @@ int mid_impl(vqe_batch* b, const vqe_batch_item* items, const std::vector<size_t
         if (int rc = upload_hamiltonian(hh)) return rc;
         const BatchPlan& bp = c->batch[dt][0];
         nblk[k] = (uint32_t)std::min<uint64_t>(1ull << (c->n - kMidWin), kMidMaxBlocks);
-        use_hw[k] = own ? hh->hw_lam : !hh->hw_wins.empty();
+        use_hw[k] = !hh->hw_wins.empty() && !(own && !hh->hw_lam && hh->w.size() <= 6 * hh->groups.size());
         nblk_e[k] = (uint32_t)std::min<uint64_t>(1ull << (c->n - (use_hw[k] ? kHwBits : kMidTileBits)), kMidMaxBlocks);
         if (own && !use_hw[k]) nblk_e[k] = 1;  // apply_h() leaves the sums
         if (use_hw[k]) {
@@ -2085,7 +2089,7 @@ int mid_impl(vqe_batch* b, const vqe_batch_item* items, const std::vector<size_t
     for (size_t p = 0; p < pmax; ++p)
         if (int rc = launch(p, false)) return rc;
     if (n_th) VQE_HIP(launch_mid_hpsi<T>((const MidHam*)(d + o_ham), (uint32_t)n_th, hblk, part, b->stream));
-    if (own && !use_hw[0])
+    if (own && !use_hw[0])  // hw_lam is false: tiles
         if (int rc = apply_h<T>(own->psi, own->lam->data, items[idx[0]].hamiltonian, part + part_base[0])) return rc;
     for (size_t l = 0; l < hw_launch.size(); ++l) {
         const HwLaunch& L = hw_launch[l];

@@ -1,6 +1,6 @@
 """Single evaluations above the LDS limit and below the specialised sizes: lam =
-H psi runs in the form that vqe_hamiltonian_plan reports, and the trace counts
-the bytes that a pass must move (the first forward pass stages |0...0> and only
+H psi runs by window passes or as one sweep over tiles, and the trace counts the
+bytes that a pass must move (the first forward pass stages |0...0> and only
 writes).  Energies and gradients against the oracle."""
 import numpy as np
 import pytest
@@ -18,19 +18,20 @@ GRAD_TOL = {_lib.VQE_C64: 1e-4, _lib.VQE_C128: 1e-9}
 
 
 def _masks(kind, n):
-    """tile: two 10-bit X masks that two windows hold, but one sweep over tiles
-    moves less; nocover: a mask that no window holds; window: one window."""
+    """tile, wide: two 10-bit X masks that two windows hold, where the plan of large
+    states takes tiles: so do few terms per group, many take windows; nocover: a
+    mask that no window holds; window: one window."""
     rng = np.random.default_rng(n)
-    x = {"tile": [0, 0x3ff << 3, 0x3ff << (n - 10)], "nocover": [0, (1 << n) - 1, 5, 0x3ff << (n - 10)],
+    x = {"tile": [0, 0x3ff << 3, 0x3ff << (n - 10)], "wide": [0, 0x3ff << 3, 0x3ff << (n - 10)], "nocover": [0, (1 << n) - 1, 5, 0x3ff << (n - 10)],
          "window": [0, 1, 6, 1 << 11]}[kind]
-    x = np.repeat(np.array(x, np.uint64), 3)
+    x = np.repeat(np.array(x, np.uint64), 7 if kind == "wide" else 3)
     z = rng.choice(1 << n, size=len(x), replace=False).astype(np.uint64)
     return x, z, rng.normal(size=len(x))
 
 
 @pytest.mark.parametrize("dt", ["c64", "c128"])
 @pytest.mark.parametrize("n", [14, 16])
-@pytest.mark.parametrize("kind", ["tile", "nocover", "window"])
+@pytest.mark.parametrize("kind", ["tile", "wide", "nocover", "window"])
 def test_form_and_traced_bytes(kind, n, dt):
     dtype = DT[dt]
     say(f"case single mid {kind} n={n} {dt}")
@@ -51,6 +52,7 @@ def test_form_and_traced_bytes(kind, n, dt):
         assert fwd[2] == (2 * fwd[0] - 1) * S
         assert rev[2] == 4 * rev[0] * S and rev[0] == fwd[0]
         D = len({int(v) >> 10 for v in x} - {0})
+        m = 2 if kind == "wide" else m
         assert (hp[0], hp[2]) == ((m, (3 * m - 1) * S) if m else (1, (D + 2) * S))
         E_ref, g_ref = ogr.adjoint(n, oracle_gates(arr), th, oham.from_masks(n, x, z, w))
         assert rel_err(E, E_ref) <= E_TOL[dtype]
