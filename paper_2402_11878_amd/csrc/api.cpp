@@ -563,10 +563,13 @@ void plan_small(vqe_hamiltonian* h, const std::vector<TermDesc<T>>& terms, std::
                 std::vector<char>& stream) {
     const int sh = batch_bits(h->n) - kProgBits;
     auto room = [&] { return kProgBlock - blocks.back().bytes; };
+    std::vector<uint32_t> order;
     for (const GroupDesc& g : h->groups) {
-        std::vector<uint32_t> order;
-        for (uint32_t t = g.begin; t < g.end; ++t) order.push_back(t);
-        std::stable_sort(order.begin(), order.end(), [&](uint32_t a, uint32_t b) { return (h->z[a] >> sh) < (h->z[b] >> sh); });
+        uint32_t at[17] = {0};  // a counting sort
+        for (uint32_t t = g.begin; t < g.end; ++t) ++at[1 + (h->z[t] >> sh)];
+        for (int u = 0; u < 16; ++u) at[u + 1] += at[u];
+        order.resize(g.end - g.begin);
+        for (uint32_t t = g.begin; t < g.end; ++t) order[at[h->z[t] >> sh]++] = t;
         for (size_t i = 0; i < order.size();) {
             if (blocks.empty() || room() < sizeof(SmallGroup) + sizeof(SmallTerm<T>)) {
                 SmallBlock b{};
@@ -574,24 +577,21 @@ void plan_small(vqe_hamiltonian* h, const std::vector<TermDesc<T>>& terms, std::
                 b.off = (uint32_t)stream.size();
                 blocks.push_back(b);
             }
-            const size_t most = (room() - sizeof(SmallGroup)) / sizeof(SmallTerm<T>);
+            const size_t most = std::min((room() - sizeof(SmallGroup)) / sizeof(SmallTerm<T>), order.size() - i);
             SmallGroup sg{};
             sg.x = (uint32_t)g.x;
-            const size_t at = stream.size();
-            stream.resize(at + sizeof(SmallGroup));
-            for (; i < order.size() && sg.n_terms < most; ++i) {
+            const size_t start = stream.size();
+            stream.resize(start + sizeof(SmallGroup) + most * sizeof(SmallTerm<T>));
+            auto* tm = (SmallTerm<T>*)&stream[start + sizeof(SmallGroup)];
+            for (; sg.n_terms < most; ++i, ++tm) {
                 const uint32_t t = order[i], u = (uint32_t)(h->z[t] >> sh);
                 if (((sg.count[u >> 2] >> (8 * (u & 3))) & 255u) == 255u) break;
                 sg.count[u >> 2] += 1u << (8 * (u & 3));
-                SmallTerm<T> tm{};
-                tm.zt = (uint32_t)h->z[t] & ((1u << sh) - 1);
-                tm.cre = terms[t].cre;
-                tm.cim = terms[t].cim;
-                const char* raw = (const char*)&tm;
-                stream.insert(stream.end(), raw, raw + sizeof(tm));
+                *tm = SmallTerm<T>{(uint32_t)h->z[t] & ((1u << sh) - 1), u, terms[t].cre, terms[t].cim};
                 ++sg.n_terms;
             }
-            std::memcpy(&stream[at], &sg, sizeof(sg));
+            stream.resize(start + sizeof(SmallGroup) + sg.n_terms * sizeof(SmallTerm<T>));
+            std::memcpy(&stream[start], &sg, sizeof(sg));
             blocks.back().bytes = (uint32_t)(stream.size() - blocks.back().off);
             ++blocks.back().n_groups;
         }

@@ -509,10 +509,18 @@ __device__ __forceinline__ void run_program(char* psi, char* lam, char* blk, uin
 // ------------------------------------------------------------------ small states
 template <typename T> constexpr int small_threads() { return 1 << ((sizeof(T) == 4 ? kBatchMaxQubitsC64 : kBatchMaxQubitsC128) - kProgBits); }
 
+// v with its sign bit xor the highest bit of s.
+__device__ __forceinline__ float flip_sign(float v, uint32_t s) { return __uint_as_float(__float_as_uint(v) ^ s); }
+__device__ __forceinline__ double flip_sign(double v, uint32_t s) {
+    return __hiloint2double((int)((uint32_t)__double2hiint(v) ^ s), __double2loint(v));
+}
+
 // lam = H psi for the thread's amplitudes b = t + p 2^(bits - 4): the terms of a
 // group go to one bucket per z pattern of the register bits, signed by the
 // thread part of their z bits, and D_x for the 16 patterns is the
-// Walsh-Hadamard transform of the bucket sums.  The tables come block by block
+// Walsh-Hadamard transform of the bucket sums; the terms of small groups are
+// added to the 16 directly (12 qubits complex64, 500 groups of 1, 2 and 4 terms:
+// 287, 371 and 547 us per call, 575, 601 and 654 with buckets for all).  The tables come block by block
 // as a program's do.
 template <typename T, bool REAL>
 __device__ __forceinline__ void small_hpsi(const BatchDesc<T>& d, const char* psi, char* blk, uint32_t t, uint32_t nt,
@@ -521,58 +529,99 @@ __device__ __forceinline__ void small_hpsi(const BatchDesc<T>& d, const char* ps
     constexpr uint32_t A = sizeof(V);
     const uint32_t sh = (uint32_t)d.bits - kProgBits, n_blocks = uni(d.n_blocks);
     const uint32_t b = slot_of<T>(t) * A;
+    // largest group summed term by term: 500 groups of four terms, directly and by
+    // buckets: complex64 10 qubits 534 and 566 us, 12 qubits 547 and 589, 13 qubits
+    // (two waves per SIMD) 681 and 648; complex128 10 qubits 691 and 633
+    const uint32_t direct = sizeof(T) == 4 && nt <= 256 ? 4 : 3;
 #pragma unroll
     for (int p = 0; p < kN; ++p) lr[p] = li[p] = 0;
     for (uint32_t k = 0; k < n_blocks; ++k) {
         const SmallBlock bk = d.ham[k];
-        char* at = blk + (k & 1) * kProgBlock;  // the block before may still be in use
+        char* buf = blk + (k & 1) * kProgBlock;  // the block before may still be in use
         {
             BlockFetch<64> f;
             f.fetch(d.ham_stream + uni(bk.off), uni(bk.bytes), t, nt);
-            f.store(at, uni(bk.bytes), t, nt);
+            f.store(buf, uni(bk.bytes), t, nt);
         }
         __syncthreads();
-        for (uint32_t g = uni(bk.n_groups); g; --g) {
-            const SmallGroup& G = *(const SmallGroup*)at;
+        const char *at = buf, *nx = buf;
+        SmallGroup head = *(const SmallGroup*)at;
+        SmallTerm<T> term = *(const SmallTerm<T>*)(at + sizeof(SmallGroup));
+        for (uint32_t g = uni(bk.n_groups); g; --g, at = nx) {
+            const uint32_t gx = uni(head.x), n_terms = uni(head.n_terms);
+            const SmallGroup G = head;
+            const SmallTerm<T> first = term;
             const SmallTerm<T>* tm = (const SmallTerm<T>*)(at + sizeof(SmallGroup));
-            const uint32_t n_terms = uni(G.n_terms);
-            const uint32_t w[4] = {uni(G.count[0]), uni(G.count[1]), uni(G.count[2]), uni(G.count[3])};
+            // what can be on its way while this group is worked on: its amplitudes, the next header and term
+            V x[kN];
+            const uint32_t from = b ^ (slot_of<T>(gx) * A);
+#pragma unroll
+            for (int p = 0; p < kN; ++p) x[p] = *(const V*)(psi + (from ^ (slot_of<T>((uint32_t)p << sh) * A)));
+            nx = at + sizeof(SmallGroup) + n_terms * sizeof(SmallTerm<T>);
+            head = *(const SmallGroup*)(g > 1 ? nx : at);
+            term = *(const SmallTerm<T>*)((g > 1 ? nx : at) + sizeof(SmallGroup));
             T er[kN], ei[kN];
+            if (n_terms <= direct) {
+                // a term is the same in all 16 patterns but for the signs of its register bits
+                auto signs = [&](const SmallTerm<T>& c, T (&sr)[kN], T (&si)[kN]) {
+                    const uint32_t neg = (uint32_t)__popc(c.zt & t) << 31, zr = uni(c.zr);
+                    sr[0] = flip_sign(c.cre, neg);
+                    if (!REAL) si[0] = flip_sign(c.cim, neg);
 #pragma unroll
-            for (int u = 0; u < kN; ++u) {
-                er[u] = ei[u] = 0;
-                for (uint32_t c = (w[u >> 2] >> (8 * (u & 3))) & 255u; c; --c, ++tm) {
-                    const bool neg = __popc(tm->zt & t) & 1;
-                    er[u] += neg ? -tm->cre : tm->cre;
-                    if (!REAL) ei[u] += neg ? -tm->cim : tm->cim;
-                }
-            }
+                    for (int q = 0; q < kProgBits; ++q) {
+                        const uint32_t nq = (zr >> q) << 31;
 #pragma unroll
-            for (int bit = 1; bit < kN; bit <<= 1)
+                        for (int p = 0; p < (1 << q); ++p) {
+                            sr[p | (1 << q)] = flip_sign(sr[p], nq);
+                            if (!REAL) si[p | (1 << q)] = flip_sign(si[p], nq);
+                        }
+                    }
+                };
+                signs(first, er, ei);
+                for (uint32_t k = 1; k < n_terms; ++k) {
+                    T sr[kN], si[kN];
+                    signs(tm[k], sr, si);
 #pragma unroll
-                for (int i = 0; i < kN; ++i) {
-                    if (i & bit) continue;
-                    const T x = er[i], y = er[i | bit];
-                    er[i] = x + y;
-                    er[i | bit] = x - y;
-                    if (!REAL) {
-                        const T u = ei[i], v = ei[i | bit];
-                        ei[i] = u + v;
-                        ei[i | bit] = u - v;
+                    for (int p = 0; p < kN; ++p) {
+                        er[p] += sr[p];
+                        if (!REAL) ei[p] += si[p];
                     }
                 }
-            const uint32_t from = b ^ (slot_of<T>(uni(G.x)) * A);
+            } else {
+                const uint32_t w[4] = {uni(G.count[0]), uni(G.count[1]), uni(G.count[2]), uni(G.count[3])};
+#pragma unroll
+                for (int u = 0; u < kN; ++u) {
+                    er[u] = ei[u] = 0;
+                    for (uint32_t c = (w[u >> 2] >> (8 * (u & 3))) & 255u; c; --c, ++tm) {
+                        const bool neg = __popc(tm->zt & t) & 1;
+                        er[u] += neg ? -tm->cre : tm->cre;
+                        if (!REAL) ei[u] += neg ? -tm->cim : tm->cim;
+                    }
+                }
+#pragma unroll
+                for (int bit = 1; bit < kN; bit <<= 1)
+#pragma unroll
+                    for (int i = 0; i < kN; ++i) {
+                        if (i & bit) continue;
+                        const T y = er[i], v = er[i | bit];
+                        er[i] = y + v;
+                        er[i | bit] = y - v;
+                        if (!REAL) {
+                            const T yi = ei[i], vi = ei[i | bit];
+                            ei[i] = yi + vi;
+                            ei[i | bit] = yi - vi;
+                        }
+                    }
+            }
 #pragma unroll
             for (int p = 0; p < kN; ++p) {
-                const V x = *(const V*)(psi + (from ^ (slot_of<T>((uint32_t)p << sh) * A)));
-                lr[p] += er[p] * x.x;
-                li[p] += er[p] * x.y;
+                lr[p] += er[p] * x[p].x;
+                li[p] += er[p] * x[p].y;
                 if (!REAL) {
-                    lr[p] -= ei[p] * x.y;
-                    li[p] += ei[p] * x.x;
+                    lr[p] -= ei[p] * x[p].y;
+                    li[p] += ei[p] * x[p].x;
                 }
             }
-            at += sizeof(SmallGroup) + n_terms * sizeof(SmallTerm<T>);
         }
     }
 }

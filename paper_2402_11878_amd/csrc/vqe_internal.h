@@ -515,13 +515,13 @@ bool build_program(bool dbl, int bits, const std::vector<Gate>& gates, const Pro
 // of groups: a header, then its terms.  A group's terms are sorted by their z
 // bits on the register part of the index (the kProgBits highest tile bits):
 // count[u] of them (a byte each) have the bits u.
-struct SmallGroup {
+struct alignas(8) SmallGroup {
     uint32_t x, n_terms, pad[2];
     uint32_t count[4];
 };
 template <typename T>
 struct SmallTerm {
-    uint32_t zt, pad;  // z bits on the thread part
+    uint32_t zt, zr;  // z bits on the thread and on the register part
     T cre, cim;
 };
 struct SmallBlock {
