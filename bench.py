@@ -136,7 +136,7 @@ def run_dtype(torch, L, core, wl, dtype, n_ckpt, steps, warmup, thetas, threshol
     sec = (t1 - t0) / steps
     return dict(name=name, sec=sec, E=energies[-1], grad=g, grads=grads, energies=energies, prof=prof,
                 threshold=th_used,
-                n_gates=len(circ.gates), n_passes_adj=circ.passes_count(dtype), n_terms=H.n_terms,
+                n_gates=len(circ.gates), n_terms=H.n_terms,
                 n_groups=H.n_groups,
                 state_bytes=(1 << n) * (8 if dtype == L.VQE_C64 else 16), n_ckpt=n_ckpt)
 
@@ -606,8 +606,8 @@ def main():
                          "batched against one at a time")
     ap.add_argument("--per-term", action="store_true", help="energy mode: also time the per-term form once")
     ap.add_argument("--specialize", default="auto", choices=["never", "auto", "always"],
-                    help="kernel form of the window passes (vqe_set_specialize): interpreted 5-qubit windows "
-                         "(never), specialised 7-qubit windows from 20 qubits on (auto, the default), or always")
+                    help="kernel form of the gate passes (vqe_set_specialize): interpreted 5-qubit windows (never), "
+                         "specialised passes from 20 qubits on (auto, the default), or always")
     ap.add_argument("--instances", type=int, default=32)
     ap.add_argument("--requests", type=int, default=200)
     ap.add_argument("--reps", type=int, default=2)
@@ -709,11 +709,11 @@ def main():
                         f"{head['name']} state, {head['n_ckpt']} checkpoint(s); energy + adjoint gradient",
             "n_qubits": wl.n_qubits,
             "state": head["name"],
-            "fused_passes_adjoint": head["n_passes_adj"],
+            "fused_passes_adjoint": n_rev // args.steps,
         },
         "roofline": {
             "bound": "hbm",
-            "kernel": "window_rev (reverse fused pass on psi and lam)",
+            "kernel": "window_rev (reverse fused pass on psi and lam: tile pass, 12 or 13 qubits)",
             "achieved": achieved,
             "peak": HBM_PEAK_GBS,
             "unit": "GB/s",
