@@ -179,14 +179,17 @@ int vqe_circuit_free(vqe_circuit* c);
 
 /* n_params = 1 + the largest param_index used (0 if none); n_passes = windows
  * of the plan under the current kernel form: the fused state sweeps per
- * application, except that tile passes (specialised, 14 or more qubits) take
- * fewer sweeps than this. */
+ * application, except that tile passes (specialised, 14 or more qubits) and the
+ * batch programs take fewer sweeps than this (vqe_profile_read counts those that
+ * ran). */
 int vqe_circuit_info(const vqe_circuit* c, size_t* n_params, size_t* n_passes);
 
 /* Inspection of the plan of windows of at most VQE_MAX_WINDOW qubits, which an
- * evaluation uses now unless it runs tile passes (it depends on the kernel form, see vqe_set_specialize: windows of at most 5 qubits for
- * interpreted kernels, VQE_MAX_WINDOW for specialised ones; the same plan for
- * both dtypes, which are only checked): pass `pass` has a window of *window
+ * evaluation uses now unless it runs tile passes or, as an adjoint evaluation in
+ * the default form below VQE_SPECIALIZE_AUTO_MIN_QUBITS, the programs of the batch
+ * kernels (it depends on the kernel form, see vqe_set_specialize: windows of at
+ * most 5 qubits for interpreted kernels, VQE_MAX_WINDOW for specialised ones; the
+ * same plan for both dtypes, which are only checked): pass `pass` has a window of *window
  * qubits (listed ascending in qubits[0..*window-1]; the caller provides
  * VQE_MAX_WINDOW entries) and applies *n_gates gates whose indices into the
  * circuit's gate list, in execution order, are written to gate_index

@@ -23,11 +23,11 @@
 //
 // What bounds it: the vector instructions and the latency of the stages of one
 // request, which uses one CU at one wave per SIMD (complex64: two at 13 qubits);
-// vector instructions issue in 46 % of a wave's cycles.  A gate per barrier with
-// the state read and written in LDS for each took, per call: 12 qubits x 4
-// layers complex64 388 us, now 136 (113 in the kernel); 24 requests of 8 to 13
-// qubits 1745 us, now 608; 4 states of 14 to 16 qubits (10-qubit windows
-// before) 1160 us, now 712; 12 qubits, excitations, complex128 439 us, now 233.
+// vector instructions issue in 45 % of the kernel's cycles (complex128 35 %).  A
+// gate per barrier with the state read and written in LDS for each took, per call:
+// 12 qubits x 4 layers complex64 388 us, now 129 (109 in the kernel); 24 requests
+// of 8 to 13 qubits 1745 us, now 614; 4 states of 14 to 16 qubits (10-qubit windows
+// before) 1160 us, now 690; 12 qubits, excitations, complex128 439 us, now 215.
 // Rows without a branch beat a switch per op (156 against 240 us at 12 qubits:
 // the arms of a switch cost copies of the 64 registers of psi and lam); rows of
 // CNOTs alone leave early (136).

@@ -15,7 +15,7 @@
 // qubits complex64 93.9 -> 46.7 ms, 24 qubits complex128 7.09 -> 3.72 ms, 20
 // qubits complex64 1.14 -> 0.52 ms.  What bounds a reverse pass: up to about 50
 // gates HBM (and address translation where nine window qubits lie above a 2 MiB
-// page), beyond that vector issue (69 % busy at 184 gates) and the LDS traffic
+// page), beyond that vector issue (75 % busy at 184 gates) and the LDS traffic
 // between stages.
 //
 // What the generated code does about arithmetic, the second cost:
@@ -534,7 +534,7 @@ bool tile_kernel(bool dbl, const TileShape& sh, const std::vector<Gate>& gates, 
     if (dir == 1) std::reverse(stages.begin(), stages.end());
 
     // Layouts: the load, one per stage, the store.  Loads and stores keep the
-    // lowest bits in the lanes (128-byte runs).  The two wave bits of every
+    // lowest bits in the lanes (runs of 128 or 64 bytes).  The two wave bits of every
     // layout are chosen so that as few layout changes as possible move data
     // between waves (those need barriers): a shortest path over the pairs.
     struct Node {

@@ -364,8 +364,8 @@ bool plan_tiles(int n, const std::vector<Gate>& gates, const TileLimits& lim, st
 // 2^R amplitudes per thread and vector, reads and writes the state once and
 // applies all gates of the window, in stages that each keep another R of the
 // T window bits in registers; the vectors change layout between stages
-// through LDS.  The amplitudes of a wave's access are runs of 128 bytes: the
-// 2^low lowest ones are in every window.
+// through LDS.  The amplitudes of a wave's access are runs of 128 bytes (64 in the
+// 12-qubit tiles of complex64): the 2^low lowest ones are in every window.
 struct TileShape {
     int T, R, low;
 };
@@ -590,8 +590,11 @@ hipError_t batch_set_lds_limit();
 // block stages a coset of 2^kMidWin amplitudes in LDS, runs the pass's program
 // there and writes it back.
 constexpr int kMidWin = 12;
-// States of the plan's beam search: 4 find the passes that 48 do up to 19 qubits x 16
-// layers, in a tenth of the time (0.4 against 3.6 ms, which a first evaluation waits for).
+// States of the plan's beam search, of 4 to 16 layers: 4 find the passes that 48 do
+// up to 20 qubits, but for 18 and 19 qubits x 8 layers (5 against 4), in a tenth of
+// the time (19 x 16 0.3 against 2.4 ms, which a first evaluation waits for); above
+// they find one or two more (24 x 8 8 against 6, 24 x 16 12 against 11; the 10-qubit
+// windows of a greedy plan 9 and 16).
 constexpr int kMidPlanWidth = 4;
 constexpr int kMidLow = 2;
 constexpr int kMidMaxQubits = 24;
