@@ -25,9 +25,9 @@
 // request, which uses one CU at one wave per SIMD (complex64: two at 13 qubits);
 // vector instructions issue in 45 % of the kernel's cycles (complex128 35 %).  A
 // gate per barrier with the state read and written in LDS for each took, per call:
-// 12 qubits x 4 layers complex64 388 us, now 129 (109 in the kernel); 24 requests
-// of 8 to 13 qubits 1745 us, now 614; 4 states of 14 to 16 qubits (10-qubit windows
-// before) 1160 us, now 690; 12 qubits, excitations, complex128 439 us, now 215.
+// 12 qubits x 4 layers complex64 388 us, now 130 (106 in the kernel); 24 requests
+// of 8 to 13 qubits 1745 us, now 609; 4 states of 14 to 16 qubits (10-qubit windows
+// before) 1160 us, now 683; 12 qubits, excitations, complex128 439 us, now 215.
 // Rows without a branch beat a switch per op (156 against 240 us at 12 qubits:
 // the arms of a switch cost copies of the 64 registers of psi and lam); rows of
 // CNOTs alone leave early (136).
